@@ -74,18 +74,27 @@ struct Smem {
   // fits in the CU's 160 KB of LDS beside the rest: it then lives in a
   // per-workgroup area of device memory (rg), accessed through r_ld / r_st.
   static constexpr bool RG = NT > kMaxNT;
-  double R[RG ? 1 : G::NP * G::LDR];         // factor store, [col][row]
+  // factor store, [col][row]; or the panels of the blocked QR (NT of NP x 16)
+  double R[RG ? 1 : G::NP * G::LDR];
   double E[ELDS ? G::NP * G::LDR : 1];       // staged operand (sweep: swizzled E; pair: [row][col])
-  double cand[2][G::P][G::NP];               // pivot candidate columns
-  double vbuf[G::KB][G::NP];                 // exp(alpha f) of the slices in flight
+  union {
+    struct {
+      double cand[2][G::P][G::NP];           // pivot candidate columns
+      double vbuf[G::KB][G::NP];             // exp(alpha f) of the slices in flight
+    };
+    double tw[NT * 256];                     // triangular factors of the blocked QR's panels
+  };
   double tau[G::NP];
   double dnew[G::NP];                        // |diag R| of the last QR
   double dcur[G::NP];                        // D of the current factorization
+  double red_diag[G::NP];                    // diag R of the blocked QR
   double ckey[2][G::P];
   double red[2][G::P];
   int ccol[2][G::P];
   int perm[G::NP];                           // perm[j] = column pivoted at step j
   int sinv[G::NP];                           // sinv[c] = step at which c was pivoted
+  int sperm[G::NP];                          // norm sort: sperm[j] = column at place j
+  int srank[G::NP];                          //            srank[c] = place of column c
   int ired[2 * G::P];
   int item;
   double* rg;  // the factor store in device memory (RG)
@@ -1024,6 +1033,8 @@ __device__ __forceinline__ void ge_solve(const Lane& L, const int n, RM<NT, P>& 
   back_subst<NT, P, ELDS>(L, n, S, Y);
 }
 
+#include "sdq_block.hpp"
+
 // left operand of R P^T: column c, rows <= s_c
 template <int NT, int P, bool ELDS>
 struct RPtOp {
@@ -1465,6 +1476,167 @@ __device__ __forceinline__ int jsvd_udt(const Lane& L, const int n, Smem<NT, P, 
   return failed;
 }
 
+
+// Acceptance of a norm-sorted QR: R's rows may exceed its diagonal by this
+// factor (a pivoted QR's never do).  Up to kSortPasses attempts, each with
+// the columns in the order of the last one's diagonal, then the pivoted QR.
+// Measured against 113-bit arithmetic (n = 16 .. 64, ordered and random
+// fields, chains with |G| up to 400): without the test G(tau, 0) is up to
+// 70 times further off than with pivoting (a chain's first blocks, whose
+// columns are not graded yet), with it the errors scatter around the pivoted
+// QR's by a factor of two either way; one to four of a chain's blocks need a
+// second pass, and none of those chains a pivoted block.
+constexpr double kSortedGrowth = 4.0;
+constexpr int kSortPasses = 4;
+
+// Stabilization of one block by the norm-sorted blocked QR: on entry W is the
+// block's product with U (D not yet applied: dcol is the column's scale), T
+// the current T; on return W = U, T the new T, S.dnew = D, *sgn the sign of
+// det U.  W's columns are scaled by powers of two to unit size, sorted by the
+// norm of W D and factorized as they stand; T's rows follow the sort and take
+// the scales.  T is in registers (sort_t moves its rows while the factor store
+// is free) or in the workgroup's scratch (load_t gathers its rows in the order
+// S.sperm); keep_t takes the new T.
+template <int NT, bool ELDS, class SortT, class LoadT, class KeepT>
+__device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>& S, RM<NT, NT>& Wm,
+                                                 double dcol, double* sgn, SortT sort_t, LoadT load_t,
+                                                 KeepT keep_t) {
+  using G = Geo<NT, NT>;
+  double(&W)[NT][4] = Wm.v[0];
+  double key, scale;
+  {
+    const Lane L = lane_id_per_item();
+    double mx = 0.0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mx = fmax(mx, fabs(W[t][r]));
+    mx = max_col(mx);
+    const double sc = pow2_scale(mx), usc = pow2_unscale(mx);
+    double sp[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        W[t][r] *= sc;
+        sp[r] = fma(W[t][r], W[t][r], sp[r]);
+      }
+    const double ss = sum_col((sp[0] + sp[1]) + (sp[2] + sp[3]));
+    scale = dcol * usc;
+    key = sqrt(ss) * scale;
+  }
+  bool sorted = false;
+#pragma unroll 1
+  for (int pass = 0;; ++pass) {
+    Lane L = lane_id_per_item();
+    const int col = 16 * L.w + L.cl;
+    const bool live = col < n;
+    key = key >= 0.0 ? key : 0.0;  // NaN -> 0
+    if (!live) key = -1.0;         // the padding columns stay last, in their order
+    // (red_diag: no wave reads it between the growth test and the next QR)
+    if (L.g == 0) S.red_diag[col] = key;
+    const int from = pass == 0 ? col : S.sperm[col];
+    __syncthreads();
+    int before = 0;
+#pragma unroll 16
+    for (int i = 0; i < G::NP / 4; ++i) {
+      const int c = L.g + 4 * i;
+      const double kc = S.red_diag[c];
+      before += (kc > key || (kc == key && c < col)) ? 1 : 0;
+    }
+    const int rank = live ? (int)sum_col((double)before) : col;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = row_of(L, t, r);
+        S.R[rank * G::LDR + row] = live ? W[t][r] : (row == col ? 1.0 : 0.0);
+      }
+    if (L.g == 0) {
+      S.dcur[rank] = live ? scale : 1.0;
+      S.srank[col] = rank;
+      S.sperm[rank] = from;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) W[t][r] = S.R[col * G::LDR + row_of(L, t, r)];
+    scale = S.dcur[col];
+    sort_t();
+    block_qr<NT, 0>(L, S, W, nullptr);
+    // growth test: |R_ic| <= gamma |R_ii| in the original scales
+    L = lane_id_per_item();
+    for (int t = L.t; t < G::NP; t += G::THREADS) S.dnew[t] = fabs(S.red_diag[t]) * S.dcur[t];
+    int bad = 0;
+    const double* pw = S.R + L.w * (NT * kTile);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+      if (t <= L.w) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = row_of(L, t, r);
+          const double x = pw[kTile * t + tile_idx(L.g + 4 * r, L.cl)];
+          const double lim = kSortedGrowth * fabs(S.red_diag[row]) * S.dcur[row];
+          if (row < col && fabs(x) * scale > lim) bad = 1;
+        }
+      }
+    const bool any = __any(bad && live);
+    if (L.l == 0) S.ired[L.w] = any ? 1 : 0;
+    __syncthreads();
+    int failed = 0;
+#pragma unroll
+    for (int q = 0; q < NT; ++q) failed |= S.ired[q];
+    sorted = !__builtin_amdgcn_readfirstlane(failed);
+    if (sorted) break;
+    block_form<NT, true>(L, S, W);  // Q R, the scaled columns themselves
+    if (pass == kSortPasses - 1) break;
+    key = S.dnew[col];
+  }
+  const Lane L = lane_id_per_item();
+  if (sorted) {
+    *sgn = (n & 1) ? -1.0 : 1.0;  // n reflectors (the padding's do not count)
+    RM<NT, NT>& T = load_t();
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) T.v[0][t][r] *= S.dcur[row_of(L, t, r)];
+    // T <- D^-1 R T, R upper triangular
+    d4 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int tk = 0; tk < NT; ++tk)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int ti = 0; ti <= tk; ++ti) {
+          double a = S.R[(tk * NT + ti) * kTile + tile_idx(L.cl, L.g + 4 * r)];
+          if (ti == tk) a = L.cl <= L.g + 4 * r ? a : 0.0;
+          acc[ti] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, T.v[0][tk][r], acc[ti], 0, 0, 0);
+        }
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) T.v[0][t][r] = acc[t][r] / S.dnew[row_of(L, t, r)];
+    keep_t(T);
+    block_form<NT, false>(L, S, W);
+  } else {
+    __syncthreads();  // the panels are read: S.R may be overwritten
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) W[t][r] *= scale;
+    cpqr<NT, NT, ELDS>(L, n, Wm, S);
+    diag_r<NT, NT, ELDS>(L, n, S);
+    *sgn = refl_sign<NT, NT, ELDS>(L, n, S);
+    RM<NT, NT>& T = load_t();
+    update_t<NT, NT, ELDS>(L, S, T);
+    keep_t(T);
+    form_q<NT, NT, ELDS>(L, n, S, Wm);
+  }
+}
+
 // DENSE: the slices are the dense matrices at I.field (B_q at
 // field + (q-1) n n; forward sweeps, and backward ones over B_q^T),
 // staged through S.E one at a time when ELDS, else read from global memory.
@@ -1473,11 +1645,14 @@ __device__ __forceinline__ int jsvd_udt(const Lane& L, const int n, Smem<NT, P, 
 // registers only for its update (after the QR, before Q is formed, while
 // the working matrix is parked in LDS), which frees one register matrix.
 struct NoT {};
-template <int NT, int P, bool ELDS, bool SVD = false, bool DENSE = false, bool TG = false, bool PSW = false>
+// FAST: the norm-sorted blocked QR (stabilize_sorted), one wave per tile.
+template <int NT, int P, bool ELDS, bool SVD = false, bool DENSE = false, bool TG = false, bool PSW = false,
+          bool FAST = false>
 __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, const Inst& I, const int flags,
                           const int jpair, double* tscr = nullptr) {
   static_assert(!PSW || (DENSE && !ELDS), "pre-swizzled slices are dense and read from device memory");
   static_assert(!(TG && SVD), "the SVD stabilizer keeps T in registers");
+  static_assert(!FAST || (P == NT && !SVD), "the blocked QR needs one wave per column tile");
   using G = Geo<NT, P>;
   // the SVD stabilizer keeps T in S.E, so E is read from its global copy
   constexpr bool EST = ELDS && !SVD && !DENSE;
@@ -1589,12 +1764,14 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
         }
       }
     }
+    if constexpr (!FAST) {
 #pragma unroll
-    for (int c = 0; c < CT; ++c)
+      for (int c = 0; c < CT; ++c)
 #pragma unroll
-      for (int ti = 0; ti < NT; ++ti)
+        for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) W.v[c][ti][r] *= dcol[c];
+          for (int r = 0; r < 4; ++r) W.v[c][ti][r] *= dcol[c];
+    }
     double* dst = nullptr;
     if (flags & SW_STORE) dst = adj ? (I.cka + (size_t)b * sd) : (I.ckf + (size_t)s * sd);
     else if ((flags & SW_LAST) && s == nb - 1) dst = I.fin;
@@ -1607,6 +1784,58 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
       svd_failed |= jsvd_udt<NT, P>(L, n, S, W, T, &ps);
       sgn_u = sgn_run * ps;
       sgn_run = sgn_u;
+    } else if constexpr (FAST) {
+      if constexpr (TG) {
+        RM<NT, P> Tr;
+        stabilize_sorted<NT, ELDS>(
+            n, S, W, dcol[0], &sgn_u, [] {},
+            [&]() -> RM<NT, P>& {
+              // rows in sorted order: from the scratch's register layout, from
+              // forward stage jpair, or of the identity
+              const Lane L = lane_id_per_item();
+              const int tcol = 16 * L.w + L.cl;
+              const auto* q = tsrc == 2 ? gmem(tscr) + L.w * 64 + L.cl
+                                        : gmem(I.ckf) + (size_t)(jpair - 1) * sd + (size_t)n * n + min(tcol, n - 1);
+#pragma unroll
+              for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                  const int src = S.sperm[row_of(L, ti, r)];
+                  const double unit = src == tcol ? 1.0 : 0.0;
+                  if (tsrc == 2) {
+                    Tr.v[0][ti][r] = q[(size_t)((src >> 4) * 4 + ((src >> 2) & 3)) * 64 * P + (src & 3) * 16];
+                  } else if (tsrc == 1) {
+                    const double x = q[(size_t)min(src, n - 1) * n];
+                    Tr.v[0][ti][r] = (src < n && tcol < n) ? x : unit;
+                  } else {
+                    Tr.v[0][ti][r] = unit;
+                  }
+                }
+              return Tr;
+            },
+            [&](RM<NT, P>& Tn) {
+              if (s + 1 < s_hi) scr_store<NT, P>(L, Tn, tscr);
+              tsrc = 2;
+              if (dst) store_rm<NT, P>(L, Tn, dst + (size_t)n * n, n);
+            });
+      } else {
+        stabilize_sorted<NT, ELDS>(
+            n, S, W, dcol[0], &sgn_u,
+            [&] {
+              const Lane L = lane_id_per_item();
+              const int base = (16 * L.w + L.cl) * G::LDR;
+#pragma unroll
+              for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) S.R[base + S.srank[row_of(L, ti, r)]] = T.v[0][ti][r];
+              __builtin_amdgcn_wave_barrier();
+#pragma unroll
+              for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) T.v[0][ti][r] = S.R[base + row_of(L, ti, r)];
+            },
+            [&]() -> RM<NT, P>& { return T; }, [](RM<NT, P>&) {});
+      }
     } else if constexpr (TG) {
       cpqr<NT, P, ELDS>(L, n, W, S);
       diag_r<NT, P, ELDS>(L, n, S);
@@ -1691,7 +1920,8 @@ __device__ __forceinline__ void pair_equal(const Lane& L, Smem<NT, P, ELDS>& S, 
 }
 
 // The sweep kernel's work loop: items from the queue until it is empty.
-template <int NT, int P, bool ELDS, bool SVD = false, bool DENSE = false, bool TG = false, bool PSW = false>
+template <int NT, int P, bool ELDS, bool SVD = false, bool DENSE = false, bool TG = false, bool PSW = false,
+          bool FAST = false>
 __device__ __forceinline__ void sweep_items(const Inst* __restrict__ insts, const SweepItem* __restrict__ items,
                                             int count, Queue* q, double* tscr) {
   __shared__ Smem<NT, P, ELDS> S;
@@ -1715,15 +1945,16 @@ __device__ __forceinline__ void sweep_items(const Inst* __restrict__ insts, cons
     if (it >= count) break;
     const SweepItem wi = items[it];
     const Inst I = insts[wi.inst];
-    sweep_one<NT, P, ELDS, SVD, DENSE, TG, PSW>(L, S, I, wi.flags, wi.j, ts);
+    sweep_one<NT, P, ELDS, SVD, DENSE, TG, PSW, FAST>(L, S, I, wi.flags, wi.j, ts);
   }
 }
 
-template <int NT, int P, bool ELDS, bool SVD = false, bool DENSE = false, bool TG = false, bool PSW = false>
+template <int NT, int P, bool ELDS, bool SVD = false, bool DENSE = false, bool TG = false, bool PSW = false,
+          bool FAST = false>
 __global__ __launch_bounds__(64 * P, minb_for(NT)) void k_sweep(const Inst* __restrict__ insts,
                                                             const SweepItem* __restrict__ items,
                                                             int count, Queue* q, double* tscr) {
-  sweep_items<NT, P, ELDS, SVD, DENSE, TG, PSW>(insts, items, count, q, tscr);
+  sweep_items<NT, P, ELDS, SVD, DENSE, TG, PSW, FAST>(insts, items, count, q, tscr);
 }
 
 

@@ -17,6 +17,8 @@ namespace sdq {
   hipError_t dense_info_nt##N(KernelInfo*);                                                      \
   hipError_t launch_prod_nt##N(const Inst*, const SweepItem*, int, Queue*, int, hipStream_t);    \
   hipError_t prod_info_nt##N(KernelInfo*);                                                       \
+  hipError_t launch_fast_sweep_nt##N(int, const Inst*, const SweepItem*, int, Queue*, int, double*, hipStream_t); \
+  hipError_t fast_sweep_info_nt##N(int, KernelInfo*);                                             \
   hipError_t launch_dense_pair_nt##N(const Inst*, const PairItem*, int, const int32_t*, Queue*, int, \
                                      hipStream_t);                                               \
   hipError_t dense_pair_info_nt##N(KernelInfo*);
@@ -43,6 +45,11 @@ hipError_t launch_prod_nt9(const Inst*, const SweepItem*, int, Queue*, int, hipS
 hipError_t launch_sweep(int nt, int variant, const Inst* inst, const SweepItem* items, int count,
                         Queue* q, int grid, double* tscr, hipStream_t s) {
   if (nt == kSweepMaxNT) return launch_sweep_nt9(variant, inst, items, count, q, grid, tscr, s);
+  if (variant >= kFastHbm) {
+#define C(N) launch_fast_sweep_nt##N(variant, inst, items, count, q, grid, tscr, s)
+    SDQ_SWITCH(C)
+#undef C
+  }
   if (variant == 3) {
 #define C(N) launch_dense_sweep_nt##N(inst, items, count, q, grid, s)
     SDQ_SWITCH(C)
@@ -96,6 +103,11 @@ hipError_t kernel_info(int kind, int nt, int variant, KernelInfo* out) {
   if (nt == kSweepMaxNT) return kernel_info_nt9(kind, variant, out);
   if (kind == KK_PROD) {
 #define C(N) prod_info_nt##N(out)
+    SDQ_SWITCH(C)
+#undef C
+  }
+  if (kind == KK_SWEEP && variant >= kFastHbm) {
+#define C(N) fast_sweep_info_nt##N(variant, out)
     SDQ_SWITCH(C)
 #undef C
   }

@@ -81,7 +81,10 @@ struct Plan {
   // call, over the same instances, made them (the layout is a function of
   // the instances, so the pointers come out the same)
   bool swz_ready = false;
-  bool dense = false;  // every instance has dense slices (sweep variant 3)
+  bool dense = false;  // every instance has dense slices
+  // the column-pivoted QR in every block: where the factors are the result,
+  // and for the single-decomposition schemes
+  bool pivoted = false;
   // block products (k_prod) of the tile classes in bprod_mask (bit nt), run
   // before those classes' sweeps, which are then variant 6
   std::vector<SweepItem> prod;
@@ -284,7 +287,7 @@ void order_items(const std::vector<Inst>& inst, std::vector<ItemT>& items,
 }
 
 const sdq::KernelInfo& info(sdq_ctx* ctx, int kind, int nt, int variant) {
-  const long long key = (long long)kind * 1000 + nt * 10 + variant;
+  const long long key = ((long long)kind * 100 + nt) * 100 + variant;
   auto it = ctx->info_cache.find(key);
   if (it == ctx->info_cache.end()) {
     sdq::KernelInfo ki{};
@@ -483,11 +486,18 @@ sdq_status build_plan(sdq_ctx* ctx, Plan& P, int32_t* status, int count, Built& 
     // (above kMaxNT tiles and up to kSweepMaxNT: the one-workgroup sweep with
     // T and the factor store in workgroup scratch, variant 4; over block
     // products, variant 6)
+    const bool bprod = ((P.bprod_mask >> r.nt) & 1u) != 0;
+    const bool fast = !P.pivoted && ctx->stab == SDQ_STAB_QR && r.nt <= sdq::kMaxNT;
+    const int tuned = r.nt <= sdq::kMaxNT ? ctx->tune[r.nt].variant : 4;
     const int variant = sweep_is_gang(r.nt) ? 0
-                        : ((P.bprod_mask >> r.nt) & 1u) ? 6
+                        : fast ? (bprod               ? sdq::kFastProd
+                                  : P.dense           ? sdq::kFastDense
+                                  : tuned == 1 || tuned == 5 ? sdq::kFastLds
+                                                      : sdq::kFastHbm)
+                        : bprod ? 6
                         : r.nt > sdq::kMaxNT ? 4
                         : P.dense ? 3
-                        : (ctx->stab == SDQ_STAB_SVD ? 2 : ctx->tune[r.nt].variant);
+                        : (ctx->stab == SDQ_STAB_SVD ? 2 : tuned);
     const int grid = grid_for(ctx, sdq::KK_SWEEP, r.nt, variant, r.count);
     // classes may run concurrently: each launch gets its own T scratch
     const size_t toff = B.tscr_doubles;
@@ -896,6 +906,7 @@ sdq_status sdq_greens(sdq_ctx* ctx, const sdq_instance* inst, int32_t count, sdq
   st = alloc_fin(ctx, inst, count, off);
   if (st) return st;
   Plan P;
+  P.pivoted = scheme == SDQ_INV_PLAIN;
   // Block products first (k_prod: every block of k slices of every chain
   // multiplied out at once), then the sweep over them with one
   // factorization each: the same stabilized product (Sec. 4.1), with the
@@ -1027,6 +1038,7 @@ sdq_status sdq_greens_noalloc(sdq_ctx* ctx, const sdq_instance* inst, int32_t co
                 "sdq_greens_noalloc: the batch needs more than the " + std::to_string(sdq::kNoAllocBytes >> 20) +
                     " MiB of fixed scratch (" + std::to_string(o_tscr) + " bytes before the plan); split it");
   Plan P;
+  P.pivoted = scheme == SDQ_INV_PLAIN;
   for (int i = 0; i < count; ++i) {
     Inst I = base_inst(inst[i]);
     I.scheme = scheme == SDQ_INV_PLAIN ? 1 : 0;
@@ -1236,6 +1248,7 @@ sdq_status sdq_greens_tdisp(sdq_ctx* ctx, const sdq_instance* inst, int32_t coun
   if (st) return st;
   double* ck = (double*)ctx->d_ck.p;
   Plan P;
+  P.pivoted = plain;
   P.llist.assign(l_list, l_list + n_l);
   P.swz_inv = plain;
   for (int i = 0; i < count; ++i) {
@@ -1860,6 +1873,7 @@ sdq_status sdq_chain_udt(sdq_ctx* ctx, const sdq_instance* inst, int32_t count, 
   HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
   const int n = inst[0].n;
   Plan P;
+  P.pivoted = true;
   for (int i = 0; i < count; ++i) {
     Inst I = base_inst(inst[i]);
     I.u_out = u + (size_t)i * n * n;
