@@ -416,6 +416,16 @@ __device__ __forceinline__ void panel_factor(SM& S, double (&b)[NT][4], const in
   }
 }
 
+// the padding columns as unit vectors
+template <int NT>
+__device__ __forceinline__ void pad_unit(const Lane& L, const int n, double (&b)[NT][4]) {
+  const int col = 16 * L.w + L.cl;
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) b[t][r] = col < n ? b[t][r] : (16 * t + L.g + 4 * r == col ? 1.0 : 0.0);
+}
+
 // W = Q R for the register matrix W as its columns stand (padding columns:
 // unit vectors), Q and R left in LDS in panels; diag R in S.red_diag.  With
 // YN > 0 the same Q^T is applied to the register matrix Y, whose rows are in

@@ -914,125 +914,6 @@ __device__ __forceinline__ void back_subst(const Lane& L, const int n, const Sme
   });
 }
 
-// Y <- A^{-1} Y for the register matrices A (n x n, padding zero) and Y, by
-// Gaussian elimination with column pivoting: at step j the pivot is the
-// live column of largest |A[j][c]| (ties: smallest column), its entries
-// below row j divided by the pivot are the multipliers l_r, and row j times
-// l_r is subtracted from every row r > j of the other live columns and of Y
-// (so Y becomes L^{-1} Y on the way; L itself is not kept).  This is Gaussian
-// elimination with partial pivoting applied to A^T, arranged like cpqr: the
-// rows are static per tile (row j of every column is fetched from a fixed
-// lane group), each wave offers its best column through LDS and one barrier
-// per step settles the pivot, and columns are never moved.  Then U (U[i][j]
-// = A[i][perm j], i <= j) is parked in S.R by original column, as cpqr parks
-// R, and Y <- U^{-1} Y by back substitution; the rows of the result are in
-// pivot order: A^{-1} Y [S.perm[s]][c] = Y[s][c].  A is destroyed.  A
-// singular A leaves non-finite entries in Y.
-template <int NT, int P, bool ELDS>
-__device__ __forceinline__ void ge_solve(const Lane& L, const int n, RM<NT, P>& A, RM<NT, P>& Y, Smem<NT, P, ELDS>& S) {
-  using G = Geo<NT, P>;
-  constexpr int CT = G::CT;
-  int ps[CT];  // -1: live, not yet chosen; else the step (padding: own index)
-#pragma unroll
-  for (int c = 0; c < CT; ++c) {
-    const int col = col_of<NT, P>(L, c);
-    ps[c] = (tile_ok<NT, P>(L, c) && col < n) ? -1 : col;
-  }
-  int buf = 0;
-  static_for<NT>([&](auto tjc) {
-    constexpr int TJ = decltype(tjc)::value;
-    const int jend = 16 * TJ + 16 < n ? 16 * TJ + 16 : n;
-    for (int j = 16 * TJ; j < jend; ++j) {
-      const int jj = j - 16 * TJ, gj = jj & 3, rj = jj >> 2;
-      const int jsrc = ((gj << 4) | L.cl) << 2;
-      // row j of each column and of Y, from the lane group holding it
-      double ajc[CT], yjc[CT];
-#pragma unroll
-      for (int c = 0; c < CT; ++c) {
-        ajc[c] = lane_fetch(jsrc, pick4(A.v[c][TJ], rj));
-        yjc[c] = lane_fetch(jsrc, pick4(Y.v[c][TJ], rj));
-      }
-      // ---- wave-local candidate: largest |A[j][c]| of this wave's live columns
-      double key = -1.0;
-#pragma unroll
-      for (int c = 0; c < CT; ++c) {
-        const double kc = ps[c] < 0 ? pivot_key(fabs(ajc[c]), col_of<NT, P>(L, c)) : -1.0;
-        key = c == 0 ? kc : key_max(key, kc);
-      }
-      key = row_max16(key);
-      const int bc = pivot_col(key);
-#pragma unroll
-      for (int c = 0; c < CT; ++c) {
-        if (key >= 0.0 && ps[c] < 0 && col_of<NT, P>(L, c) == bc) {
-#pragma unroll
-          for (int ti = TJ; ti < NT; ++ti)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) S.cand[buf][L.w][row_of(L, ti, r)] = A.v[c][ti][r];
-        }
-      }
-      double pk = key;
-      if constexpr (P > 1) {
-        if (L.l == 0) S.ckey[buf][L.w] = key;
-        __syncthreads();
-        pk = S.ckey[buf][0];
-#pragma unroll
-        for (int q = 1; q < P; ++q) pk = key_max(pk, S.ckey[buf][q]);
-      } else {
-        __builtin_amdgcn_wave_barrier();
-      }
-      const int pc = pivot_col(pk);
-      const int pw = (pc >> 4) % P;
-      const double* xc = S.cand[buf][pw];
-      const double rinv = 1.0 / xc[j];
-      // multipliers of the rows below j (zero at and above j)
-      double ml[NT][4];
-#pragma unroll
-      for (int ti = TJ; ti < NT; ++ti)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ml[ti][r] = xc[row_of(L, ti, r)];
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int ti = TJ; ti < NT; ++ti)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          ml[ti][r] = (ti > TJ || L.g + 4 * r > jj) ? ml[ti][r] * rinv : 0.0;
-#pragma unroll
-      for (int c = 0; c < CT; ++c) {
-        const bool upd = ps[c] < 0 && col_of<NT, P>(L, c) != pc;
-        const double a = upd ? ajc[c] : 0.0;
-#pragma unroll
-        for (int ti = TJ; ti < NT; ++ti)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            A.v[c][ti][r] = fma(-ml[ti][r], a, A.v[c][ti][r]);
-            Y.v[c][ti][r] = fma(-ml[ti][r], yjc[c], Y.v[c][ti][r]);
-          }
-        if (ps[c] < 0 && col_of<NT, P>(L, c) == pc) ps[c] = j;
-      }
-      if (L.t == 0) S.perm[j] = pc;
-      buf ^= 1;
-    }
-  });
-  // ---- park U in LDS by original column (rows <= its step), as cpqr does
-#pragma unroll
-  for (int c = 0; c < CT; ++c) {
-    if (!tile_ok<NT, P>(L, c)) continue;
-    const int col = col_of<NT, P>(L, c);
-    const bool live = col < n;
-#pragma unroll
-    for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = row_of(L, ti, r);
-        S.R[col * G::LDR + row] = live ? A.v[c][ti][r] : (row == col ? 1.0 : 0.0);
-      }
-    if (L.g == 0) S.sinv[col] = ps[c];
-  }
-  for (int t = n + L.t; t < G::NP; t += G::THREADS) S.perm[t] = t;
-  __syncthreads();
-  back_subst<NT, P, ELDS>(L, n, S, Y);
-}
-
 #include "sdq_block.hpp"
 
 // left operand of R P^T: column c, rows <= s_c
@@ -1091,12 +972,14 @@ __device__ __forceinline__ double perm_sign(const Lane& L, const int n, Smem<NT,
 // the printed factorization, which needs U^T rather than T^{-1}:
 //   1 + U Dm Dp T = U Dp (Dp^{-1} U^T + Dm T),  Dp = max(D,1), Dm = min(D,1)
 //   G = M^{-1} Dp^{-1} U^T,   M = Dp^{-1} U^T + Dm T,
-// M inverted through its pivoted QR, M P = Q R:  G = P R^{-1} Q^T Dp^{-1} U^T.
+// M inverted through a QR (any backward-stable solve serves: the split leaves
+// M with entries of order one):  G = R^{-1} Q^T Dp^{-1} U^T by the blocked QR.
 //   det(1 + U D T) = det U * prod(Dp) * det M.
-// With loh = false the same code runs the single-decomposition scheme
-// (Sec. 5.1 inv_one_plus, mirrored): Dp = 1, Dm = D, M = U^T + D T.
+// With LOH = false the single-decomposition scheme (Sec. 5.1 inv_one_plus,
+// mirrored): Dp = 1, Dm = D, M = U^T + D T, through the pivoted QR.
 // U, T: register matrices (padding: identity); D: S.dcur.  Returns Z with
-// G[S.perm[s]][c] = Z[s][c] (caller writes it out), and log|det|, sign.
+// G[S.perm[s]][c] = Z[s][c] for LOH = false, G = Z for true (caller writes it
+// out), and log|det|, sign.
 template <int NT, int P, bool ELDS, bool LOH = true>
 __device__ __forceinline__ void inv_one_plus(const Lane& L, const int n, Smem<NT, P, ELDS>& S, const RM<NT, P>& U,
                              const RM<NT, P>& T, double sgn_u, RM<NT, P>& Z, double* logdet,
@@ -1135,12 +1018,21 @@ __device__ __forceinline__ void inv_one_plus(const Lane& L, const int n, Smem<NT
       }
   }
   double lsum = 0.0;
-  if constexpr (loh)
-    for (int t = L.t; t < n; t += G::THREADS) lsum += log(fmax(S.dcur[t], 1.0));
-  cpqr<NT, P, ELDS>(L, n, M, S);  // begins with barriers before S.R is overwritten
-  for (int t = L.t; t < n; t += G::THREADS) lsum += log(fabs(S.R[S.perm[t] * G::LDR + t]));
   int neg = 0;
-  for (int t = L.t; t < n; t += G::THREADS) neg += (S.R[S.perm[t] * G::LDR + t] < 0.0);
+  if constexpr (loh) {
+    for (int t = L.t; t < n; t += G::THREADS) lsum += log(fmax(S.dcur[t], 1.0));
+    pad_unit<NT>(L, n, M.v[0]);
+    block_qr<NT, 1>(L, S, M.v[0], Z.v[0]);  // begins with a barrier
+    for (int t = L.t; t < n; t += G::THREADS) {
+      const double d = S.red_diag[t];
+      lsum += log(fabs(d));
+      neg += d > 0.0;  // det Q = (-1)^n
+    }
+  } else {
+    cpqr<NT, P, ELDS>(L, n, M, S);  // begins with barriers before S.R is overwritten
+    for (int t = L.t; t < n; t += G::THREADS) lsum += log(fabs(S.R[S.perm[t] * G::LDR + t]));
+    for (int t = L.t; t < n; t += G::THREADS) neg += (S.R[S.perm[t] * G::LDR + t] < 0.0);
+  }
   // wave sums
   for (int m = 32; m >= 1; m >>= 1) {
     lsum += __shfl_xor(lsum, m);
@@ -1150,8 +1042,13 @@ __device__ __forceinline__ void inv_one_plus(const Lane& L, const int n, Smem<NT
     S.red[0][L.w] = lsum;
     S.ired[G::P + L.w] = neg;
   }
-  const double sq = refl_sign<NT, P, ELDS>(L, n, S);
-  const double sp = perm_sign<NT, P, ELDS>(L, n, S);  // its barrier makes S.red visible
+  double sq = 1.0, sp = 1.0;
+  if constexpr (loh) {
+    __syncthreads();  // S.red, S.ired written
+  } else {
+    sq = refl_sign<NT, P, ELDS>(L, n, S);
+    sp = perm_sign<NT, P, ELDS>(L, n, S);  // its barrier makes S.red visible
+  }
   double ld = 0.0;
   int ng = 0;
   for (int q = 0; q < G::P; ++q) {
@@ -1160,8 +1057,12 @@ __device__ __forceinline__ void inv_one_plus(const Lane& L, const int n, Smem<NT
   }
   *logdet = ld;
   *sign = sgn_u * sq * sp * ((ng & 1) ? -1.0 : 1.0);
-  apply_qt<NT, P, ELDS>(L, n, S, Z);
-  back_subst<NT, P, ELDS>(L, n, S, Z);
+  if constexpr (loh) {
+    block_back_subst<NT>(L, S, Z.v[0]);
+  } else {
+    apply_qt<NT, P, ELDS>(L, n, S, Z);
+    back_subst<NT, P, ELDS>(L, n, S, Z);
+  }
 }
 
 // write G[perm[s]][c] = Z[s][c] (leading n x n block) to global memory
@@ -1910,7 +1811,10 @@ __device__ __forceinline__ void pair_equal(const Lane& L, Smem<NT, P, ELDS>& S, 
   else
     inv_one_plus<NT, P, ELDS, false>(L, n, S, U, T, sgn_u, Z, &ld, &sg);
   if (!all_finite<NT, P>(L, Z) || !isfinite(ld)) bad = 1;
-  if (I.g) store_perm_rows<NT, P, ELDS>(L, n, S, Z, I.g);
+  if (I.g) {
+    if (I.scheme == 0) store_rm<NT, P>(L, Z, I.g, n);
+    else store_perm_rows<NT, P, ELDS>(L, n, S, Z, I.g);
+  }
   if (L.t == 0) {
     if (I.logdet) *I.logdet = ld;
     if (I.sign) *I.sign = sg;
@@ -2168,14 +2072,16 @@ __device__ __forceinline__ void tdisp_outputs(const Lane& L, Smem<NT, P, ELDS>& 
 // i.e. D_L = D1^{-1}, D_R = D2, X_L X_R^{-1} = U1^T U2, U_L^{-1} U_R = T1 T2^T:
 //   Mid = D_Lm (U1^T U2) D_Rp^{-1} + D_Lp^{-1} (T1 T2^T) D_Rm
 //   G(tau,0) = U2 D_Rp^{-1} Mid^{-1} D_Lp^{-1} T1.
-// Then, for requested l inside the block, G(tau_l, 0) = B_l ... G(tau_j, 0)
-// (Sec. 6, propagation form), never across more than k-1 slices.
-template <int NT, int P, bool ELDS, bool DENSE = false>
-__device__ __forceinline__ void pair_tdisp(const Lane& L, Smem<NT, P, ELDS>& S, const Inst& I, const int j,
-                           const int ilo, const int ihi, const int32_t* __restrict__ l_list) {
+// EQUAL: the equal-time G at the same boundary,
+//   [1 + B(tau,0) B(beta,tau)]^{-1} = U2 D_Rp^{-1} Mid^{-1} D_Lm U1^T
+// with the same middle matrix (App. A.1's two factors split as in Sec. 5.1).
+template <int NT, int P, bool ELDS, bool EQUAL>
+__device__ __forceinline__ void pair_middle(const Lane& L, Smem<NT, P, ELDS>& S, const Inst& I, const int j,
+                                            RM<NT, P>& Gm) {
+  static_assert(P == NT, "the blocked QR needs one wave per column tile");
   using G = Geo<NT, P>;
   constexpr int CT = G::CT;
-  const int n = I.n, m = I.m, k = I.k, nb = I.nb;
+  const int n = I.n, nb = I.nb;
   const int64_t sd = stage_doubles(n);
   const double* F = j > 0 ? I.ckf + (size_t)(j - 1) * sd : nullptr;
   const double* A = j < nb ? I.cka + (size_t)j * sd : nullptr;
@@ -2201,13 +2107,14 @@ __device__ __forceinline__ void pair_tdisp(const Lane& L, Smem<NT, P, ELDS>& S, 
     load_lds_rm<NT, P>(L, S.R, B, true);  // T2^T
     gemm_rb<NT, P>(L, [&](int, int, int, int i, int kk) -> double { return S.E[i * G::LDR + kk]; }, B,
                    P2);
-    load_lds_rm<NT, P>(L, S.E, Y, false);  // T1 (right-hand sides)
+    if constexpr (!EQUAL) load_lds_rm<NT, P>(L, S.E, Y, false);  // T1 (right-hand sides)
     __syncthreads();
     stage_to2<NT, P>(L, S.R, U1, S.E, U2, n);  // U2 stays in S.E for the final product
     __syncthreads();
     load_lds_rm<NT, P>(L, S.E, B, false);  // U2
     gemm_rb<NT, P>(L, [&](int, int, int, int i, int kk) -> double { return S.R[kk * G::LDR + i]; }, B,
                    P1);
+    if constexpr (EQUAL) load_lds_rm<NT, P>(L, S.R, Y, true);  // U1^T
   } else {
     load_rm<NT, P>(L, B, U2, n, false);
     gemm_gm<NT, P>(L, U1, n, true, B, P1);
@@ -2231,44 +2138,45 @@ __device__ __forceinline__ void pair_tdisp(const Lane& L, Smem<NT, P, ELDS>& S, 
         P1.v[c][ti][r] = lm * P1.v[c][ti][r] * rpi + lpi * P2.v[c][ti][r] * rm;
       }
     }
-  // Y = D_Lp^{-1} T1 (without LDS staging it is loaded here, after the
-  // products, so that it is not live in registers during them)
-  if constexpr (!ELDS) load_rm<NT, P>(L, Y, T1, n, false);
+  // Y = D_Lp^{-1} T1 or D_Lm U1^T (without LDS staging it is loaded here, after
+  // the products, so that it is not live in registers during them)
+  if constexpr (!ELDS) load_rm<NT, P>(L, Y, EQUAL ? U1 : T1, n, EQUAL);
 #pragma unroll
   for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const double d1 = S.dcur[row_of(L, ti, r)];
-      const double lpi = d1 < 1.0 ? d1 : 1.0;  // D_Lp^{-1}
+      const double f = EQUAL ? 1.0 / (d1 > 1.0 ? d1 : 1.0) : (d1 < 1.0 ? d1 : 1.0);
 #pragma unroll
-      for (int c = 0; c < CT; ++c) Y.v[c][ti][r] *= lpi;
+      for (int c = 0; c < CT; ++c) Y.v[c][ti][r] *= f;
     }
-  // Y <- Mid^{-1} Y by Gaussian elimination with column pivoting (any
-  // backward-stable solve of the middle matrix serves, Sec. 6.1); the rows
-  // of the result come out in pivot order, S.perm
-  __syncthreads();
-  ge_solve<NT, P, ELDS>(L, n, P1, Y, S);
-  // G = U2 D_Rp^{-1} P Z: row s of Z scaled by 1 / max(D2[perm s], 1), then
-  // the product with the columns of U2 gathered by perm
+  // Y <- Mid^{-1} Y through the blocked QR (any backward-stable solve of the
+  // middle matrix serves, Sec. 6.1)
+  pad_unit<NT>(L, n, P1.v[0]);
+  block_qr<NT, 1>(L, S, P1.v[0], Y.v[0]);
+  block_back_subst<NT>(L, S, Y.v[0]);
+  // G = U2 D_Rp^{-1} Y
 #pragma unroll
   for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const double d2 = S.dnew[S.perm[row_of(L, ti, r)]];
+      const double d2 = S.dnew[row_of(L, ti, r)];
       const double rpi = 1.0 / (d2 > 1.0 ? d2 : 1.0);
 #pragma unroll
       for (int c = 0; c < CT; ++c) Y.v[c][ti][r] *= rpi;
     }
+  if constexpr (ELDS)
+    gemm_rb<NT, P>(L, [&](int, int, int, int i, int kk) -> double { return S.E[i * G::LDR + kk]; }, Y, Gm);
+  else
+    gemm_gm<NT, P>(L, U2, n, false, Y, Gm);
+}
+
+// G(tau_j, 0) and the outputs of stage pair j.
+template <int NT, int P, bool ELDS, bool DENSE = false>
+__device__ __forceinline__ void pair_tdisp(const Lane& L, Smem<NT, P, ELDS>& S, const Inst& I, const int j,
+                                           const int ilo, const int ihi, const int32_t* __restrict__ l_list) {
   RM<NT, P> Gm;
-  if constexpr (ELDS) {
-    gemm_rb<NT, P>(L,
-                   [&](int, int, int, int i, int s) -> double {
-                     return s < n ? S.E[i * G::LDR + S.perm[s]] : 0.0;
-                   },
-                   Y, Gm);
-  } else {
-    gemm_gm_perm<NT, P>(L, U2, n, S.perm, Y, Gm);
-  }
+  pair_middle<NT, P, ELDS, false>(L, S, I, j, Gm);
   if (!all_finite<NT, P>(L, Gm) && L.l == 0 && I.status) atomicOr(I.status, kStatusRange);
   tdisp_outputs<NT, P, ELDS, DENSE>(L, S, I, j, ilo, ihi, l_list, Gm);
 }
@@ -2403,102 +2311,24 @@ __device__ __forceinline__ void pair_tdisp_plain(const Lane& L, Smem<NT, P, ELDS
 }
 
 // G_{jk+1} = [1 + B(tau_j,0) B(beta,tau_j)]^{-1} from forward stage j and
-// backward stage j (App. A.1): udt(D1 (T1 T2^T) D2) = u d t, U = U1 u,
-// T = t U2^T, then Loh's equal-time inversion; written to S.R row-major
-// ([row][col], padding as identity), ends with a barrier.
+// backward stage j, written to S.R row-major ([row][col], padding as
+// identity), ends with a barrier.
 template <int NT, int P, bool ELDS>
 __device__ __forceinline__ void block_start_g(const Lane L, Smem<NT, P, ELDS>& S, const Inst& I, const int j) {
   using G = Geo<NT, P>;
-  constexpr int CT = G::CT;
-  const int n = I.n, nb = I.nb;
-  const int64_t sd = stage_doubles(n);
-  const double* F = j > 0 ? I.ckf + (size_t)(j - 1) * sd : nullptr;
-  const double* A = j < nb ? I.cka + (size_t)j * sd : nullptr;
-  const double* U1 = F;
-  const double* T1 = F ? F + (size_t)n * n : nullptr;
-  const double* D1 = F ? F + 2 * (size_t)n * n : nullptr;
-  const double* U2 = A;
-  const double* T2 = A ? A + (size_t)n * n : nullptr;
-  const double* D2 = A ? A + 2 * (size_t)n * n : nullptr;
-
-  RM<NT, P> B, Mm;
-  if constexpr (ELDS) {
-    __syncthreads();
-    stage_mat<NT, P, ELDS>(L, S, T2, n);
-    __syncthreads();
-    load_rm_staged<NT, P, ELDS>(L, S, B, true);  // T2^T
-    __syncthreads();
-    stage_mat<NT, P, ELDS>(L, S, T1, n);
-    __syncthreads();
-    gemm_rb<NT, P>(L, [&](int, int, int, int i, int kk) -> double { return S.E[i * G::LDR + kk]; }, B,
-                   Mm);
-  } else {
-    load_rm<NT, P>(L, B, T2, n, true);
-    gemm_gm<NT, P>(L, T1, n, false, B, Mm);
-  }
-  // D1 (in S.tau) and D2 (in S.dcur), both free until the QR below
-  __syncthreads();
-  for (int t = L.t; t < G::NP; t += G::THREADS) {
-    S.tau[t] = (D1 && t < n) ? gmem(D1)[t] : 1.0;
-    S.dcur[t] = (D2 && t < n) ? gmem(D2)[t] : 1.0;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int c = 0; c < CT; ++c) {
-    const double d2 = S.dcur[col_of<NT, P>(L, c) < G::NP ? col_of<NT, P>(L, c) : 0];
-#pragma unroll
-    for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) Mm.v[c][ti][r] *= S.tau[row_of(L, ti, r)] * d2;
-  }
-  __syncthreads();
-  cpqr<NT, P, ELDS>(L, n, Mm, S);
-  diag_r<NT, P, ELDS>(L, n, S);
-  RM<NT, P> u, Tm, Um;
-  form_q<NT, P, ELDS>(L, n, S, u);
-  if constexpr (ELDS) {
-    __syncthreads();
-    stage_mat<NT, P, ELDS>(L, S, U2, n);
-    __syncthreads();
-    load_rm_staged<NT, P, ELDS>(L, S, B, true);  // U2^T
-    __syncthreads();
-    stage_mat<NT, P, ELDS>(L, S, U1, n);
-    __syncthreads();
-  } else {
-    load_rm<NT, P>(L, B, U2, n, true);  // U2^T
-  }
-  gemm_rb<NT, P>(L, RPtOp<NT, P, ELDS>{S}, B, Tm);
-#pragma unroll
-  for (int c = 0; c < CT; ++c)
-#pragma unroll
-    for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) Tm.v[c][ti][r] /= S.dnew[row_of(L, ti, r)];
-  if constexpr (ELDS) {
-    gemm_rb<NT, P>(L, [&](int, int, int, int i, int kk) -> double { return S.E[i * G::LDR + kk]; }, u,
-                   Um);
-  } else {
-    gemm_gm<NT, P>(L, U1, n, false, u, Um);
-  }
-  for (int t = L.t; t < G::NP; t += G::THREADS) S.dcur[t] = S.dnew[t];
+  const int n = I.n;
   RM<NT, P> Z;
-  double ld, sg;
-  inv_one_plus<NT, P, ELDS>(L, n, S, Um, Tm, 1.0, Z, &ld, &sg);
-  // G_l into LDS, row-major [row][col]
   __syncthreads();
+  pair_middle<NT, P, ELDS, true>(L, S, I, j, Z);
+  __syncthreads();
+  const int col = col_of<NT, P>(L, 0);
 #pragma unroll
-  for (int c = 0; c < CT; ++c) {
-    if (!tile_ok<NT, P>(L, c)) continue;
-    const int col = col_of<NT, P>(L, c);
+  for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
-    for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int s = row_of(L, ti, r);
-        const int row = s < n ? S.perm[s] : s;
-        S.R[row * G::LDR + col] = (s < n && col < n) ? Z.v[c][ti][r] : (row == col ? 1.0 : 0.0);
-      }
-  }
+    for (int r = 0; r < 4; ++r) {
+      const int row = row_of(L, ti, r);
+      S.R[row * G::LDR + col] = (row < n && col < n) ? Z.v[0][ti][r] : (row == col ? 1.0 : 0.0);
+    }
   __syncthreads();
 }
 
@@ -2915,12 +2745,12 @@ struct Launch {
   // instantiated in sdq_nt_dense.hip only
   static hipError_t dense_pair(const Inst* inst, const PairItem* items, int count, const int32_t* l_list,
                                Queue* q, int grid, hipStream_t s) {
-    hipLaunchKernelGGL((k_pair<NT, P, kPairLds, PAIR_TDISP_DENSE>), dim3(grid), dim3(Geo<NT, P>::THREADS), 0, s,
+    hipLaunchKernelGGL((k_pair<NT, NT, kPairLds, PAIR_TDISP_DENSE>), dim3(grid), dim3(Geo<NT, NT>::THREADS), 0, s,
                        inst, items, count, l_list, q);
     return hipGetLastError();
   }
   static hipError_t dense_pair_info(KernelInfo* out) {
-    return info_of(k_pair<NT, P, kPairLds, PAIR_TDISP_DENSE>, (int)sizeof(Smem<NT, P, kPairLds>), out);
+    return info_of<NT>(k_pair<NT, NT, kPairLds, PAIR_TDISP_DENSE>, (int)sizeof(Smem<NT, NT, kPairLds>), out);
   }
   // variants 4 and 5: one wave per 16-column tile (PT = NT waves), T in the
   // per-workgroup scratch between blocks
@@ -2956,20 +2786,20 @@ struct Launch {
   }
   static hipError_t pair(int mode, const Inst* inst, const PairItem* items, int count,
                          const int32_t* l_list, Queue* q, int grid, hipStream_t s) {
-    const dim3 b(Geo<NT, P>::THREADS);
+    const dim3 b(Geo<NT, P>::THREADS), bt(Geo<NT, PT>::THREADS);
     if (mode == PAIR_TDISP)
-      hipLaunchKernelGGL((k_pair<NT, P, kPairLds, PAIR_TDISP>), dim3(grid), b, 0, s, inst, items, count, l_list, q);
+      hipLaunchKernelGGL((k_pair<NT, PT, kPairLds, PAIR_TDISP>), dim3(grid), bt, 0, s, inst, items, count, l_list, q);
     else if (mode == PAIR_GRAD)
-      hipLaunchKernelGGL((k_pair<NT, P, kPairLds, PAIR_GRAD>), dim3(grid), b, 0, s, inst, items, count, l_list, q);
+      hipLaunchKernelGGL((k_pair<NT, PT, kPairLds, PAIR_GRAD>), dim3(grid), bt, 0, s, inst, items, count, l_list, q);
     else if (mode == PAIR_TDISP_PLAIN)
       hipLaunchKernelGGL((k_pair<NT, P, kPairLds, PAIR_TDISP_PLAIN>), dim3(grid), b, 0, s, inst, items, count,
                          l_list, q);
     else if (mode == PAIR_LOCAL)
       hipLaunchKernelGGL((k_pair<NT, P, kPairLds, PAIR_LOCAL>), dim3(grid), b, 0, s, inst, items, count, l_list, q);
     else if (mode == PAIR_BSTART)
-      hipLaunchKernelGGL((k_pair<NT, P, kPairLds, PAIR_BSTART>), dim3(grid), b, 0, s, inst, items, count, l_list, q);
+      hipLaunchKernelGGL((k_pair<NT, PT, kPairLds, PAIR_BSTART>), dim3(grid), bt, 0, s, inst, items, count, l_list, q);
     else
-      hipLaunchKernelGGL((k_pair<NT, P, kPairLds, PAIR_EQUAL>), dim3(grid), b, 0, s, inst, items, count, l_list, q);
+      hipLaunchKernelGGL((k_pair<NT, PT, kPairLds, PAIR_EQUAL>), dim3(grid), bt, 0, s, inst, items, count, l_list, q);
     return hipGetLastError();
   }
   static hipError_t similarity(int n, int count, double* const* mats, const double* left,
@@ -3008,7 +2838,7 @@ struct Launch {
       return info_of(k_sweep<NT, P, false>, (int)sizeof(Smem<NT, P, false>), out);
     }
     if (kind == KK_PAIR)
-      return info_of(k_pair<NT, P, kPairLds, PAIR_TDISP>, (int)sizeof(Smem<NT, P, kPairLds>), out);
+      return info_of<PT>(k_pair<NT, PT, kPairLds, PAIR_TDISP>, (int)sizeof(Smem<NT, PT, kPairLds>), out);
     return info_of(k_udt<NT, P>, (int)sizeof(Smem<NT, P, false>), out);
   }
 };
