@@ -1378,17 +1378,23 @@ __device__ __forceinline__ int jsvd_udt(const Lane& L, const int n, Smem<NT, P, 
 }
 
 
+// The first block of a chain, a product of slices alone, is not graded: from
+// three tiles on its growth test fails in every pass (R outgrows its diagonal
+// by 5 to 15 at n = 64 to 256), so it takes the pivoted QR at once.
+constexpr int kFirstPivotedNT = 3;
 // Acceptance of a norm-sorted QR: R's rows may exceed its diagonal by this
 // factor (a pivoted QR's never do).  Up to kSortPasses attempts, each with
-// the columns in the order of the last one's diagonal, then the pivoted QR.
+// the columns in the order of the last one's diagonal, a column that exceeds a
+// row's diagonal by more raised to its entry there (it should have come before
+// that row), then the pivoted QR.
 // Measured against 113-bit arithmetic (n = 16 .. 64, ordered and random
 // fields, chains with |G| up to 400): without the test G(tau, 0) is up to
 // 70 times further off than with pivoting (a chain's first blocks, whose
 // columns are not graded yet), with it the errors scatter around the pivoted
 // QR's by a factor of two either way; one to four of a chain's blocks need a
-// second pass, and none of those chains a pivoted block.
+// second pass, and none of those chains another pivoted block (n up to 576).
 constexpr double kSortedGrowth = 4.0;
-constexpr int kSortPasses = 4;
+constexpr int kSortPasses = 6;
 
 // Stabilization of one block by the norm-sorted blocked QR: on entry W is the
 // block's product with U (D not yet applied: dcol is the column's scale), T
@@ -1400,8 +1406,8 @@ constexpr int kSortPasses = 4;
 // S.sperm); keep_t takes the new T.
 template <int NT, bool ELDS, class SortT, class LoadT, class KeepT>
 __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>& S, RM<NT, NT>& Wm,
-                                                 double dcol, double* sgn, SortT sort_t, LoadT load_t,
-                                                 KeepT keep_t) {
+                                                 double dcol, const bool first, double* sgn, SortT sort_t,
+                                                 LoadT load_t, KeepT keep_t) {
   using G = Geo<NT, NT>;
   double(&W)[NT][4] = Wm.v[0];
   double key, scale;
@@ -1425,10 +1431,12 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
     const double ss = sum_col((sp[0] + sp[1]) + (sp[2] + sp[3]));
     scale = dcol * usc;
     key = sqrt(ss) * scale;
+    // (an ungraded first block straight to the pivoted QR: its columns in place)
+    if (first && L.g == 0) S.sperm[16 * L.w + L.cl] = 16 * L.w + L.cl;
   }
   bool sorted = false;
 #pragma unroll 1
-  for (int pass = 0;; ++pass) {
+  for (int pass = 0; !first; ++pass) {
     Lane L = lane_id_per_item();
     const int col = 16 * L.w + L.cl;
     const bool live = col < n;
@@ -1469,7 +1477,7 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
     // growth test: |R_ic| <= gamma |R_ii| in the original scales
     L = lane_id_per_item();
     for (int t = L.t; t < G::NP; t += G::THREADS) S.dnew[t] = fabs(S.red_diag[t]) * S.dcur[t];
-    int bad = 0;
+    double lift = 0.0;
     const double* pw = S.R + L.w * (NT * kTile);
 #pragma unroll
     for (int t = 0; t < NT; ++t)
@@ -1479,10 +1487,12 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
           const int row = row_of(L, t, r);
           const double x = pw[kTile * t + tile_idx(L.g + 4 * r, L.cl)];
           const double lim = kSortedGrowth * fabs(S.red_diag[row]) * S.dcur[row];
-          if (row < col && fabs(x) * scale > lim) bad = 1;
+          const double y = fabs(x) * scale;
+          if (row < col && y > lim) lift = fmax(lift, y);
         }
       }
-    const bool any = __any(bad && live);
+    lift = max_col(lift);
+    const bool any = __any(lift > 0.0 && live);
     if (L.l == 0) S.ired[L.w] = any ? 1 : 0;
     __syncthreads();
     int failed = 0;
@@ -1492,7 +1502,7 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
     if (sorted) break;
     block_form<NT, true>(L, S, W);  // Q R, the scaled columns themselves
     if (pass == kSortPasses - 1) break;
-    key = S.dnew[col];
+    key = fmax(S.dnew[col], lift);
   }
   const Lane L = lane_id_per_item();
   if (sorted) {
@@ -1686,10 +1696,11 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
       sgn_u = sgn_run * ps;
       sgn_run = sgn_u;
     } else if constexpr (FAST) {
+      const bool first = NT >= kFirstPivotedNT && s == s_lo && !(block && jpair > 0);
       if constexpr (TG) {
         RM<NT, P> Tr;
         stabilize_sorted<NT, ELDS>(
-            n, S, W, dcol[0], &sgn_u, [] {},
+            n, S, W, dcol[0], first, &sgn_u, [] {},
             [&]() -> RM<NT, P>& {
               // rows in sorted order: from the scratch's register layout, from
               // forward stage jpair, or of the identity
@@ -1721,7 +1732,7 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
             });
       } else {
         stabilize_sorted<NT, ELDS>(
-            n, S, W, dcol[0], &sgn_u,
+            n, S, W, dcol[0], first, &sgn_u,
             [&] {
               const Lane L = lane_id_per_item();
               const int base = (16 * L.w + L.cl) * G::LDR;

@@ -41,12 +41,12 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
-#include "sdq_internal.h"
+#include "sdq_device.hpp"
 
 namespace sdq {
-namespace {
+hipError_t launch_fill_i32(int32_t* p, int n, int32_t v, hipStream_t s);
 
-typedef double d4 __attribute__((ext_vector_type(4)));
+namespace {
 
 constexpr int kWaves = kGangThreads / 64;  // 16
 constexpr int kPairs = 5;                  // MFMA output tiles per wave in a slab product
@@ -62,13 +62,21 @@ struct GLds {
   double S[kGangSlab];       // column slab, [col][row]
   double tau[kGangMaxN];     // reflector scalars; also a slice's exp(alpha f)
   double beta[kGangMaxN];    // diag R of the last QR (D = |beta|)
-  int piv[kGangMaxN];        // piv[p] = global column chosen at step p
+  short piv[kGangMaxN];      // piv[p] = global column chosen at step p
   double vn1[kGangMaxW], vn2[kGangMaxW];
   int posl[kGangMaxW];       // step at which a slab column was chosen; -1 live, -2 padding
   unsigned long long wkey[kWaves];
   double red[2 * kWaves];
   unsigned vis[kGangMaxN / 32];
+  unsigned vote;
   int ok;
+  union {
+    double xbuf[4 * 256];         // partial products of a panel application
+    struct {
+      double pred[2 * 17 * 16];   // a panel step's dot products and pivot row, two steps
+      double gram[256];           // products of a panel's reflectors
+    };
+  };
 };
 
 // The workgroup's LDS block.  Declared at namespace scope (not passed by
@@ -86,6 +94,8 @@ struct GC {
   double* base; // per-gang scratch
   unsigned* bar;
   unsigned epoch;
+  unsigned pseq;   // panels published so far (bar[8])
+  unsigned votes;  // growth votes so far (bar[9])
   bool ok;
 };
 
@@ -96,8 +106,14 @@ __device__ __forceinline__ double* sc_U(const GC& c) { return c.base + 3 * gang_
 __device__ __forceinline__ double* sc_G(const GC& c, int b) { return c.base + (4 + b) * gang_mat(c.geo); }
 __device__ __forceinline__ double* sc_X(const GC& c) { return c.base + 6 * gang_mat(c.geo); }
 __device__ __forceinline__ double* sc_cand(const GC& c, int buf) {
-  return c.base + 7 * gang_mat(c.geo) + (int64_t)buf * c.geo.G * gang_cand_stride(c.geo);
+  return c.base + 8 * gang_mat(c.geo) + (int64_t)buf * c.geo.G * gang_cand_stride(c.geo);
 }
+__device__ __forceinline__ double* sc_V2(const GC& c) { return c.base + 7 * gang_mat(c.geo); }
+__device__ __forceinline__ double* sc_tw(const GC& c) {
+  return c.base + 8 * gang_mat(c.geo) + 2 * c.geo.G * gang_cand_stride(c.geo) + 64;
+}
+__device__ __forceinline__ double* sc_meta(const GC& c) { return sc_tw(c) + (int64_t)(c.geo.npad / 16) * 256; }
+__device__ __forceinline__ double* sc_keys(const GC& c) { return sc_meta(c) + (int64_t)(c.geo.npad / 16) * 32; }
 
 // ---- wave reductions ----------------------------------------------------------
 // A butterfly in which each step combines a lane with a partner that
@@ -156,11 +172,6 @@ __device__ __forceinline__ double wave_max(double v) {
 __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
   return wave_reduce(v, [](unsigned long long a, unsigned long long b) { return a > b ? a : b; });
 }
-__device__ __forceinline__ double pow2_scale(double x) {
-  if (!(x > 0.0) || !isfinite(x)) return 1.0;
-  return ldexp(1.0, -ilogb(x));
-}
-
 // Pivot key: bits 63..16 the norm's top 48 bits, bits 15..11 a step tag,
 // bits 10..0 2047 - column.  Among keys of one step the largest norm wins
 // and, among norms equal to 2^-36 relative, the smallest column.  A member
@@ -175,14 +186,6 @@ __device__ __forceinline__ unsigned long long tag_key(unsigned long long k, int 
   return (k & ~0xF800ull) | ((unsigned long long)(p & 31) << 11);
 }
 __device__ __forceinline__ int key_tag(unsigned long long k) { return (int)((k >> 11) & 31); }
-
-// Device memory seen as the global address space: accesses through these
-// compile to global instructions (flat ones would also count against LDS
-// waits and be ordered against the spill slots).
-template <class T>
-__device__ __forceinline__ __attribute__((address_space(1))) T* gmem(T* p) {
-  return (__attribute__((address_space(1))) T*)p;
-}
 
 // ---- gang barrier ----------------------------------------------------------
 __device__ bool gang_sync(GC& c) {
@@ -929,6 +932,8 @@ __device__ double refl_sign(GC& c) {
   return (((long long)cnt) & 1) ? -1.0 : 1.0;
 }
 
+#include "sdq_gang_block.hpp"
+
 // ---- stage loop ----------------------------------------------------------------
 __device__ void load_slice_scale(GC& c, const Inst& I, int q) {
   const double* f = I.field + (int64_t)(q - 1) * I.n;
@@ -939,16 +944,35 @@ __device__ void load_slice_scale(GC& c, const Inst& I, int q) {
 // Stabilized chain (Sec. 4.1) with the UDT of Sec. 4.2.2 every k slices,
 // forward over B_1..B_m or, with SW_ADJ, backward over B_m^T..B_1^T; stage
 // storage as in the single-workgroup kernels (U | T | D | sgn det U).
-template <int kRL>
-__device__ void sweep_gang(GC& c, const Inst& I, int flags) {
+// Blocks s0 .. s1 - 1 of it.  PIVOT: with the column-pivoted QR (every block
+// where the factors are the result, for the single-decomposition schemes, and
+// for a chain that stabilize_gang gave up; else the first one, whose columns
+// are not graded yet), else with stabilize_gang, continued from the stage that
+// block s0 - 1 left; false where that gives up.
+template <int kRL, bool PIVOT>
+__device__ bool sweep_gang(GC& c, const Inst& I, int flags, int s0, int s1) {
   const int n = I.n, m = I.m, k = I.k, nb = I.nb, np = c.geo.npad;
   const bool adj = (flags & SW_ADJ) != 0;
   const int64_t sd = stage_doubles(n);
   double* Tg = sc_T(c);  // T of the chain, row-major n x n (own columns)
-  slab_identity(c);
+  // stage of block s (a chain that stores none keeps the first and the last
+  // one at fin)
+  auto stage_of = [&](int s) -> double* {
+    if (flags & SW_STORE) return adj ? I.cka + (int64_t)(nb - 1 - s) * sd : I.ckf + (int64_t)s * sd;
+    return (flags & SW_LAST) && (s == nb - 1 || s + 1 == s1) ? I.fin : nullptr;
+  };
   for (int i = c.t; i < np; i += kGangThreads) L.beta[i] = 1.0;
-  __syncthreads();
-  slab_store_rowmajor(c, Tg);
+  if constexpr (PIVOT) {
+    slab_identity(c);
+    slab_store_rowmajor(c, Tg);
+  } else {
+    const double* F = (flags & SW_STORE) ? stage_of(s0 - 1) : I.fin;
+    __syncthreads();
+    for (int i = c.t; i < n; i += kGangThreads) L.beta[i] = gmem(F)[2 * (int64_t)n * n + i];
+    slab_fill_rows(c, [&](int i, int gc) { return gmem(F)[(int64_t)n * n + (int64_t)i * n + gc]; });
+    slab_store_rowmajor(c, Tg);
+    slab_fill_rows(c, [&](int i, int gc) { return gmem(F)[(int64_t)i * n + gc]; });
+  }
   double sgn_u = 1.0;
   const ASwz aop{adj ? I.eswt : I.esw, np / 16};
   auto copy_t = [&](double* dst) {
@@ -957,15 +981,18 @@ __device__ void sweep_gang(GC& c, const Inst& I, int flags) {
       if (gc < n) gmem(dst)[(int64_t)i * n + gc] = gmem(Tg)[(int64_t)i * n + gc];
     }
   };
-  for (int s = 0; s < nb; ++s) {
+  for (int s = s0; s < s1; ++s) {
     const int b = adj ? nb - 1 - s : s;
     const int q0 = b * k + 1, q1 = (b + 1) * k < m ? (b + 1) * k : m;
-    // U D (column scale), then the block of slices
-    for (int idx = c.t; idx < np * c.geo.w; idx += kGangThreads) {
-      const int cc = idx / np, i = idx - cc * np, gc = c.c0 + cc;
-      if (gc < n) L.S[cc * c.geo.ldr + i] *= fabs(L.beta[gc]);
+    // U D (column scale; stabilize_gang applies it itself), then the block of
+    // slices
+    if constexpr (PIVOT) {
+      for (int idx = c.t; idx < np * c.geo.w; idx += kGangThreads) {
+        const int cc = idx / np, i = idx - cc * np, gc = c.c0 + cc;
+        if (gc < n) L.S[cc * c.geo.ldr + i] *= fabs(L.beta[gc]);
+      }
+      __syncthreads();
     }
-    __syncthreads();
     for (int qq = 0; qq <= q1 - q0; ++qq) {
       const int q = adj ? q1 - qq : q0 + qq;
       load_slice_scale(c, I, q);
@@ -974,22 +1001,24 @@ __device__ void sweep_gang(GC& c, const Inst& I, int flags) {
       else
         slab_gemm(c, aop, One{}, [&](int row) { return L.tau[row]; });
     }
-    cpqr_gang<kRL>(c);
-    // T <- D^{-1} R P^T T with D = |diag R|
-    slab_fill_rows(c, [&](int i, int gc) { return gmem(Tg)[(int64_t)i * n + gc]; });
-    __syncthreads();
-    slab_gemm(c, AColMajor{sc_R(c), np}, One{},
-              [&](int row) { return row < n ? 1.0 / fabs(L.beta[row]) : 0.0; });
-    slab_store_rowmajor(c, Tg);
-    sgn_u = refl_sign(c);
-    // U <- Q
-    slab_identity(c);
-    __syncthreads();
-    apply_reflectors<false, kRL>(c, true);
-    double* dst = nullptr;
-    if (flags & SW_STORE) dst = adj ? (I.cka + (int64_t)b * sd) : (I.ckf + (int64_t)s * sd);
-    else if ((flags & SW_LAST) && s == nb - 1) dst = I.fin;
-    if (dst) {
+    if constexpr (PIVOT) {
+      cpqr_gang<kRL>(c);
+      // T <- D^{-1} R P^T T with D = |diag R|
+      slab_fill_rows(c, [&](int i, int gc) { return gmem(Tg)[(int64_t)i * n + gc]; });
+      __syncthreads();
+      slab_gemm(c, AColMajor{sc_R(c), np}, One{},
+                [&](int row) { return row < n ? 1.0 / fabs(L.beta[row]) : 0.0; });
+      slab_store_rowmajor(c, Tg);
+      sgn_u = refl_sign(c);
+      // U <- Q
+      slab_identity(c);
+      __syncthreads();
+      apply_reflectors<false, kRL>(c, true);
+    } else {
+      if (!stabilize_gang(c, Tg)) return false;
+      sgn_u = (n & 1) ? -1.0 : 1.0;  // every one of the n reflectors reflects
+    }
+    if (double* dst = stage_of(s)) {
       slab_store_rowmajor(c, dst);
       copy_t(dst + (int64_t)n * n);
       if (c.g == 0) {
@@ -1011,6 +1040,7 @@ __device__ void sweep_gang(GC& c, const Inst& I, int flags) {
   }
   if ((__any(bad) || !c.ok) && c.l == 0 && I.status) atomicOr(I.status, kStatusRange);
   __syncthreads();
+  return true;
 }
 
 // Equal-time G, log|det| and sign from the final forward stage (Sec. 5.1,
@@ -1030,18 +1060,26 @@ __device__ void equal_gang(GC& c, const Inst& I) {
   slab_fill_rows(c, [&](int i, int gc) { return dm(i) * gmem(T)[(int64_t)i * n + gc]; });
   __syncthreads();
   slab_for_each<false>(c, [&](int i, int gc) { return gmem(U)[(int64_t)gc * n + i] / dp(i); }, AddInside{});
-  cpqr_gang<kRL>(c);
+  if (loh) bqr_gang(c, false);
+  else cpqr_gang<kRL>(c);
   slab_fill_cols(c, [&](int i, int gc) { return gmem(U)[(int64_t)gc * n + i] / dp(i); });
   __syncthreads();
-  apply_reflectors<true, kRL>(c, false);
-  back_subst<kRL>(c);
+  if (loh) {
+    bsolve_gang(c);
+  } else {
+    apply_reflectors<true, kRL>(c, false);
+    back_subst<kRL>(c);
+  }
   int bad = 0;
   for (int idx = c.t; idx < c.geo.npad * c.geo.w; idx += kGangThreads) {
     const int cc = idx / c.geo.npad, i = idx - cc * c.geo.npad;
     if (i < n && c.c0 + cc < n && !isfinite(L.S[cc * c.geo.ldr + i])) bad = 1;
   }
-  if (I.g) slab_store_rowmajor_perm(c, I.g);
-  const double sp = perm_sign(c);
+  if (I.g) {
+    if (loh) slab_store_rowmajor(c, I.g);
+    else slab_store_rowmajor_perm(c, I.g);
+  }
+  const double sp = loh ? 1.0 : perm_sign(c);
   if (c.g == 0 && c.w == 0) {
     double ls = 0.0, ng = 0.0;
     for (int i = c.l; i < n; i += 64) {
@@ -1052,7 +1090,8 @@ __device__ void equal_gang(GC& c, const Inst& I) {
     }
     ls = wave_sum(ls);
     ng = wave_sum(ng);
-    const double sq = refl_sign(c);
+    // the blocked QR's n reflectors all reflect
+    const double sq = loh ? ((n & 1) ? -1.0 : 1.0) : refl_sign(c);
     if (!isfinite(ls)) bad = 1;
     if (c.l == 0) {
       if (I.logdet) *I.logdet = ls;
@@ -1068,11 +1107,11 @@ __device__ void equal_gang(GC& c, const Inst& I) {
 //   Mid = D_Lm (U1^T U2) D_Rp^{-1} + D_Lp^{-1} (T1 T2^T) D_Rm,
 //   G(tau,0) = U2 D_Rp^{-1} Mid^{-1} D_Lp^{-1} T1,
 // with D_L = D1^{-1}, D_R = D2; then B_l ... G(tau_j, 0) for the requested
-// l of the block (Sec. 6).
-template <int kRL>
-__device__ void tdisp_gang(GC& c, const Inst& I, int j, int ilo, int ihi,
-                           const int32_t* l_list) {
-  const int n = I.n, m = I.m, k = I.k, nb = I.nb, np = c.geo.npad;
+// l of the block (Sec. 6).  EQUAL: the equal-time G at the same boundary,
+// U2 D_Rp^{-1} Mid^{-1} D_Lm U1^T.  The slab holds the result.
+template <bool EQUAL>
+__device__ void middle_gang(GC& c, const Inst& I, int j) {
+  const int n = I.n, nb = I.nb, np = c.geo.npad;
   const int64_t sd = stage_doubles(n);
   const double* F = j > 0 ? I.ckf + (int64_t)(j - 1) * sd : nullptr;
   const double* A = j < nb ? I.cka + (int64_t)j * sd : nullptr;
@@ -1115,9 +1154,14 @@ __device__ void tdisp_gang(GC& c, const Inst& I, int j, int ilo, int ihi,
                          return lm * e * rpi + lpi * gmem(Xg)[(int64_t)gc * np + i] * rm;
                        },
                        SetInside{});
-  cpqr_gang<kRL>(c);
-  // Y = D_Lp^{-1} T1 -> Q^T Y -> R^{-1} (pivot order)
-  if (T1) {
+  bqr_gang(c, false);
+  // Y = D_Lp^{-1} T1, or D_Lm U1^T -> R^{-1} Q^T Y
+  if (EQUAL && U1) {
+    slab_fill_cols(c, [&](int i, int gc) {
+      const double a = gmem(D1)[i];
+      return gmem(U1)[(int64_t)gc * n + i] / (a > 1.0 ? a : 1.0);
+    });
+  } else if (!EQUAL && T1) {
     slab_fill_rows(c, [&](int i, int gc) {
       const double a = gmem(D1)[i];
       return gmem(T1)[(int64_t)i * n + gc] * (a < 1.0 ? a : 1.0);
@@ -1125,23 +1169,7 @@ __device__ void tdisp_gang(GC& c, const Inst& I, int j, int ilo, int ihi,
   } else {
     slab_identity(c);
   }
-  apply_reflectors<true, kRL>(c, false);
-  back_subst<kRL>(c);
-  // undo the pivot order through HBM: X[piv[q]][:] = Z[q][:]
-  for (int idx = c.t; idx < np * c.geo.w; idx += kGangThreads) {
-    const int cc = idx / np, q = idx - cc * np, gc = c.c0 + cc;
-    if (gc >= np) continue;
-    if (q < n) {
-      int row = L.piv[q];
-      row = row < 0 ? 0 : (row >= n ? n - 1 : row);
-      gmem(Xg)[(int64_t)gc * np + row] = gc < n ? L.S[cc * c.geo.ldr + q] : 0.0;
-    } else {
-      gmem(Xg)[(int64_t)gc * np + q] = 0.0;
-    }
-  }
-  __syncthreads();
-  slab_fill_cols(c, [&](int i, int gc) { return gmem(Xg)[(int64_t)gc * np + i]; });
-  __syncthreads();
+  bsolve_gang(c);
   // G = (U2 D_Rp^{-1}) X, D_Rp^{-1} in L.beta (free after the solve)
   for (int i = c.t; i < np; i += kGangThreads) {
     const double b = (D2 && i < n) ? gmem(D2)[i] : 1.0;
@@ -1150,6 +1178,12 @@ __device__ void tdisp_gang(GC& c, const Inst& I, int j, int ilo, int ihi,
   __syncthreads();
   if (U2) slab_gemm(c, ARowMajor<BetaScale>{U2, n, BetaScale{}}, One{}, One{});
   else slab_gemm(c, AIdent<BetaScale>{n, BetaScale{}}, One{}, One{});
+}
+
+// G(tau_j, 0) and the outputs of stage pair j.
+__device__ void tdisp_gang(GC& c, const Inst& I, int j, int ilo, int ihi, const int32_t* l_list) {
+  const int n = I.n, m = I.m, k = I.k, np = c.geo.npad;
+  middle_gang<false>(c, I, j);
   int bad = 0;
   for (int idx = c.t; idx < np * c.geo.w; idx += kGangThreads) {
     const int cc = idx / np, i = idx - cc * np;
@@ -1171,75 +1205,15 @@ __device__ void tdisp_gang(GC& c, const Inst& I, int j, int ilo, int ihi,
   __syncthreads();
 }
 
-// Gradient rows of the slices j*k+1 .. min((j+1)k, m) (App. A.1):
-//   G_{jk+1} = [1 + U1 (D1 (T1 T2^T) D2) U2^T]^{-1}; udt(D1 T1 T2^T D2) = u d t,
-//   U = U1 u, T = t U2^T, then the equal-time inversion (Sec. 5.1), and
+// Gradient rows of the slices j*k+1 .. min((j+1)k, m) (App. A.1): G_{jk+1}
+// from the stage pair (middle_gang), then
 //   G_{l+1} = E diag(v_l) G_l diag(1/v_l) Ebar,  grad[l-1][i] = alpha (1 - G_l)_ii.
-template <int kRL>
 __device__ void grad_gang(GC& c, const Inst& I, int j) {
-  const int n = I.n, m = I.m, k = I.k, nb = I.nb, np = c.geo.npad, ldr = c.geo.ldr;
-  const int64_t sd = stage_doubles(n);
-  const double* F = j > 0 ? I.ckf + (int64_t)(j - 1) * sd : nullptr;
-  const double* A = j < nb ? I.cka + (int64_t)j * sd : nullptr;
-  const double* U1 = F;
-  const double* T1 = F ? F + (int64_t)n * n : nullptr;
-  const double* D1 = F ? F + 2 * (int64_t)n * n : nullptr;
-  const double* U2 = A;
-  const double* T2 = A ? A + (int64_t)n * n : nullptr;
-  const double* D2 = A ? A + 2 * (int64_t)n * n : nullptr;
-  double* Ug = sc_U(c);
-  double* Tg = sc_T(c);
-  // D1 (T1 T2^T) D2, with D1 in L.tau and D2 in L.beta (free until the QR)
-  for (int i = c.t; i < np; i += kGangThreads) {
-    L.tau[i] = (D1 && i < n) ? gmem(D1)[i] : 1.0;
-    L.beta[i] = (D2 && i < n) ? gmem(D2)[i] : 1.0;
-  }
-  if (T2) slab_fill_cols(c, [&](int i, int gc) { return gmem(T2)[(int64_t)gc * n + i]; });
-  else slab_identity(c);
-  if (T1) slab_gemm(c, ARowMajor<One>{T1, n, One{}}, One{}, [&](int row) { return L.tau[row]; });
-  else slab_gemm(c, AIdent<One>{n, One{}}, One{}, [&](int row) { return L.tau[row]; });
-  slab_for_each<false>(c, [&](int, int gc) { return L.beta[gc]; }, MulInside{});
-  cpqr_gang<kRL>(c);
-  // T = d^{-1} (R P^T) U2^T  (slab columns), to HBM
-  if (U2) slab_fill_cols(c, [&](int i, int gc) { return gmem(U2)[(int64_t)gc * n + i]; });
-  else slab_identity(c);
-  slab_gemm(c, AColMajor{sc_R(c), np}, One{},
-            [&](int row) { return row < n ? 1.0 / fabs(L.beta[row]) : 0.0; });
-  slab_store_colmajor(c, Tg);
-  // U = U1 u
-  slab_identity(c);
-  __syncthreads();
-  apply_reflectors<false, kRL>(c, true);
-  if (U1) slab_gemm(c, ARowMajor<One>{U1, n, One{}}, One{}, One{});
-  slab_store_colmajor(c, Ug);
-  // D of the combined factorization: |beta| (kept in L.red-free storage: HBM)
-  double* Dg = sc_X(c);
-  if (c.g == 0)
-    for (int i = c.t; i < n; i += kGangThreads) gmem(Dg)[i] = fabs(L.beta[i]);
-  gang_sync(c);
-  // M = Dp^{-1} U^T + Dm T
-  auto dp = [&](int i) { const double d = gmem(Dg)[i]; return d > 1.0 ? d : 1.0; };
-  auto dm = [&](int i) { const double d = gmem(Dg)[i]; return d < 1.0 ? d : 1.0; };
-  slab_fill_rows(c, [&](int i, int gc) { return gmem(Ug)[(int64_t)i * np + gc] / dp(i); });
-  slab_for_each<false>(c, [&](int i, int gc) { return dm(i) * gmem(Tg)[(int64_t)gc * np + i]; }, AddInside{});
-  cpqr_gang<kRL>(c);
-  slab_fill_rows(c, [&](int i, int gc) { return gmem(Ug)[(int64_t)i * np + gc] / dp(i); });
-  __syncthreads();
-  apply_reflectors<true, kRL>(c, false);
-  back_subst<kRL>(c);
-  // G_{jk+1} = P X into HBM buffer 0 (column-major, rows un-permuted)
+  const int n = I.n, m = I.m, k = I.k, np = c.geo.npad, ldr = c.geo.ldr;
+  middle_gang<true>(c, I, j);
+  // into HBM buffer 0 (column-major)
   double* Gb[2] = {sc_G(c, 0), sc_G(c, 1)};
-  for (int idx = c.t; idx < np * c.geo.w; idx += kGangThreads) {
-    const int cc = idx / np, q = idx - cc * np, gc = c.c0 + cc;
-    if (gc >= np) continue;
-    if (q < n) {
-      int row = L.piv[q];
-      row = row < 0 ? 0 : (row >= n ? n - 1 : row);
-      gmem(Gb[0])[(int64_t)gc * np + row] = gc < n ? L.S[cc * ldr + q] : 0.0;
-    } else {
-      gmem(Gb[0])[(int64_t)gc * np + q] = 0.0;
-    }
-  }
+  slab_store_colmajor(c, Gb[0]);
   gang_sync(c);
   const int l0 = j * k + 1, l1 = (j + 1) * k < m ? (j + 1) * k : m;
   bool bad = false;
@@ -1315,6 +1289,8 @@ __device__ GC gang_ctx(const GangArgs& a) {
   c.base = a.scratch + (int64_t)gang * gang_doubles(c.geo);
   c.bar = a.bars + (int64_t)gang * kGangBarWords;
   c.epoch = 0;
+  c.pseq = 0;
+  c.votes = 0;
   c.ok = true;
   c.n = 0;
   return c;
@@ -1332,18 +1308,29 @@ __device__ __forceinline__ void gang_lanes_per_item(GC& c) {
   c.l = t & 63;
 }
 
-template <int RL>
+template <int RL, bool PIVOT>
 __global__ __launch_bounds__(kGangThreads, 1) void k_gang_sweep(const Inst* __restrict__ insts,
-                                                                 const SweepItem* __restrict__ items,
-                                                                 int count, GangArgs a) {
+                                                                 SweepItem* __restrict__ items, int count,
+                                                                 int phase, GangArgs a) {
+  // PIVOT: whole chains (phase 0), their first blocks (1), or whole chains
+  // that the sorted sweep marked (2); else the sorted sweep from block 1 on
   GC c = gang_ctx(a);
+  const bool redo = phase == 2;
+  if (redo) {
+    bool any = false;
+    for (int it = c.gang; it < count; it += a.ngangs) any |= items[it].redo != 0;
+    if (!any) return;  // the same for every member of the gang
+  }
   if (c.gang < count) gang_assemble(c);
   for (int it = c.gang; it < count; it += a.ngangs) {
     const SweepItem wi = items[it];
+    if (redo && !wi.redo) continue;
     const Inst I = insts[wi.inst];
     c.n = I.n;
     gang_lanes_per_item(c);
-    sweep_gang<RL>(c, I, wi.flags);
+    const int s0 = PIVOT ? 0 : 1, s1 = phase == 1 ? 1 : I.nb;
+    if (s0 >= s1) continue;
+    if (!sweep_gang<RL, PIVOT>(c, I, wi.flags, s0, s1) && c.g == 0 && c.t == 0) gmem(&items[it].redo)[0] = 1;
   }
 }
 
@@ -1360,8 +1347,8 @@ __global__ __launch_bounds__(kGangThreads, 1) void k_gang_pair(const Inst* __res
     c.n = I.n;
     gang_lanes_per_item(c);
     if (MODE == PAIR_EQUAL) equal_gang<RL>(c, I);
-    else if (MODE == PAIR_TDISP) tdisp_gang<RL>(c, I, wi.j, wi.ilo, wi.ihi, l_list);
-    else grad_gang<RL>(c, I, wi.j);
+    else if (MODE == PAIR_TDISP) tdisp_gang(c, I, wi.j, wi.ilo, wi.ihi, l_list);
+    else grad_gang(c, I, wi.j);
   }
 }
 
@@ -1393,7 +1380,7 @@ int rl_of(int nt) { return nt <= 16 ? 4 : (nt <= 32 ? 8 : 16); }
 hipError_t gang_capacity(int nt, int num_cu, int* ngangs) {
   const GangGeom g = gang_geom(nt);
   if (g.G == 0) return hipErrorInvalidValue;
-  const void* ks[] = {(const void*)k_gang_sweep<16>, (const void*)k_gang_pair<PAIR_TDISP, 16>,
+  const void* ks[] = {(const void*)k_gang_sweep<16, false>, (const void*)k_gang_sweep<16, true>, (const void*)k_gang_pair<PAIR_TDISP, 16>,
                       (const void*)k_gang_pair<PAIR_GRAD, 16>, (const void*)k_gang_pair<PAIR_EQUAL, 16>};
   int per_cu = 1 << 30;
   for (const void* k : ks) {
@@ -1413,9 +1400,28 @@ hipError_t gang_capacity(int nt, int num_cu, int* ngangs) {
     default: return CALL(16); \
   }
 
-hipError_t launch_gang_sweep(const Inst* inst, const SweepItem* items, int count, GangArgs a,
+hipError_t launch_gang_sweep(bool pivoted, const Inst* inst, SweepItem* items, int count, GangArgs a,
                              hipStream_t s) {
-#define C(R) coop_launch(k_gang_sweep<R>, a, s, inst, items, count)
+  if (!pivoted) {
+    // the first blocks, the rest of the chains, and the pivoted sweep of what
+    // the growth test gave up (most often nothing: that launch ends at once)
+    hipError_t e = [&]() -> hipError_t {
+#define C(R) coop_launch(k_gang_sweep<R, true>, a, s, inst, items, count, 1)
+      SDQ_RL_SWITCH(C)
+#undef C
+    }();
+    if (e == hipSuccess) e = launch_fill_i32((int32_t*)a.bars, a.ngangs * kGangBarWords, 0, s);
+    if (e != hipSuccess) return e;
+    e = [&]() -> hipError_t {
+#define C(R) coop_launch(k_gang_sweep<R, false>, a, s, inst, items, count, 0)
+      SDQ_RL_SWITCH(C)
+#undef C
+    }();
+    if (e == hipSuccess) e = launch_fill_i32((int32_t*)a.bars, a.ngangs * kGangBarWords, 0, s);
+    if (e != hipSuccess) return e;
+  }
+  const int phase = pivoted ? 0 : 2;
+#define C(R) coop_launch(k_gang_sweep<R, true>, a, s, inst, items, count, phase)
   SDQ_RL_SWITCH(C)
 #undef C
 }

@@ -71,7 +71,7 @@ struct SweepItem {
   int32_t inst;
   int32_t flags;
   int32_t j;  // stage pair of SW_LEFT / SW_RIGHT
-  int32_t pad;
+  int32_t redo;  // set by a gang's sorted sweep whose growth test failed: the pivoted one does the chain
 };
 
 enum PairMode : int32_t { PAIR_TDISP = 0, PAIR_GRAD = 1, PAIR_EQUAL = 2, PAIR_TDISP_PLAIN = 3,
@@ -263,7 +263,9 @@ constexpr int kGangMaxN = 1024;
 constexpr int kGangThreads = 1024;
 constexpr int kGangSlab = 16640;  // doubles of the LDS column slab
 constexpr int kGangMaxW = 128;
-constexpr int kGangBarWords = 32;  // uint32 words per gang (barrier counter, abort flag, arrivals)
+// uint32 words per gang: barrier counter, abort flag, arrivals; 8: panels
+// published, 9: growth votes
+constexpr int kGangBarWords = 32;
 
 struct GangGeom {
   int npad;  // 16 * ceil(n / 16)
@@ -289,11 +291,13 @@ __host__ __device__ inline GangGeom gang_geom(int nt) {
   return g;
 }
 
-// per-gang scratch (doubles): R, V, T, U, two G buffers, X, candidates
+// per-gang scratch (doubles): R, V, T, U, two G buffers, X, V in operand
+// order, candidates, then the panels' triangular factors and diagonals, and
+// the sort's keys and scales
 __host__ __device__ inline int64_t gang_mat(const GangGeom& g) { return (int64_t)g.npad * g.npad; }
 __host__ __device__ inline int64_t gang_cand_stride(const GangGeom& g) { return g.npad + 8; }
 __host__ __device__ inline int64_t gang_doubles(const GangGeom& g) {
-  return 7 * gang_mat(g) + 2 * g.G * gang_cand_stride(g) + 64;
+  return 8 * gang_mat(g) + 2 * g.G * gang_cand_stride(g) + 64 + (int64_t)(g.npad / 16) * (256 + 32) + 2 * g.npad;
 }
 
 struct GangArgs {
@@ -303,7 +307,8 @@ struct GangArgs {
   int nt;
 };
 
-hipError_t launch_gang_sweep(const Inst* inst, const SweepItem* items, int count, GangArgs a,
+// pivoted: the column-pivoted QR in every block
+hipError_t launch_gang_sweep(bool pivoted, const Inst* inst, SweepItem* items, int count, GangArgs a,
                              hipStream_t s);
 hipError_t launch_gang_pair(int mode, const Inst* inst, const PairItem* items, int count,
                             const int32_t* l_list, GangArgs a, hipStream_t s);

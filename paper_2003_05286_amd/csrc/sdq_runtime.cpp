@@ -489,7 +489,7 @@ sdq_status build_plan(sdq_ctx* ctx, Plan& P, int32_t* status, int count, Built& 
     const bool bprod = ((P.bprod_mask >> r.nt) & 1u) != 0;
     const bool fast = !P.pivoted && ctx->stab == SDQ_STAB_QR && r.nt <= sdq::kMaxNT;
     const int tuned = r.nt <= sdq::kMaxNT ? ctx->tune[r.nt].variant : 4;
-    const int variant = sweep_is_gang(r.nt) ? 0
+    const int variant = sweep_is_gang(r.nt) ? (P.pivoted ? 1 : 0)
                         : fast ? (bprod               ? sdq::kFastProd
                                   : P.dense           ? sdq::kFastDense
                                   : tuned == 1 || tuned == 5 ? sdq::kFastLds
@@ -536,7 +536,7 @@ size_t gang_need(const Built& B) {
   return need;
 }
 
-hipError_t launch_gang_rec(sdq_ctx* ctx, const LaunchRec& L, const Inst* d_inst, const char* d,
+hipError_t launch_gang_rec(sdq_ctx* ctx, const LaunchRec& L, const Inst* d_inst, char* d,
                            const int32_t* d_ll, hipStream_t s) {
   sdq::GangArgs a;
   a.bars = (unsigned*)ctx->d_gang.p;
@@ -546,7 +546,7 @@ hipError_t launch_gang_rec(sdq_ctx* ctx, const LaunchRec& L, const Inst* d_inst,
   hipError_t e = sdq::launch_fill_i32((int32_t*)a.bars, L.grid * sdq::kGangBarWords, 0, s);
   if (e != hipSuccess) return e;
   if (L.kind == sdq::KK_SWEEP)
-    return sdq::launch_gang_sweep(d_inst, (const SweepItem*)(d + L.items_off), L.count, a, s);
+    return sdq::launch_gang_sweep(L.variant != 0, d_inst, (SweepItem*)(d + L.items_off), L.count, a, s);
   return sdq::launch_gang_pair(L.mode, d_inst, (const PairItem*)(d + L.items_off), L.count, d_ll, a, s);
 }
 
