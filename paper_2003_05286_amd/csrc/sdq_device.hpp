@@ -1177,6 +1177,22 @@ __device__ __forceinline__ void stage_e(const Lane& L, Smem<NT, P, ELDS>& S, con
   // visibility: the next fill_vbuf begins with a barrier
 }
 
+// the same into any LDS array, the loads of up to sixteen values together
+template <int NT, int P>
+__device__ __forceinline__ void stage_swizzled(const Lane& L, double* dst, const double* esw) {
+  using G = Geo<NT, P>;
+  constexpr int TOT = G::NP * G::NP, IT = TOT / G::THREADS, CH = IT <= 16 ? IT : IT / 2;
+  static_assert(TOT % G::THREADS == 0 && IT % CH == 0, "whole rounds");
+#pragma unroll 1
+  for (int b = 0; b < IT; b += CH) {
+    double x[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) x[q] = gmem(esw)[L.t + (b + q) * G::THREADS];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) dst[L.t + (b + q) * G::THREADS] = x[q];
+  }
+}
+
 // A register matrix kept in a workgroup's private global scratch between
 // uses: register [c][ti][r] of lane l of wave w at ((c NT + ti) 4 + r) 64 P +
 // 64 w + l, so every access of a wave is one contiguous 512-byte block.  Each
@@ -1566,7 +1582,10 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
   static_assert(!FAST || (P == NT && !SVD), "the blocked QR needs one wave per column tile");
   using G = Geo<NT, P>;
   // the SVD stabilizer keeps T in S.E, so E is read from its global copy
-  constexpr bool EST = ELDS && !SVD && !DENSE;
+  // the blocked QR's panels and the slice products never overlap: from three
+  // tiles on E is staged in the factor store, once per block
+  constexpr bool ESTR = FAST && !DENSE && NT >= 3 && !Smem<NT, P, ELDS>::RG;
+  constexpr bool EST = (ELDS && !SVD && !DENSE) || ESTR;
   constexpr int CT = G::CT;
   const int n = I.n, m = I.m, k = I.k, nb = I.nb;
   const bool left = (flags & SW_LEFT) != 0, right = (flags & SW_RIGHT) != 0;
@@ -1577,7 +1596,7 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
   const int s_lo = (right || block) ? jpair : 0;
   const int s_hi = left ? (tauj + k - 1) / k : (block ? jpair + 1 : nb);
   const double* e_op = left ? I.eswi : (adj ? I.eswt : I.esw);
-  if constexpr (EST) stage_e<NT, P, ELDS>(L, S, e_op);
+  if constexpr (EST && !ESTR) stage_e<NT, P, ELDS>(L, S, e_op);
   // W holds U between blocks and the block product inside a block
   RM<NT, P> W;
   std::conditional_t<TG, NoT, RM<NT, P>> T;
@@ -1602,7 +1621,7 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
 #pragma unroll
     for (int c = 0; c < CT; ++c) dcol[c] = 1.0;
   }
-  const EOp<NT, P, EST> eop{S.E, e_op, L.l};
+  const EOp<NT, P, EST> eop{ESTR ? S.R : S.E, e_op, L.l};
   int svd_failed = 0;
   // sign of det U of the current factorization (the SVD path carries it)
   double sgn_run = (block && jpair > 0) ? gmem(I.ckf + (size_t)(jpair - 1) * sd)[2 * (size_t)n * n + n] : 1.0;
@@ -1659,6 +1678,7 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
         }
       }
     } else {
+      if constexpr (ESTR) stage_swizzled<NT, P>(L, S.R, e_op);  // visible after fill_vbuf's barriers
       for (int c0 = 0; c0 < cnt; c0 += G::KB) {
         const int cn = (cnt - c0) < G::KB ? (cnt - c0) : G::KB;
         if (left) fill_vbuf<NT, P, ELDS>(L, S, I, q1 - c0, -1, cn, -1.0);

@@ -45,7 +45,7 @@ hipError_t launch_prod_nt9(const Inst*, const SweepItem*, int, Queue*, int, hipS
 hipError_t launch_sweep(int nt, int variant, const Inst* inst, const SweepItem* items, int count,
                         Queue* q, int grid, double* tscr, hipStream_t s) {
   if (nt == kSweepMaxNT) return launch_sweep_nt9(variant, inst, items, count, q, grid, tscr, s);
-  if (variant >= kFastHbm) {
+  if (variant >= kFastPlain) {
 #define C(N) launch_fast_sweep_nt##N(variant, inst, items, count, q, grid, tscr, s)
     SDQ_SWITCH(C)
 #undef C
@@ -106,7 +106,7 @@ hipError_t kernel_info(int kind, int nt, int variant, KernelInfo* out) {
     SDQ_SWITCH(C)
 #undef C
   }
-  if (kind == KK_SWEEP && variant >= kFastHbm) {
+  if (kind == KK_SWEEP && variant >= kFastPlain) {
 #define C(N) fast_sweep_info_nt##N(variant, out)
     SDQ_SWITCH(C)
 #undef C

@@ -194,10 +194,9 @@ constexpr int kSweepVariants = 6;
 // each, one wave per tile with T in the workgroup scratch like variant 4
 // The sweeps with the norm-sorted blocked QR (one wave per tile), which every
 // caller takes whose factors are not themselves a result:
-constexpr int kFastHbm = 7;    // slice exponential from its HBM copy
-constexpr int kFastLds = 8;    // staged in LDS (3 <= nt <= 5)
-constexpr int kFastDense = 9;  // dense slices
-constexpr int kFastProd = 10;  // block products (k_prod), tile counts kProdMinNT ..
+constexpr int kFastPlain = 7;  // slices E diag(v)
+constexpr int kFastDense = 8;  // dense slices
+constexpr int kFastProd = 9;   // block products (k_prod), tile counts kProdMinNT ..
 // T in the workgroup scratch between blocks (else in registers)
 __host__ __device__ constexpr bool fast_sweep_tg(int nt) { return nt >= 6; }
 __host__ __device__ constexpr bool sweep_variant_tg(int variant) {
@@ -206,7 +205,7 @@ __host__ __device__ constexpr bool sweep_variant_tg(int variant) {
 // doubles of T scratch per workgroup of a variant-4/5 sweep (0 otherwise):
 // one 16 x 16 FP64 tile = 256 doubles per (wave, tile column, tile row)
 __host__ __device__ inline int64_t sweep_tscr_doubles(int nt, int variant) {
-  if (!sweep_variant_tg(variant) && !(variant >= kFastHbm && fast_sweep_tg(nt))) return 0;
+  if (!sweep_variant_tg(variant) && !(variant >= kFastPlain && fast_sweep_tg(nt))) return 0;
   // above kMaxNT tiles the factor store (16 nt x (16 nt + 1)) follows T
   return (int64_t)nt * nt * 256 + (nt > kMaxNT ? (int64_t)16 * nt * (16 * nt + 1) : 0);
 }

@@ -15,7 +15,6 @@ namespace sdq {
 namespace {
 constexpr int NT = SDQ_NT;
 constexpr bool TG = fast_sweep_tg(NT);
-constexpr bool kLdsE = NT >= 3 && NT <= 5;   // the slice exponential beside the panels in LDS
 constexpr bool kLdsB = NT <= 5;              // a dense slice beside them
 template <class KF>
 hipError_t launch(KF kern, const Inst* inst, const SweepItem* items, int count, Queue* q, int grid, double* tscr,
@@ -26,9 +25,7 @@ hipError_t launch(KF kern, const Inst* inst, const SweepItem* items, int count, 
 }
 template <class F>
 hipError_t with_kernel(int variant, F f) {
-  if (variant == kFastLds && kLdsE) return f(k_sweep<NT, NT, kLdsE, false, false, TG, false, true>, kLdsE);
-  if (variant == kFastLds || variant == kFastHbm)
-    return f(k_sweep<NT, NT, false, false, false, TG, false, true>, false);
+  if (variant == kFastPlain) return f(k_sweep<NT, NT, false, false, false, TG, false, true>, false);
   if (variant == kFastDense) return f(k_sweep<NT, NT, kLdsB, false, true, TG, false, true>, kLdsB);
   if constexpr (NT >= kProdMinNT)
     if (variant == kFastProd) return f(k_sweep<NT, NT, false, false, true, true, true, true>, false);

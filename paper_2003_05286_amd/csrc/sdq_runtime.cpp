@@ -492,8 +492,7 @@ sdq_status build_plan(sdq_ctx* ctx, Plan& P, int32_t* status, int count, Built& 
     const int variant = sweep_is_gang(r.nt) ? (P.pivoted ? 1 : 0)
                         : fast ? (bprod               ? sdq::kFastProd
                                   : P.dense           ? sdq::kFastDense
-                                  : tuned == 1 || tuned == 5 ? sdq::kFastLds
-                                                      : sdq::kFastHbm)
+                                                      : sdq::kFastPlain)
                         : bprod ? 6
                         : r.nt > sdq::kMaxNT ? 4
                         : P.dense ? 3

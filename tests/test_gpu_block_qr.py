@@ -1,6 +1,5 @@
 """The stabilized sweeps' norm-sorted blocked QR at the sizes where it can go
-wrong: one tile to eight, full and ragged (n = 1, 16 j - 1, 16 j, 16 j + 1),
-last blocks shorter than k, against the oracle's column-pivoted chains; and
+wrong: one tile to eight and the gangs above, full and ragged, last blocks shorter than k, against the oracle's column-pivoted chains; and
 blocks whose columns are nearly dependent, where the order by norm is not
 good enough and the sort is repeated or the pivoted QR takes over.  Bar: the
 suite's relative 1e-10 per matrix; where B is scaled to norm 1/2, 1 + B has
@@ -44,6 +43,32 @@ def test_sizes(ctx, n):
             assert abs(l[i].item() - ldo) <= 1e-12 * max(1.0, abs(ldo)) and s[i].item() == sgo
         for q, l in enumerate(ls):
             assert relF(gts[i][q].cpu().numpy(), oracle.greens_tdisp(E, Ei, f, a, k, l)) <= 1e-10, l
+
+
+@pytest.mark.parametrize("n", [130, 145, 160, 161, 177, 241, 257, 272, 321, 336, 400])
+def test_gang_sizes(ctx, n):
+    """Chains over several workgroups: every split of a panel's rows and of a
+    column slab into tiles, ragged sizes; the second call reuses the scratch."""
+    m, k = 8, 3
+    E, Ei = wl.expk_pair(wl.chain_hopping_matrix(n), 0.1)
+    rng = np.random.default_rng(wl.BASE_SEED + n)
+    f = 2.0 * rng.integers(0, 2, (m, n)) - 1.0
+    lam = wl.hirsch_lambda(4.0, 0.1)
+    ch = [sdq.Chain(torch.from_numpy(E).to(DEV), torch.from_numpy(f).to(DEV), lam, k, torch.from_numpy(Ei).to(DEV))]
+    say(f"[gpu] gang sizes: n = {n}")
+    gts, gs, ld, sg, st = ctx.greens_tdisp(ch, [2, 6])
+    g2, ld2, sg2, st2 = ctx.greens(ch)
+    grads, ld3, sg3, st3 = ctx.logdet_grad(ch)
+    torch.cuda.synchronize()
+    assert st.item() == 0 and st2.item() == 0 and st3.item() == 0
+    G, ldo, sgo = oracle.greens(E, f, lam, k)
+    for g, l, s in ((gs[0], ld, sg), (g2[0], ld2, sg2), (None, ld3, sg3)):
+        if g is not None:
+            assert relF(g.cpu().numpy(), G) <= 1e-10
+        assert abs(l.item() - ldo) <= 1e-12 * max(1.0, abs(ldo)) and s.item() == sgo
+    for q, l in enumerate((2, 6)):
+        assert relF(gts[0][q].cpu().numpy(), oracle.greens_tdisp(E, Ei, f, lam, k, l)) <= 1e-10, l
+    assert relF(grads[0][3].cpu().numpy(), oracle.logdet_grad(E, f, lam, k, [4])[0]) <= 1e-10
 
 
 @pytest.mark.parametrize("n,noise", [(36, 1e-3), (64, 1e-3), (64, 1e-6), (64, 1e-9), (100, 1e-6), (128, 1e-3)])
