@@ -25,6 +25,37 @@
 constexpr int kTile = 256;
 __device__ __forceinline__ int tile_idx(int i, int c) { return 16 * i + (c ^ i); }
 
+// Above kMaxNT tiles (SM::RG) LDS holds the panels from their diagonal tile
+// down only; R's tiles above go to the workgroup's device memory (S.rg).
+template <int NT, class SM>
+__device__ __forceinline__ int panel_off(int p) {
+  return SM::RG ? (p * NT - p * (p - 1) / 2) * kTile : (p * NT + p) * kTile;
+}
+// (through a buffer resource with the tile in the scalar offset: no 64-bit
+// address per tile is kept in vector registers)
+template <class SM>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rg_rsrc(const SM& S, int bytes) {
+  const unsigned long long a = (unsigned long long)S.rg;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((unsigned long long)hi << 32) | lo), (short)0, bytes, 0x00020000);
+}
+typedef unsigned u2 __attribute__((ext_vector_type(2)));
+template <int NT, class SM>
+__device__ __forceinline__ double upper_ld(const SM& S, int p, int rt, int idx) {
+  if constexpr (SM::RG)
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rg_rsrc(S, NT * NT * kTile * 8), idx * 8,
+                                                                          (p * NT + rt) * kTile * 8, 0));
+  else return S.R[(p * NT + rt) * kTile + idx];
+}
+template <int NT, class SM>
+__device__ __forceinline__ void upper_st(SM& S, int p, int rt, int idx, double v) {
+  if constexpr (SM::RG)
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rg_rsrc(S, NT * NT * kTile * 8), idx * 8,
+                                          (p * NT + rt) * kTile * 8, 0);
+  else S.R[(p * NT + rt) * kTile + idx] = v;
+}
+
 // lane J of each 16-lane row to all lanes of the row (one instruction for
 // the 64-bit value)
 template <int J>
@@ -377,14 +408,14 @@ __device__ __forceinline__ void panel_factor(SM& S, double (&b)[NT][4], const in
   const Lane L = lane_id_per_item();
   double T[16], su_l, beta_l;
   const int cnt = NT - p;
-  double* pp = S.R + p * (NT * kTile);
+  double* vp = S.R + panel_off<NT, SM>(p);
   // R above the panel goes out first; its registers are zero rows from here on
 #pragma unroll
   for (int t = 1; t < NT; ++t)
     if (t >= cnt) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        pp[kTile * (t - cnt) + tile_idx(L.g + 4 * r, L.cl)] = b[t][r];
+        upper_st<NT>(S, p, t - cnt, tile_idx(L.g + 4 * r, L.cl), b[t][r]);
         b[t][r] = 0.0;
       }
     }
@@ -401,7 +432,7 @@ __device__ __forceinline__ void panel_factor(SM& S, double (&b)[NT][4], const in
   for (int t = 0; t < NT; ++t)
     if (t < cnt) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) pp[kTile * (p + t) + tile_idx(L.g + 4 * r, L.cl)] = b[t][r];
+      for (int r = 0; r < 4; ++r) vp[kTile * t + tile_idx(L.g + 4 * r, L.cl)] = b[t][r];
     }
   double* tw = S.tw + p * kTile;
 #pragma unroll
@@ -438,7 +469,7 @@ __device__ __forceinline__ void block_qr(const Lane& L, SM& S, double (&b)[NT][4
   for (int p = 0; p < NT; ++p) {
     if (L.w == p) panel_factor<NT>(S, b, p);
     __syncthreads();
-    const double* vp = S.R + p * (NT * kTile) + p * kTile;
+    const double* vp = S.R + panel_off<NT, SM>(p);
     const double* tw = S.tw + p * kTile;
     if (L.w > p) {
       panel_apply<NT, true>(b, NT - p, vp, tw, S.tau + 16 * p);
@@ -457,7 +488,7 @@ __device__ __forceinline__ void block_qr(const Lane& L, SM& S, double (&b)[NT][4
 template <int NT, bool FROM_R, class SM>
 __device__ __forceinline__ void block_form(const Lane& L, const SM& S, double (&b)[NT][4]) {
   const int w = L.w;
-  const double* rw = S.R + w * (NT * kTile);
+  const double* dg = S.R + panel_off<NT, SM>(w);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -465,19 +496,19 @@ __device__ __forceinline__ void block_form(const Lane& L, const SM& S, double (&
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int row = L.g + 4 * r;
-    if (FROM_R) b[0][r] = row <= L.cl ? rw[kTile * L.w + tile_idx(row, L.cl)] : 0.0;
+    if (FROM_R) b[0][r] = row <= L.cl ? dg[tile_idx(row, L.cl)] : 0.0;
     else b[0][r] = row == L.cl ? 1.0 : 0.0;
   }
 #pragma unroll 1
   for (int p = w; p >= 0; --p) {
     const Lane L = lane_id_per_item();
-    panel_apply<NT, false>(b, NT - p, S.R + p * (NT * kTile) + p * kTile, S.tw + p * kTile,
+    panel_apply<NT, false>(b, NT - p, S.R + panel_off<NT, SM>(p), S.tw + p * kTile,
                            S.tau + 16 * p);
     if (p > 0) {
       rotate_down<NT>(b);
       if (FROM_R) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) b[0][r] = rw[kTile * (p - 1) + tile_idx(L.g + 4 * r, L.cl)];
+        for (int r = 0; r < 4; ++r) b[0][r] = upper_ld<NT>(S, w, p - 1, tile_idx(L.g + 4 * r, L.cl));
       }
     }
   }

@@ -74,8 +74,9 @@ struct Smem {
   // fits in the CU's 160 KB of LDS beside the rest: it then lives in a
   // per-workgroup area of device memory (rg), accessed through r_ld / r_st.
   static constexpr bool RG = NT > kMaxNT;
-  // factor store, [col][row]; or the panels of the blocked QR (NT of NP x 16)
-  double R[RG ? 1 : G::NP * G::LDR];
+  // factor store, [col][row]; or the panels of the blocked QR (NT of NP x 16;
+  // with RG from their diagonal tiles down)
+  double R[RG ? NT * (NT + 1) / 2 * 256 : G::NP * G::LDR];
   double E[ELDS ? G::NP * G::LDR : 1];       // staged operand (sweep: swizzled E; pair: [row][col])
   union {
     struct {
@@ -1475,7 +1476,7 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = row_of(L, t, r);
-        S.R[rank * G::LDR + row] = live ? W[t][r] : (row == col ? 1.0 : 0.0);
+        r_st(S, rank * G::LDR + row, live ? W[t][r] : (row == col ? 1.0 : 0.0));
       }
     if (L.g == 0) {
       S.dcur[rank] = live ? scale : 1.0;
@@ -1486,7 +1487,7 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) W[t][r] = S.R[col * G::LDR + row_of(L, t, r)];
+      for (int r = 0; r < 4; ++r) W[t][r] = r_ld(S, col * G::LDR + row_of(L, t, r));
     scale = S.dcur[col];
     sort_t();
     block_qr<NT, 0>(L, S, W, nullptr);
@@ -1494,14 +1495,15 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
     L = lane_id_per_item();
     for (int t = L.t; t < G::NP; t += G::THREADS) S.dnew[t] = fabs(S.red_diag[t]) * S.dcur[t];
     double lift = 0.0;
-    const double* pw = S.R + L.w * (NT * kTile);
+    const double* dg = S.R + panel_off<NT, Smem<NT, NT, ELDS>>(L.w);
 #pragma unroll
     for (int t = 0; t < NT; ++t)
       if (t <= L.w) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int row = row_of(L, t, r);
-          const double x = pw[kTile * t + tile_idx(L.g + 4 * r, L.cl)];
+          const int at = tile_idx(L.g + 4 * r, L.cl);
+          const double x = t == L.w ? dg[at] : upper_ld<NT>(S, L.w, t, at);
           const double lim = kSortedGrowth * fabs(S.red_diag[row]) * S.dcur[row];
           const double y = fabs(x) * scale;
           if (row < col && y > lim) lift = fmax(lift, y);
@@ -1528,24 +1530,23 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
     for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int r = 0; r < 4; ++r) T.v[0][t][r] *= S.dcur[row_of(L, t, r)];
-    // T <- D^-1 R T, R upper triangular
-    d4 acc[NT];
+    // T <- D^-1 R T, R upper triangular: row tile ti needs T's tiles from ti on,
+    // so it can replace tile ti
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int ti = 0; ti < NT; ++ti) {
+      d4 acc = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int tk = 0; tk < NT; ++tk)
+      for (int tk = ti; tk < NT; ++tk)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int ti = 0; ti <= tk; ++ti) {
-          double a = S.R[(tk * NT + ti) * kTile + tile_idx(L.cl, L.g + 4 * r)];
+        for (int r = 0; r < 4; ++r) {
+          const int at = tile_idx(L.cl, L.g + 4 * r);
+          double a = ti == tk ? S.R[panel_off<NT, Smem<NT, NT, ELDS>>(tk) + at] : upper_ld<NT>(S, tk, ti, at);
           if (ti == tk) a = L.cl <= L.g + 4 * r ? a : 0.0;
-          acc[ti] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, T.v[0][tk][r], acc[ti], 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, T.v[0][tk][r], acc, 0, 0, 0);
         }
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) T.v[0][t][r] = acc[t][r] / S.dnew[row_of(L, t, r)];
+      for (int r = 0; r < 4; ++r) T.v[0][ti][r] = acc[r] / S.dnew[row_of(L, ti, r)];
+    }
     keep_t(T);
     block_form<NT, false>(L, S, W);
   } else {

@@ -9,17 +9,23 @@
 namespace sdq {
 
 // variant 4: slices E diag(exp(alpha f)); variant 6: the block products of
-// k_prod (swizzled), one factorization each
+// k_prod (swizzled), one factorization each; kFastPlain and kFastProd the
+// same with the norm-sorted blocked QR
+template <class F>
+static hipError_t with_kernel9(int variant, F f) {
+  if (variant == 4) return f(k_sweep<9, 9, false, false, false, true>);
+  if (variant == 6) return f(k_sweep<9, 9, false, false, true, true, true>);
+  if (variant == kFastPlain) return f(k_sweep<9, 9, false, false, false, true, false, true>);
+  if (variant == kFastProd) return f(k_sweep<9, 9, false, false, true, true, true, true>);
+  return hipErrorInvalidValue;
+}
 hipError_t launch_sweep_nt9(int variant, const Inst* inst, const SweepItem* items, int count, Queue* q,
                             int grid, double* tscr, hipStream_t s) {
-  if ((variant != 4 && variant != 6) || !tscr) return hipErrorInvalidValue;
-  if (variant == 6)
-    hipLaunchKernelGGL((k_sweep<9, 9, false, false, true, true, true>), dim3(grid), dim3(Geo<9, 9>::THREADS), 0, s,
-                       inst, items, count, q, tscr);
-  else
-    hipLaunchKernelGGL((k_sweep<9, 9, false, false, false, true>), dim3(grid), dim3(Geo<9, 9>::THREADS), 0, s,
-                       inst, items, count, q, tscr);
-  return hipGetLastError();
+  if (!tscr) return hipErrorInvalidValue;
+  return with_kernel9(variant, [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Geo<9, 9>::THREADS), 0, s, inst, items, count, q, tscr);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_prod_nt9(const Inst* inst, const SweepItem* items, int count, Queue* q, int grid, hipStream_t s) {
@@ -39,10 +45,8 @@ static hipError_t info9(KF kern, int lds, KernelInfo* out) {
 
 hipError_t kernel_info_nt9(int kind, int variant, KernelInfo* out) {
   if (kind == KK_PROD) return info9(k_prod<9, 9>, (int)sizeof(ProdSmem<9, 9>), out);
-  if (kind != KK_SWEEP || (variant != 4 && variant != 6)) return hipErrorInvalidValue;
-  if (variant == 6)
-    return info9(k_sweep<9, 9, false, false, true, true, true>, (int)sizeof(Smem<9, 9, false>), out);
-  return info9(k_sweep<9, 9, false, false, false, true>, (int)sizeof(Smem<9, 9, false>), out);
+  if (kind != KK_SWEEP) return hipErrorInvalidValue;
+  return with_kernel9(variant, [&](auto kern) { return info9(kern, (int)sizeof(Smem<9, 9, false>), out); });
 }
 
 }  // namespace sdq

@@ -487,7 +487,7 @@ sdq_status build_plan(sdq_ctx* ctx, Plan& P, int32_t* status, int count, Built& 
     // T and the factor store in workgroup scratch, variant 4; over block
     // products, variant 6)
     const bool bprod = ((P.bprod_mask >> r.nt) & 1u) != 0;
-    const bool fast = !P.pivoted && ctx->stab == SDQ_STAB_QR && r.nt <= sdq::kMaxNT;
+    const bool fast = !P.pivoted && ctx->stab == SDQ_STAB_QR && r.nt <= sdq::kSweepMaxNT;
     const int tuned = r.nt <= sdq::kMaxNT ? ctx->tune[r.nt].variant : 4;
     const int variant = sweep_is_gang(r.nt) ? (P.pivoted ? 1 : 0)
                         : fast ? (bprod               ? sdq::kFastProd
