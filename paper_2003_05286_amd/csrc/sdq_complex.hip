@@ -2,24 +2,37 @@
 // complex numbers, as the complex slices of App. B need it):
 //   W P = Q R (column-pivoted Householder QR), U = Q, D = |diag R|,
 //   T = D^{-1} R P^T.
-// One workgroup (four wave64s) per matrix, the matrix resident in LDS as
-// interleaved (re, im) pairs, n <= 64.  Reflector convention: for x = A[i:, i]
-// with alpha = x_0, beta = -sign(Re alpha) ||x|| is real, tau = (beta -
-// alpha) / beta, v = x / (alpha - beta); H = I - tau v v^H, H^H x = beta e_0,
-// so the diagonal of R is real.  Pivot: the first column of largest remaining
-// norm, norms downdated with an exact recompute when cancellation threatens
-// (Drmac & Bujanovic).  Q is formed in place from the reflectors after R has
-// been written out (backward accumulation, Q = H_0 H_1 ... H_{n-1}).
+// One workgroup (four wave64s) per matrix, n <= 64, held in registers while
+// it is factored (lane = column, the rows dealt to the waves) and in LDS, as
+// interleaved (re, im) pairs, for what follows.  Reflector convention: for
+// x = A[i:, i] with alpha = x_0, beta = -sign(Re alpha) ||x|| is real, tau =
+// (beta - alpha) / beta, v = x / (alpha - beta); H = I - tau v v^H, H^H x =
+// beta e_0, so the diagonal of R is real.  Pivot: the first column of largest
+// remaining norm, norms downdated with an exact recompute when cancellation
+// threatens (Drmac & Bujanovic).  Q is formed from the reflectors by backward
+// accumulation, Q = H_0 H_1 ... H_{n-1}.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "sdq_internal.h"
 
 namespace sdq {
 namespace {
 
-constexpr int kCN = 64;           // largest n
-constexpr int kCLD = kCN + 1;     // LDS row stride (in complex entries)
-constexpr int kCThreads = 256;    // four waves: wave w takes rows w, w+4, ...
+constexpr int kCN = 64;         // largest n
+constexpr int kCThreads = 256;  // four waves: wave w takes rows w, w+4, ...
+
+// The kernels are built for NT = 1 .. 4 tiles of 16 (n <= 16 NT): registers,
+// LDS and the padding of the products follow the size.
+template <int NT>
+struct Dim {
+  static constexpr int cn = 16 * NT;  // padded n
+  static constexpr int ld = cn + 1;   // LDS row stride (in complex entries)
+  // workgroups of a CU: what LDS and 512 registers a SIMD lane hold of them
+  static constexpr int udt_groups = NT == 4 ? 2 : NT == 3 ? 3 : NT == 2 ? 4 : 6;
+  static constexpr int chain_groups = NT >= 3 ? 1 : 2;
+};
 
 struct cplx {
   double x, y;
@@ -27,14 +40,6 @@ struct cplx {
 __device__ __forceinline__ cplx cmul(cplx a, cplx b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 // conj(a) * b
 __device__ __forceinline__ cplx cjmul(cplx a, cplx b) { return {a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x}; }
-
-struct CSmem {
-  cplx a[kCN * kCLD];
-  cplx red[4][kCN];
-  cplx tau[kCN];
-  double vn1[kCN], vn2[kCN];
-  int jpvt[kCN], ipiv[kCN];
-};
 
 // Cross-lane reductions over the wave on the DPP paths of the VALU (no LDS
 // round trips): swap neighbours (quad_perm 1,0,3,2 and 2,3,0,1), mirror
@@ -72,227 +77,400 @@ __device__ __forceinline__ double wave_sum_(double v) {
 __device__ __forceinline__ double wave_sum(double v) { return wave_sum_<0>(v); }
 
 // for values >= 0
-template <int S = 0>
-__device__ __forceinline__ double wave_max_(double v) {
-  if constexpr (S == 6) {
-    return lane63(v);
-  } else {
-    return wave_max_<S + 1>(fmax(v, dpp_d<S>(0.0, v)));
-  }
-}
-__device__ __forceinline__ double wave_max(double v) { return wave_max_<0>(v); }
+// LDS work space of the factorization and of applying its Q.
+struct QrScratch {
+  cplx sc[kCN];         // the reflectors' factors
+  cplx row[2][kCN];     // a row of a solution
+  cplx red[2][5][kCN];  // per wave: partial column products; [4]: row i
+  double beta[kCN];     // diag R
+};
 
-// (value, index) of the largest value, the lowest index among equal ones;
-// the result is the same for every reduction order
-template <int S = 0>
-__device__ __forceinline__ void wave_argmax_(double& v, int& p) {
-  if constexpr (S < 6) {
-    const double v2 = dpp_d<S>(v, v);
-    const int p2 = dpp_i<S>(p, p);
-    if (v2 > v || (v2 == v && p2 < p)) {
-      v = v2;
-      p = p2;
-    }
-    wave_argmax_<S + 1>(v, p);
-  }
-}
-__device__ __forceinline__ int wave_argmax(double v, int p) {
-  wave_argmax_<0>(v, p);
-  return __builtin_amdgcn_readlane(p, 63);
+// A matrix in registers: lane = column, wave w holds the rows 16 q + 4 t + w.
+// Every register index is static: a loop over the steps is one loop for each
+// 16 rows, which leaves out the rows that its steps don't touch.
+template <int NT>
+struct RegMat {
+  cplx a[NT][4];
+};
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+template <int NT, class F>
+__device__ __forceinline__ void each_row(F f) {
+  const int w = wave_id();
+#pragma unroll
+  for (int q = 0; q < NT; ++q)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) f(q, t, 16 * q + 4 * t + w);
 }
 
-// 2-norm of A[r0..n-1][c] by one lane (max-scaled, so no overflow)
-template <class SM>
-__device__ double col_norm(const SM& S, int r0, int n, int c) {
-  double mx = 0.0;
-  for (int r = r0; r < n; ++r) mx = fmax(mx, fmax(fabs(S.a[r * kCLD + c].x), fabs(S.a[r * kCLD + c].y)));
-  if (mx == 0.0) return 0.0;
-  const double inv = 1.0 / mx;
+// f(q, i) for the steps i of 0 .. n-1 upwards (or n-1 .. 0), q = i / 16 a
+// constant
+template <int Q>
+struct TileNo {
+  static constexpr int q = Q;
+};
+template <int NT, int Q = 0, class F>
+__device__ __forceinline__ void steps_up(int n, F f) {
+  if constexpr (Q < NT) {
+    for (int i = 16 * Q; i < min(n, 16 * Q + 16); ++i) f(TileNo<Q>{}, i);
+    steps_up<NT, Q + 1>(n, f);
+  }
+}
+template <int NT, int Q = NT - 1, class F>
+__device__ __forceinline__ void steps_down(int n, F f) {
+  if constexpr (Q >= 0) {
+    for (int i = min(n, 16 * Q + 16) - 1; i >= 16 * Q; --i) f(TileNo<Q>{}, i);
+    steps_down<NT, Q - 1>(n, f);
+  }
+}
+
+// A uniform value as one per lane, for conditions that select instead of
+// branch: a taken branch costs more than the four selects of a value.
+__device__ __forceinline__ int per_lane(int x) {
+  asm("" : "+v"(x));
+  return x;
+}
+__device__ __forceinline__ cplx select(bool c, cplx a, cplx b) { return {c ? a.x : b.x, c ? a.y : b.y}; }
+
+__device__ __forceinline__ double lane_of(double v, int l) {
+  const long long x = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)x, l), hi = __builtin_amdgcn_readlane((int)(x >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// A column as the wave's own rows use it: lane l < 4 NT holds row 4 l + w, and the rows are handed to the products as uniform values.
+// Sixteen broadcast reads of every wave instead would keep LDS busy longer
+// than the products take.
+template <int NT>
+__device__ __forceinline__ int own_row(int lane, int w) {
+  return 4 * min(lane & 15, 4 * NT - 1) + w;
+}
+__device__ __forceinline__ cplx row_of(cplx v, int q, int t) { return {lane_of(v.x, 4 * q + t), lane_of(v.y, 4 * q + t)}; }
+
+// Sums of the squares of the rows >= r0 of every column (lane = column),
+// 16 Q0 <= r0; the same in every wave.  One barrier inside; `buf` is a
+// QrScratch::red that no wave reads any more.
+template <int NT, int Q0>
+__device__ __forceinline__ double col_squares(cplx (*buf)[kCN], const RegMat<NT>& A, int r0) {
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const int w0 = per_lane(16 * Q0 + w - r0);  // row 16 Q0 + w + d counts if w0 + d >= 0
   double s = 0.0;
-  for (int r = r0; r < n; ++r) {
-    const double p = S.a[r * kCLD + c].x * inv, q = S.a[r * kCLD + c].y * inv;
-    s += p * p + q * q;
-  }
-  return mx * sqrt(s);
-}
-
-// orders the LDS accesses of one wave's lanes around it (compiler fence)
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// 2-norm of the wave's 64 complex values: the plain sum of squares where it
-// neither overflows nor underflows, else max-scaled
-__device__ __forceinline__ double wave_norm(cplx x) {
-  const double ss = wave_sum(x.x * x.x + x.y * x.y);
-  if (ss > 1e-280 && ss < 1e280) return sqrt(ss);
-  const double mx = wave_max(fmax(fabs(x.x), fabs(x.y)));
-  if (mx == 0.0) return 0.0;
-  const double p0 = x.x / mx, q0 = x.y / mx;
-  return mx * sqrt(wave_sum(p0 * p0 + q0 * q0));
-}
-
-// norm downdate of column `lane` after step i (exact recompute when the
-// downdated value has lost too many digits)
-template <class SM>
-__device__ __forceinline__ void downdate(SM& S, int n, int i, int lane, double tol3z) {
-  if (lane > i && lane < n && S.vn1[lane] != 0.0) {
-    const cplx aij = S.a[i * kCLD + lane];
-    double tmp = hypot(aij.x, aij.y) / S.vn1[lane];
-    tmp = 1.0 - tmp * tmp;
-    if (tmp < 0.0) tmp = 0.0;
-    const double ratio = S.vn1[lane] / S.vn2[lane];
-    if (tmp * ratio * ratio <= tol3z) {
-      S.vn1[lane] = i + 1 < n ? col_norm(S, i + 1, n, lane) : 0.0;
-      S.vn2[lane] = S.vn1[lane];
-    } else {
-      S.vn1[lane] *= sqrt(tmp);
+#pragma unroll
+  for (int q = Q0; q < NT; ++q)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int d = 16 * (q - Q0) + 4 * t;
+      const cplx x = d >= 16 ? A.a[q][t] : select(w0 + d >= 0, A.a[q][t], cplx{0.0, 0.0});
+      s = fma(x.x, x.x, fma(x.y, x.y, s));
     }
-  }
-}
-
-// A[i:, c] <- (I - t v v^H) A[i:, c] for the columns c0 <= c < n, v = A[i:, i]
-// with v_i = 1 implied (row i taken by wave 0 outside the loop); four waves
-// split the rows.
-template <class SM>
-__device__ void apply_reflector(SM& S, int n, int i, int c0, cplx t) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int c = lane;
-  const int r0 = w == 0 ? i + 4 : i + w;
-  cplx part = {0.0, 0.0};
-  if (c >= c0 && c < n) {
-    if (w == 0) part = S.a[i * kCLD + c];
-    // unrolled so that the LDS loads of several rows are in flight at once
-#pragma unroll 8
-    for (int r = r0; r < n; r += 4) {
-      const cplx p = cjmul(S.a[r * kCLD + i], S.a[r * kCLD + c]);
-      part.x += p.x;
-      part.y += p.y;
-    }
-  }
-  S.red[w][c] = part;
+  buf[w][lane].x = s;
   __syncthreads();
-  if (c >= c0 && c < n) {
-    cplx s = {S.red[0][c].x + S.red[1][c].x + S.red[2][c].x + S.red[3][c].x,
-              S.red[0][c].y + S.red[1][c].y + S.red[2][c].y + S.red[3][c].y};
-    s = cmul(t, s);
-    if (w == 0) {
-      S.a[i * kCLD + c].x -= s.x;
-      S.a[i * kCLD + c].y -= s.y;
-    }
-#pragma unroll 8
-    for (int r = r0; r < n; r += 4) {
-      const cplx d = cmul(S.a[r * kCLD + i], s);
-      S.a[r * kCLD + c].x -= d.x;
-      S.a[r * kCLD + c].y -= d.y;
-    }
-  }
-  __syncthreads();
+  return (buf[0][lane].x + buf[1][lane].x) + (buf[2][lane].x + buf[3][lane].x);
 }
 
-// Column-pivoted Householder QR of S.a (n x n, in place, columns swapped
-// physically): on return S.a holds R on and above the diagonal and the
-// reflectors below it, S.tau the reflector scalars, S.jpvt the original
-// column of each position.  Ends with a barrier.
-template <class SM>
-__device__ void cpqr_lds(SM& S, int n) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+// sqrt(c) and 1 / sqrt(c) (Goldschmidt from v_rsq_f64), 1 / c (Newton from
+// v_rcp_f64) to the last place or two, for c in 1e-285 .. 1e285: what the
+// library adds for the other arguments is a third of a step's scalar chain.
+__device__ __forceinline__ double sqrt_mid(double c, double* inv) {
+  const double y = __builtin_amdgcn_rsq(c);
+  double g = c * y, h = 0.5 * y;
+  double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  r = fma(-h, g, 0.5);
+  h = fma(h, r, h);
+  *inv = 2.0 * h;
+  return fma(fma(-g, g, c), h, g);
+}
+__device__ __forceinline__ double rcp_mid(double c) {
+  double y = __builtin_amdgcn_rcp(c);
+  y = fma(fma(-c, y, 1.0), y, y);
+  return fma(fma(-c, y, 1.0), y, y);
+}
+
+// lane of the largest key (keys >= 0, or -1 for none), among equal ones the
+// one of lowest `pos`.  The high words first: their maximum takes one DPP
+// operation a step and nearly always belongs to one lane.
+__device__ __forceinline__ int max_lane(double key, int pos) {
+  const long long k = __double_as_longlong(key);
+  const int hi = (int)(k >> 32);
+  int m = hi;
+#define SDQ_MAX_STEP(S) m = max(m, dpp_i<S>(m, m))
+  SDQ_MAX_STEP(0);
+  SDQ_MAX_STEP(1);
+  SDQ_MAX_STEP(2);
+  SDQ_MAX_STEP(3);
+  SDQ_MAX_STEP(4);
+  SDQ_MAX_STEP(5);
+#undef SDQ_MAX_STEP
+  m = __builtin_amdgcn_readlane(m, 63);
+  unsigned long long bl = __ballot(hi == m);
+  int best = __ffsll((long long)bl) - 1;
+#pragma unroll 1
+  while ((bl &= bl - 1) != 0) {
+    const int l = __ffsll((long long)bl) - 1;
+    const unsigned a = __builtin_amdgcn_readlane((int)k, l), b = __builtin_amdgcn_readlane((int)k, best);
+    if (a > b || (a == b && __builtin_amdgcn_readlane(pos, l) < __builtin_amdgcn_readlane(pos, best))) best = l;
+  }
+  return best;
+}
+
+// Column-pivoted Householder QR of M (n x n in LDS, zero below row n): on
+// return M holds R on and above the diagonal, columns permuted, and the
+// reflectors below it, tau the reflector scalars, jpvt the original column
+// of each position.  Ends with a barrier.
+//
+// A serial chain of n steps, bound by the instructions one step issues.  The
+// matrix is held in registers (lane = column) and a column keeps its lane
+// (its place in the order is a number), so a step passes over LDS only for
+// the pivot column and the products with it, with two barriers.  The products
+// are taken with the column itself: the pivot lane's own is its squared norm,
+// and every wave works out the reflector's scalars and the norms that remain
+// for itself from the same numbers.  Norms are kept as c2 = (norm / norm at
+// the last recompute)^2, so that a downdate is a subtraction; c2 is also what
+// Drmac & Bujanovic's test of a downdate asks for.
+//
+// 64 x 64 complex matrices, one / 4096 of them factored with Q and T: 0.34 ->
+// 0.16 ms / 3.23 -> 1.65 ms against the matrix in LDS with one wave choosing
+// pivots while three wait (three barriers a step); a step takes about 2900
+// cycles, and one of apply_q 1300.  At n = 16 the tile-sized variants take
+// 4096 matrices from 0.50 to 0.21 ms.
+template <int NT>
+__device__ __forceinline__ void cpqr_lds(cplx* M, QrScratch& X, cplx* tau, int* jpvt, int n) {
+  const int lane = threadIdx.x & 63, w = wave_id();
   const double tol3z = sqrt(2.220446049250313e-16);
-  if (tid < n) {
-    S.jpvt[tid] = tid;
-    S.vn1[tid] = col_norm(S, 0, n, tid);
-    S.vn2[tid] = S.vn1[tid];
+  RegMat<NT> A;
+  const int lc = min(lane, Dim<NT>::cn - 1);
+  each_row<NT>([&](int q, int t, int r) {
+    const cplx v = M[r * Dim<NT>::ld + lc];
+    A.a[q][t] = r < n && lane < n ? v : cplx{0.0, 0.0};
+  });
+  // every column to entries of at most 1 by a power of two, undone in R: a
+  // reflector does not depend on its column's scale, no square overflows, and
+  // a column whose squares vanish is zero to 1e-140 of what it was
+  double mx = 0.0;
+  each_row<NT>([&](int q, int t, int r) { mx = fmax(mx, fmax(fabs(A.a[q][t].x), fabs(A.a[q][t].y))); });
+  X.red[0][w][lane].x = mx;
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < 4; ++v) mx = fmax(mx, X.red[0][v][lane].x);
+  const int e = __builtin_amdgcn_frexp_exp(mx);
+  each_row<NT>([&](int q, int t, int r) { A.a[q][t] = cplx{ldexp(A.a[q][t].x, -e), ldexp(A.a[q][t].y, -e)}; });
+  int pos = lane;  // place of this lane's column
+  // squared norm at its last computation, its inverse, and what is left of it
+  double s0 = col_squares<NT, 0>(X.red[1], A, 0), c2 = 1.0;
+  double r0 = s0 > 1e-280 ? 1.0 / s0 : 0.0;
+  steps_up<NT>(n, [&](auto tile, int i) {
+    constexpr int iq = decltype(tile)::q;
+    const bool mine = w == (i & 3);  // this wave holds row i
+    // the column of largest remaining norm, the first among equals
+    double inv;
+    const double nk = r0 != 0.0 ? ldexp(sqrt_mid(s0 * c2, &inv), e) : 0.0;
+    const int lp = max_lane(pos >= i && lane < n ? (nk >= 0.0 ? nk : 0.0) : -1.0, pos);
+    const int p = __builtin_amdgcn_readlane(pos, lp);
+    if (pos == i) pos = p;
+    if (lane == lp) pos = i;
+    const int below = 16 * iq + w - i;  // row 16 iq + w + d is i + below + d
+    cplx row = {0.0, 0.0};
+    if (mine) {
+      const int b = per_lane(below);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) row = select(b + 4 * t == 0, A.a[iq][t], row);
+    }
+    cplx v[NT][4];  // uniform: the rows of the column that are this wave's
+    cplx part = {0.0, 0.0};
+#pragma unroll
+    for (int q = iq; q < NT; ++q)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const cplx x = {lane_of(A.a[q][t].x, lp), lane_of(A.a[q][t].y, lp)};
+        v[q][t] = q > iq || below + 4 * t > 0 ? x : cplx{0.0, 0.0};
+        const cplx z = cjmul(v[q][t], A.a[q][t]);
+        part.x += z.x;
+        part.y += z.y;
+      }
+    if (lane == lp) {
+#pragma unroll
+      for (int q = iq; q < NT; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          M[(16 * q + 4 * t + w) * Dim<NT>::ld + i] = A.a[q][t];
+    }
+    auto& red = X.red[i & 1];
+    red[w][lane] = part;
+    if (mine) red[4][lane] = row;
+    __syncthreads();
+    cplx g = {(red[0][lane].x + red[1][lane].x) + (red[2][lane].x + red[3][lane].x),
+              (red[0][lane].y + red[1][lane].y) + (red[2][lane].y + red[3][lane].y)};
+    cplx ri = red[4][lane];
+    // the reflector I - tau u u^H, u = (1, sc x), of (al, x): with
+    // dn = al - beta, tau = -dn / beta and sc = 1 / dn
+    const cplx al = {lane_of(ri.x, lp), lane_of(ri.y, lp)};
+    const double ss = lane_of(g.x, lp);
+    double beta = al.x, rb = 0.0;
+    cplx dn = {0.0, 0.0}, sc = {0.0, 0.0};
+    const double tot = ss + (al.x * al.x + al.y * al.y);
+    if (tot > 1e-280 && (ss != 0.0 || al.y != 0.0)) {
+      beta = -copysign(sqrt_mid(tot, &rb), al.x);
+      rb = -copysign(rb, al.x);
+      dn = cplx{al.x - beta, al.y};
+      const double rd = rcp_mid(fma(dn.x, dn.x, dn.y * dn.y));
+      sc = cplx{dn.x * rd, -dn.y * rd};
+    }
+    const cplx ti = {-dn.x * rb, -dn.y * rb};
+    // A -= conj(tau) u u^H A
+    const cplx ug = cjmul(sc, g);
+    g = cjmul(ti, cplx{ri.x + ug.x, ri.y + ug.y});
+    ri = cplx{ri.x - g.x, ri.y - g.y};
+    const cplx f = cmul(sc, g);
+#pragma unroll
+    for (int q = iq; q < NT; ++q) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const cplx z = cmul(v[q][t], f);
+        A.a[q][t].x -= z.x;
+        A.a[q][t].y -= z.y;
+      }
+    }
+    // row i's wave keeps the row and the reflector's scalars
+    if (mine) {
+      const int b = per_lane(below);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) A.a[iq][t] = select(b + 4 * t == 0, ri, A.a[iq][t]);
+      if (lane == 0) {
+        tau[i] = ti;
+        X.sc[i] = sc;
+        X.beta[i] = beta;
+        jpvt[i] = lp;
+      }
+    }
+    // the norms that remain, downdated by row i; recomputed where the
+    // difference has lost too many digits (the same lanes in every wave)
+    bool again = false;
+    if (pos > i && lane < n && r0 != 0.0) {
+      c2 -= fma(ri.x, ri.x, ri.y * ri.y) * r0;
+      again = !(c2 > tol3z);
+    }
+    if (__any(again)) {
+      const double sn = col_squares<NT, iq>(X.red[(i + 1) & 1], A, i + 1);
+      if (again) {
+        s0 = sn;
+        r0 = sn > 1e-280 ? 1.0 / sn : 0.0;
+        c2 = 1.0;
+      }
+    }
+  });
+  // R to the places of the columns; a lane's rows below its place are rounding
+  each_row<NT>([&](int q, int t, int r) {
+    if (lane < n && r < pos) M[r * Dim<NT>::ld + pos] = cplx{ldexp(A.a[q][t].x, e), ldexp(A.a[q][t].y, e)};
+  });
+  __syncthreads();
+  if (w == 0 && lane < n) {
+    const double b = ldexp(X.beta[pos], e);
+    X.beta[pos] = b;
+    M[pos * Dim<NT>::ld + pos] = cplx{b, 0.0};
   }
   __syncthreads();
-  for (int i = 0; i < n; ++i) {
-    // wave 0 alone, lane-synchronous (LDS operations of one wave complete
-    // in order): the norm downdate of step i-1, the pivot, the column swap
-    // and the reflector of step i; the other waves wait at the barrier
-    if (wv == 0) {
-      if (i > 0) downdate(S, n, i - 1, lane, tol3z);
-      wave_fence();
-      const int p = wave_argmax((lane >= i && lane < n) ? S.vn1[lane] : -1.0, lane);
-      if (p != i) {
-        if (lane < n) {
-          const cplx x = S.a[lane * kCLD + i];
-          S.a[lane * kCLD + i] = S.a[lane * kCLD + p];
-          S.a[lane * kCLD + p] = x;
-        }
-        if (lane == 0) {
-          const int tj = S.jpvt[i];
-          S.jpvt[i] = S.jpvt[p];
-          S.jpvt[p] = tj;
-          S.vn1[p] = S.vn1[i];
-          S.vn2[p] = S.vn2[i];
-        }
-      }
-      wave_fence();
-      // reflector of A[i:, i]; lane handles row i + 1 + lane
-      const int r = i + 1 + lane;
-      const cplx x = r < n ? S.a[r * kCLD + i] : cplx{0.0, 0.0};
-      const double xnorm = wave_norm(x);
-      const cplx al = S.a[i * kCLD + i];
-      cplx ti = {0.0, 0.0};
-      if (xnorm != 0.0 || al.y != 0.0) {
-        const double nrm = hypot(hypot(al.x, al.y), xnorm);
-        const double beta = -copysign(nrm, al.x);
-        ti = {(beta - al.x) / beta, -al.y / beta};
-        // s = 1 / (alpha - beta), scaled so that no square overflows
-        const cplx dn = {al.x - beta, al.y};
-        const double sm = fmax(fabs(dn.x), fabs(dn.y));
-        const double ax = dn.x / sm, ay = dn.y / sm, den = (ax * ax + ay * ay) * sm;
-        const cplx sc = {ax / den, -ay / den};
-        if (r < n) S.a[r * kCLD + i] = cmul(x, sc);
-        wave_fence();
-        if (lane == 0) S.a[i * kCLD + i] = {beta, 0.0};
-      }
-      if (lane == 0) S.tau[i] = ti;
-    }
-    __syncthreads();
-    const cplx ti = S.tau[i];
-    if (ti.x != 0.0 || ti.y != 0.0) apply_reflector(S, n, i, i + 1, cplx{ti.x, -ti.y});
-  }
 }
 
-// Q = H_0 H_1 ... H_{n-1} in place in S.a from the reflectors cpqr_lds left
-// there (backward accumulation).  Ends with a barrier.
-template <class SM>
-__device__ void form_q_lds(SM& S, int n) {
-  const int tid = threadIdx.x;
-  // Q in place: for i = n-1 .. 0, apply H_i to columns i+1.. and turn
-  // column i into H_i e_i
-  for (int i = n - 1; i >= 0; --i) {
-    const cplx ti = S.tau[i];
-    if (i < n - 1 && (ti.x != 0.0 || ti.y != 0.0)) apply_reflector(S, n, i, i + 1, ti);
-    if (tid < n) {
-      if (tid > i) {
-        const cplx v = S.a[tid * kCLD + i];
-        S.a[tid * kCLD + i] = cplx{-(ti.x * v.x - ti.y * v.y), -(ti.x * v.y + ti.y * v.x)};
-      } else if (tid == i) {
-        S.a[tid * kCLD + i] = cplx{1.0 - ti.x, -ti.y};
-      } else {
-        S.a[tid * kCLD + i] = cplx{0.0, 0.0};
+// A <- Q A (or Q^H A) for Q = H_0 H_1 ... H_{n-1} from the reflectors
+// cpqr_lds left below the diagonal of M, A in registers: one barrier per
+// reflector, every wave with its own rows.  M is zero below row n.
+template <int NT, bool ADJ>
+__device__ __forceinline__ void apply_q(const cplx* M, QrScratch& X, const cplx* tau, int n, RegMat<NT>& A) {
+  const int lane = threadIdx.x & 63, w = wave_id();
+  auto step = [&](auto tile, int i) {
+    constexpr int iq = decltype(tile)::q;
+    const int own = own_row<NT>(lane, w);
+    const cplx vl = select(own > i, cmul(M[own * Dim<NT>::ld + i], X.sc[i]), cplx{own == i ? 1.0 : 0.0, 0.0});
+    cplx part = {0.0, 0.0};
+#pragma unroll
+    for (int q = iq; q < NT; ++q)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const cplx z = cjmul(row_of(vl, q, t), A.a[q][t]);
+        part.x += z.x;
+        part.y += z.y;
+      }
+    auto& red = X.red[i & 1];
+    red[w][lane] = part;
+    cplx ti = tau[i];
+    if (ADJ) ti.y = -ti.y;
+    __syncthreads();
+    const cplx g = cmul(ti, cplx{(red[0][lane].x + red[1][lane].x) + (red[2][lane].x + red[3][lane].x),
+                                 (red[0][lane].y + red[1][lane].y) + (red[2][lane].y + red[3][lane].y)});
+#pragma unroll
+    for (int q = iq; q < NT; ++q) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const cplx z = cmul(row_of(vl, q, t), g);
+        A.a[q][t].x -= z.x;
+        A.a[q][t].y -= z.y;
       }
     }
-    __syncthreads();
-  }
+  };
+  if constexpr (ADJ)
+    steps_up<NT>(n, step);
+  else
+    steps_down<NT>(n, step);
 }
 
-__global__ __launch_bounds__(kCThreads) void k_udt_complex(int n, int count, const double* __restrict__ w,
+// Q of the reflectors in M into M itself; what is outside n x n becomes zero.
+// Ends with a barrier.
+template <int NT>
+__device__ __forceinline__ void form_q_lds(cplx* M, QrScratch& X, const cplx* tau, int n) {
+  const int lane = threadIdx.x & 63;
+  RegMat<NT> A;
+  each_row<NT>([&](int q, int t, int r) { A.a[q][t] = cplx{r == lane && r < n ? 1.0 : 0.0, 0.0}; });
+  apply_q<NT, false>(M, X, tau, n, A);
+  __syncthreads();
+  if (lane < Dim<NT>::cn) each_row<NT>([&](int q, int t, int r) { M[r * Dim<NT>::ld + lane] = A.a[q][t]; });
+  __syncthreads();
+}
+
+// det Q, the product of det H_j = -tau_j / conj(tau_j), by every wave on its
+// own (lane = reflector).
+__device__ __forceinline__ cplx det_q(const cplx* tau, int n) {
+  const int lane = threadIdx.x & 63;
+  cplx h = {1.0, 0.0};
+  if (lane < n) {
+    const cplx t = tau[lane];
+    if (t.x != 0.0 || t.y != 0.0) {
+      const double a2 = t.x * t.x + t.y * t.y;
+      h = cplx{-(t.x * t.x - t.y * t.y) / a2, -(2.0 * t.x * t.y) / a2};
+    }
+  }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) h = cmul(h, cplx{__shfl_xor(h.x, d), __shfl_xor(h.y, d)});
+  return h;
+}
+
+template <int NT>
+struct CSmem {
+  cplx a[Dim<NT>::cn * Dim<NT>::ld];
+  QrScratch x;
+  cplx tau[kCN];
+  int jpvt[kCN], ipiv[kCN];
+};
+
+template <int NT>
+__global__ __launch_bounds__(kCThreads, Dim<NT>::udt_groups) void k_udt_complex(int n, int count, const double* __restrict__ w,
                                                            double* __restrict__ u, double* __restrict__ d,
                                                            double* __restrict__ t) {
-  __shared__ CSmem S;
+  __shared__ CSmem<NT> S;
+  constexpr int CN = Dim<NT>::cn, LD = Dim<NT>::ld;
   const int tid = threadIdx.x;
   for (int b = blockIdx.x; b < count; b += gridDim.x) {
     const size_t off = (size_t)b * n * n;
     const cplx* W = reinterpret_cast<const cplx*>(w) + off;
-    for (int e = tid; e < n * n; e += kCThreads) S.a[(e / n) * kCLD + e % n] = W[e];
+    for (int e = tid; e < CN * CN; e += kCThreads) {
+      const int r = e / CN, c = e % CN;
+      S.a[r * LD + c] = r < n && c < n ? W[r * n + c] : cplx{0.0, 0.0};
+    }
     __syncthreads();
-    cpqr_lds(S, n);
+    cpqr_lds<NT>(S.a, S.x, S.tau, S.jpvt, n);
     // D = |diag R| (real), T = D^{-1} R P^T (rows with D = 0 undivided)
     if (tid < n) {
-      d[(size_t)b * n + tid] = fabs(S.a[tid * kCLD + tid].x);
+      d[(size_t)b * n + tid] = fabs(S.a[tid * LD + tid].x);
       S.ipiv[S.jpvt[tid]] = tid;
     }
     __syncthreads();
@@ -301,16 +479,16 @@ __global__ __launch_bounds__(kCThreads) void k_udt_complex(int n, int count, con
       const int r = e / n, col = e % n, c = S.ipiv[col];
       cplx v = {0.0, 0.0};
       if (c >= r) {
-        const double dr = fabs(S.a[r * kCLD + r].x);
+        const double dr = fabs(S.a[r * LD + r].x);
         const double sc = dr > 0.0 ? 1.0 / dr : 1.0;
-        v = {S.a[r * kCLD + c].x * sc, S.a[r * kCLD + c].y * sc};
+        v = {S.a[r * LD + c].x * sc, S.a[r * LD + c].y * sc};
       }
       T[e] = v;
     }
     __syncthreads();
-    form_q_lds(S, n);
+    form_q_lds<NT>(S.a, S.x, S.tau, n);
     cplx* U = reinterpret_cast<cplx*>(u) + off;
-    for (int e = tid; e < n * n; e += kCThreads) U[e] = S.a[(e / n) * kCLD + e % n];
+    for (int e = tid; e < n * n; e += kCThreads) U[e] = S.a[(e / n) * LD + e % n];
     __syncthreads();
   }
 }
@@ -325,43 +503,46 @@ __global__ __launch_bounds__(kCThreads) void k_udt_complex(int n, int count, con
 //     U = Q formed in place;
 //   inversion (Sec. 5.1, Loh's split, in the mirror form of the real path):
 //     1 + U D T = U D_p (D_p^{-1} U^H + D_m T), so G = M^{-1} D_p^{-1} U^H
-//     with M = D_p^{-1} U^H + D_m T, solved by Gaussian elimination with
-//     partial pivoting (row swaps in LDS) and back substitution;
+//     with M = D_p^{-1} U^H + D_m T, solved through the same pivoted QR, Q^H
+//     applied to the right-hand sides in registers, and back substitution;
 //   determinant: det(1 + B) = det U prod(D_p) det M, det U the product of
 //     det H_j = -tau_j / conj(tau_j) over the reflectors of the last QR, det M
-//     the product of the pivots and the row-swap signs.
+//     that of its own, the diagonal of R and the sign of the permutation.
+// 128 chains of 200 slices, k = 10, n = 64: 10.5 -> 5.6 ms, of which the
+// slice products take 2.3 (1.4 at the FP64 matrix rate of the 128 CUs in use),
+// 21 factorizations 3; the elimination in LDS that the QR replaced took 0.6.
+template <int NT>
 struct CCSmem {
-  cplx a[kCN * kCLD];  // W, then R and the reflectors, then U = Q, then the right-hand sides / G
-  cplx t[kCN * kCLD];  // T, then M
-  cplx red[4][kCN];
+  cplx a[Dim<NT>::cn * Dim<NT>::ld];  // W, then R and the reflectors, then U = Q, then the right-hand sides / G
+  cplx t[Dim<NT>::cn * Dim<NT>::ld];  // T, then M
+  QrScratch x;
   cplx tau[kCN];
-  double vn1[kCN], vn2[kCN];
   double d[kCN];  // D of the current factorization
-  int jpvt[kCN], ipiv[kCN];
-  int piv;
+  int jpvt[kCN];
 };
 
 typedef double cd4 __attribute__((ext_vector_type(4)));
 
-// C = A X for the n x n (padded to 64) complex matrices A (by a callable:
+// C = A X for the n x n (padded to 16 NT) complex matrices A (by a callable:
 // A(i, k) for the calling lane) and X in LDS (X(k, c) callable): wave w
-// produces the output columns 16 w .. 16 w + 15, all four row tiles, into
+// (w < NT) produces the output columns 16 w .. 16 w + 15, all row tiles, into
 // cr / ci in the FP64 MFMA 16x16x4 accumulator layout (lane l: rows
 // 16 ti + l / 16 + 4 r of column 16 w + l % 16).
-template <class AF, class XF>
-__device__ __forceinline__ void cgemm(AF A, XF X, cd4 (&cr)[4], cd4 (&ci)[4]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+template <int NT, class AF, class XF>
+__device__ __forceinline__ void cgemm(AF A, XF X, cd4 (&cr)[NT], cd4 (&ci)[NT]) {
+  const int lane = threadIdx.x & 63, w = wave_id();
+  if (NT < 4 && w >= NT) return;
   const int g = lane >> 4, cl = lane & 15;
 #pragma unroll
-  for (int ti = 0; ti < 4; ++ti) cr[ti] = ci[ti] = cd4{0.0, 0.0, 0.0, 0.0};
+  for (int ti = 0; ti < NT; ++ti) cr[ti] = ci[ti] = cd4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int tk = 0; tk < 4; ++tk) {
+  for (int tk = 0; tk < NT; ++tk) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int kk = 16 * tk + g + 4 * r;
       const cplx b = X(kk, 16 * w + cl);
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti) {
+      for (int ti = 0; ti < NT; ++ti) {
         const cplx a = A(16 * ti + cl, kk);
         cr[ti] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, cr[ti], 0, 0, 0);
         cr[ti] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, cr[ti], 0, 0, 0);
@@ -378,19 +559,20 @@ __device__ __forceinline__ void cgemm(AF A, XF X, cd4 (&cr)[4], cd4 (&ci)[4]) {
 // and the next tile's loads are in flight while the current tile's MFMAs
 // run: a load behind a per-entry branch would be waited for before the
 // next one.
-template <class XF>
-__device__ __forceinline__ void cgemm_hbm(const cplx* Bq, int n, XF X, cd4 (&cr)[4], cd4 (&ci)[4]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+template <int NT, class XF>
+__device__ __forceinline__ void cgemm_hbm(const cplx* Bq, int n, XF X, cd4 (&cr)[NT], cd4 (&ci)[NT]) {
+  const int lane = threadIdx.x & 63, w = wave_id();
+  if (NT < 4 && w >= NT) return;
   const int g = lane >> 4, cl = lane & 15;
   const auto* gB = (const __attribute__((address_space(1))) double*)Bq;
 #pragma unroll
-  for (int ti = 0; ti < 4; ++ti) cr[ti] = ci[ti] = cd4{0.0, 0.0, 0.0, 0.0};
-  cplx a[2][4][4];  // [buffer][r][ti]
-  auto load = [&](int tk, cplx (&dst)[4][4]) {
+  for (int ti = 0; ti < NT; ++ti) cr[ti] = ci[ti] = cd4{0.0, 0.0, 0.0, 0.0};
+  cplx a[2][4][NT];  // [buffer][r][ti]
+  auto load = [&](int tk, cplx (&dst)[4][NT]) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti) {
+      for (int ti = 0; ti < NT; ++ti) {
         const int i = 16 * ti + cl, kk = 16 * tk + g + 4 * r;
         const size_t off = 2 * ((size_t)min(i, n - 1) * n + min(kk, n - 1));
         dst[r][ti] = cplx{gB[off], gB[off + 1]};
@@ -398,14 +580,14 @@ __device__ __forceinline__ void cgemm_hbm(const cplx* Bq, int n, XF X, cd4 (&cr)
   };
   load(0, a[0]);
 #pragma unroll
-  for (int tk = 0; tk < 4; ++tk) {
-    if (tk + 1 < 4) load(tk + 1, a[(tk + 1) & 1]);
+  for (int tk = 0; tk < NT; ++tk) {
+    if (tk + 1 < NT) load(tk + 1, a[(tk + 1) & 1]);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int kk = 16 * tk + g + 4 * r;
       const cplx b = X(kk, 16 * w + cl);
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti) {
+      for (int ti = 0; ti < NT; ++ti) {
         const bool ok = 16 * ti + cl < n && kk < n;
         const cplx av = a[tk & 1][r][ti];
         const double ax = ok ? av.x : 0.0, ay = ok ? av.y : 0.0;
@@ -420,191 +602,147 @@ __device__ __forceinline__ void cgemm_hbm(const cplx* Bq, int n, XF X, cd4 (&cr)
 
 // write the accumulators of cgemm to an LDS matrix, each column scaled by
 // cs(c) and each row by rs(i)
-template <class CS, class RS>
-__device__ __forceinline__ void cstore(cplx* M, const cd4 (&cr)[4], const cd4 (&ci)[4], CS cs, RS rs) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+template <int NT, class CS, class RS>
+__device__ __forceinline__ void cstore(cplx* M, const cd4 (&cr)[NT], const cd4 (&ci)[NT], CS cs, RS rs) {
+  const int lane = threadIdx.x & 63, w = wave_id();
+  if (NT < 4 && w >= NT) return;
   const int g = lane >> 4, c = 16 * w + (lane & 15);
   const double sc = cs(c);
 #pragma unroll
-  for (int ti = 0; ti < 4; ++ti)
+  for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = 16 * ti + g + 4 * r;
       const double f = sc * rs(i);
-      M[i * kCLD + c] = cplx{cr[ti][r] * f, ci[ti][r] * f};
+      M[i * Dim<NT>::ld + c] = cplx{cr[ti][r] * f, ci[ti][r] * f};
     }
 }
 
-__global__ __launch_bounds__(kCThreads) void k_greens_complex(const CChain* __restrict__ tab, int count) {
-  __shared__ CCSmem S;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+template <int NT>
+__global__ __launch_bounds__(kCThreads, Dim<NT>::chain_groups) void k_greens_complex(const CChain* __restrict__ tab, int count) {
+  __shared__ CCSmem<NT> S;
+  constexpr int CN = Dim<NT>::cn, LD = Dim<NT>::ld;
+  const int tid = threadIdx.x, lane = tid & 63, wv = wave_id();
   for (int b = blockIdx.x; b < count; b += gridDim.x) {
     const CChain C = tab[b];
     const int n = C.n, m = C.m, k = C.k;
     const cplx* Bs = reinterpret_cast<const cplx*>(C.slices);
     // W = U = 1, T = 1, D = 1; the padding of both matrices zero
-    for (int e = tid; e < kCN * kCLD; e += kCThreads) {
-      const int i = e / kCLD, j = e % kCLD;
+    for (int e = tid; e < CN * LD; e += kCThreads) {
+      const int i = e / LD, j = e % LD;
       const cplx one = {(i == j && i < n) ? 1.0 : 0.0, 0.0};
       S.a[e] = one;
       S.t[e] = one;
     }
-    if (tid < kCN) S.d[tid] = 1.0;
+    if (tid < CN) S.d[tid] = 1.0;
     __syncthreads();
     for (int q0 = 1; q0 <= m; q0 += k) {
       const int q1 = q0 + k - 1 < m ? q0 + k - 1 : m;
       // W <- B_q W for q = q0 .. q1; after the last, W <- W D
       for (int q = q0; q <= q1; ++q) {
         const cplx* Bq = Bs + (size_t)(q - 1) * n * n;
-        cd4 cr[4], ci[4];
-        cgemm_hbm(Bq, n, [&](int kk, int c) -> cplx { return S.a[kk * kCLD + c]; }, cr, ci);
+        cd4 cr[NT], ci[NT];
+        cgemm_hbm<NT>(Bq, n, [&](int kk, int c) -> cplx { return S.a[kk * LD + c]; }, cr, ci);
         __syncthreads();
         const bool last = q == q1;
-        cstore(S.a, cr, ci, [&](int c) { return last ? S.d[c] : 1.0; }, [](int) { return 1.0; });
+        cstore<NT>(S.a, cr, ci, [&](int c) { return last ? S.d[c] : 1.0; }, [](int) { return 1.0; });
         __syncthreads();
       }
       // pivoted QR, D <- |diag R|
-      cpqr_lds(S, n);
+      cpqr_lds<NT>(S.a, S.x, S.tau, S.jpvt, n);
       __syncthreads();
-      if (tid < n) S.d[tid] = fabs(S.a[tid * kCLD + tid].x);
-      if (tid >= n && tid < kCN) S.jpvt[tid] = tid;
+      if (tid < n) S.d[tid] = fabs(S.a[tid * LD + tid].x);
+      if (tid >= n && tid < CN) S.jpvt[tid] = tid;
       __syncthreads();
       // T <- D^{-1} R P^T T: row i of the result is sum_{j >= i} R[i][j] T[jpvt[j]][:] / D_i
       {
-        cd4 cr[4], ci[4];
-        cgemm([&](int i, int j) -> cplx { return (i < n && j < n && j >= i) ? S.a[i * kCLD + j] : cplx{0.0, 0.0}; },
-              [&](int j, int c) -> cplx { return S.t[S.jpvt[j] * kCLD + c]; }, cr, ci);
+        cd4 cr[NT], ci[NT];
+        cgemm<NT>([&](int i, int j) -> cplx { return (i < n && j < n && j >= i) ? S.a[i * LD + j] : cplx{0.0, 0.0}; },
+              [&](int j, int c) -> cplx { return S.t[S.jpvt[j] * LD + c]; }, cr, ci);
         __syncthreads();
-        cstore(S.t, cr, ci, [](int) { return 1.0; },
+        cstore<NT>(S.t, cr, ci, [](int) { return 1.0; },
                [&](int i) { return (i < n && S.d[i] > 0.0) ? 1.0 / S.d[i] : 1.0; });
         __syncthreads();
       }
       // U = Q in place
-      form_q_lds(S, n);
+      form_q_lds<NT>(S.a, S.x, S.tau, n);
     }
-    // phase of det U: the reflectors of the last QR
-    if (wv == 0) {
-      double pr = 1.0, pi = 0.0;
-      if (lane == 0) {
-        for (int j = 0; j < n; ++j) {
-          const cplx t = S.tau[j];
-          if (t.x == 0.0 && t.y == 0.0) continue;
-          // -tau / conj(tau) = -tau^2 / |tau|^2
-          const double a2 = t.x * t.x + t.y * t.y;
-          const cplx h = {-(t.x * t.x - t.y * t.y) / a2, -(2.0 * t.x * t.y) / a2};
-          const double nr = pr * h.x - pi * h.y, ni = pr * h.y + pi * h.x;
-          pr = nr;
-          pi = ni;
-        }
-        S.red[0][0] = cplx{pr, pi};
-      }
-    }
-    __syncthreads();
-    const cplx phu = S.red[0][0];
+    const cplx phu = det_q(S.tau, n);  // phase of det U: the reflectors of the last QR
     // M = D_p^{-1} U^H + D_m T into S.t (reads U, writes T's own entry)
     for (int e = tid; e < n * n; e += kCThreads) {
       const int i = e / n, j = e % n;
       const double di = S.d[i], dp = di > 1.0 ? di : 1.0, dm = di > 1.0 ? 1.0 : di;
-      const cplx u = S.a[j * kCLD + i];
-      const cplx t = S.t[i * kCLD + j];
-      S.t[i * kCLD + j] = cplx{u.x / dp + dm * t.x, -u.y / dp + dm * t.y};
+      const cplx u = S.a[j * LD + i];
+      const cplx t = S.t[i * LD + j];
+      S.t[i * LD + j] = cplx{u.x / dp + dm * t.x, -u.y / dp + dm * t.y};
     }
     __syncthreads();
-    // right-hand sides D_p^{-1} U^H into S.a, in place by pairs (i, j), (j, i)
-    for (int e = tid; e < n * n; e += kCThreads) {
-      const int i = e / n, j = e % n;
-      if (j < i) continue;
-      const cplx uij = S.a[i * kCLD + j], uji = S.a[j * kCLD + i];
-      const double dpi = S.d[i] > 1.0 ? S.d[i] : 1.0, dpj = S.d[j] > 1.0 ? S.d[j] : 1.0;
-      S.a[i * kCLD + j] = cplx{uji.x / dpi, -uji.y / dpi};
-      S.a[j * kCLD + i] = cplx{uij.x / dpj, -uij.y / dpj};
-    }
+    // G = M^{-1} D_p^{-1} U^H through the pivoted QR of M: the right-hand
+    // sides in registers (lane = column), Q^H applied by reflectors, then
+    // back substitution with the rows of the result passed over LDS
+    RegMat<NT> Y;
+    each_row<NT>([&](int q, int t, int r) {
+      const cplx u = S.a[min(lane, CN - 1) * LD + r];
+      const double dp = r < n && S.d[r] > 1.0 ? S.d[r] : 1.0;
+      Y.a[q][t] = r < n && lane < n ? cplx{u.x / dp, -u.y / dp} : cplx{0.0, 0.0};
+    });
+    __syncthreads();  // det_q has read tau
+    cpqr_lds<NT>(S.t, S.x, S.tau, S.jpvt, n);
+    apply_q<NT, true>(S.t, S.x, S.tau, n, Y);
     __syncthreads();
-    // Gaussian elimination with partial pivoting on M, the same row
-    // operations on the right-hand sides
-    double ldm = 0.0, ppr = 1.0, ppi = 0.0;  // log|det M| and its phase (thread 0)
-    for (int j = 0; j < n; ++j) {
-      if (wv == 0) {
-        const double am = (lane >= j && lane < n) ? hypot(S.t[lane * kCLD + j].x, S.t[lane * kCLD + j].y) : -1.0;
-        const int p = wave_argmax(am, lane);
-        if (lane == 0) S.piv = p;
-      }
-      __syncthreads();
-      const int p = S.piv;
-      if (p != j) {
-        for (int e = tid; e < 2 * n; e += kCThreads) {
-          cplx* Mt = e < n ? S.t : S.a;
-          const int c = e < n ? e : e - n;
-          const cplx x = Mt[j * kCLD + c];
-          Mt[j * kCLD + c] = Mt[p * kCLD + c];
-          Mt[p * kCLD + c] = x;
+    if (tid < n) S.x.beta[tid] = 1.0 / S.x.beta[tid];
+    __syncthreads();
+    steps_down<NT>(n, [&](auto tile, int j) {
+      constexpr int jq = decltype(tile)::q;
+      cplx* row = S.x.row[j & 1];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (16 * jq + 4 * t + wv == j) {
+          const double rb = S.x.beta[j];
+          Y.a[jq][t] = cplx{Y.a[jq][t].x * rb, Y.a[jq][t].y * rb};
+          row[lane] = Y.a[jq][t];
         }
-        __syncthreads();
-      }
-      const cplx pv = S.t[j * kCLD + j];
-      if (tid == 0) {
-        const double ap = hypot(pv.x, pv.y);
-        ldm += log(ap);
-        const double ux = pv.x / ap, uy = pv.y / ap;
-        const double nr = ppr * ux - ppi * uy, ni = ppr * uy + ppi * ux;
-        ppr = p != j ? -nr : nr;
-        ppi = p != j ? -ni : ni;
-      }
-      // 1 / pivot, scaled so that no square overflows
-      const double sm = fmax(fabs(pv.x), fabs(pv.y));
-      const double ax = pv.x / sm, ay = pv.y / sm, den = (ax * ax + ay * ay) * sm;
-      const cplx rp = {ax / den, -ay / den};
-      // rows r > j: M[r][c] -= l_r M[j][c] (c > j), rhs[r][:] -= l_r rhs[j][:]
-      const int rows = n - 1 - j;
-      for (int e = tid; e < rows * 2 * n; e += kCThreads) {
-        const int r = j + 1 + e / (2 * n), cc = e % (2 * n);
-        const cplx l = cmul(S.t[r * kCLD + j], rp);
-        if (cc < n) {
-          if (cc > j) {
-            const cplx x = cmul(l, S.t[j * kCLD + cc]);
-            S.t[r * kCLD + cc].x -= x.x;
-            S.t[r * kCLD + cc].y -= x.y;
-          }
-        } else {
-          const int c = cc - n;
-          const cplx x = cmul(l, S.a[j * kCLD + c]);
-          S.a[r * kCLD + c].x -= x.x;
-          S.a[r * kCLD + c].y -= x.y;
+      __syncthreads();
+      const cplx y = row[lane];
+#pragma unroll
+      for (int q = 0; q <= jq; ++q) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int r = 16 * q + 4 * t + wv;
+          const cplx z = cmul(r < j ? S.t[r * LD + j] : cplx{0.0, 0.0}, y);
+          Y.a[q][t].x -= z.x;
+          Y.a[q][t].y -= z.y;
         }
       }
-      __syncthreads();
-    }
-    // back substitution: rhs <- U^{-1} rhs
-    for (int j = n - 1; j >= 0; --j) {
-      const cplx pv = S.t[j * kCLD + j];
-      const double sm = fmax(fabs(pv.x), fabs(pv.y));
-      const double ax = pv.x / sm, ay = pv.y / sm, den = (ax * ax + ay * ay) * sm;
-      const cplx rp = {ax / den, -ay / den};
-      if (tid < n) S.a[j * kCLD + tid] = cmul(S.a[j * kCLD + tid], rp);
-      __syncthreads();
-      for (int e = tid; e < j * n; e += kCThreads) {
-        const int r = e / n, c = e % n;
-        const cplx x = cmul(S.t[r * kCLD + j], S.a[j * kCLD + c]);
-        S.a[r * kCLD + c].x -= x.x;
-        S.a[r * kCLD + c].y -= x.y;
-      }
-      __syncthreads();
+    });
+    // det M: the diagonal of R, det Q and the sign of the permutation
+    cplx phm = det_q(S.tau, n);
+    double ldm = 0.0;
+    if (wv == 0) {
+      const double rb = lane < n ? S.x.beta[lane] : 1.0;
+      ldm = wave_sum(-log(fabs(rb)));
+      unsigned long long inv = __ballot(lane < n && rb < 0.0);
+      int odd = __popcll(inv) & 1;
+      const int pj = lane < n ? S.jpvt[lane] : lane;
+      for (int j = 0; j < n; ++j) odd ^= __popcll(__ballot(lane > j && pj < __builtin_amdgcn_readlane(pj, j))) & 1;
+      if (odd) phm = cplx{-phm.x, -phm.y};
     }
     // outputs
     int bad = 0;
     if (C.g) {
       cplx* G = reinterpret_cast<cplx*>(C.g);
-      for (int e = tid; e < n * n; e += kCThreads) {
-        const cplx x = S.a[(e / n) * kCLD + e % n];
-        G[e] = x;
+      each_row<NT>([&](int q, int t, int r) {
+        if (r >= n || lane >= n) return;
+        const cplx x = Y.a[q][t];
+        G[S.jpvt[r] * n + lane] = x;
         if (!isfinite(x.x) || !isfinite(x.y)) bad = 1;
-      }
+      });
     }
     if (tid == 0) {
       double ldp = 0.0;
       for (int i = 0; i < n; ++i) ldp += log(S.d[i] > 1.0 ? S.d[i] : 1.0);
       const double ld = ldp + ldm;
-      const double fr = phu.x * ppr - phu.y * ppi, fi = phu.x * ppi + phu.y * ppr;
+      const double fr = phu.x * phm.x - phu.y * phm.y, fi = phu.x * phm.y + phu.y * phm.x;
       if (C.logdet) *C.logdet = ld;
       if (C.phase) {
         C.phase[0] = fr;
@@ -623,17 +761,38 @@ __global__ __launch_bounds__(kCThreads) void k_greens_complex(const CChain* __re
 
 int complex_udt_max_n() { return kCN; }
 
-hipError_t launch_greens_complex(const CChain* tab, int count, int grid, hipStream_t s) {
-  if (count < 1 || grid < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_greens_complex, dim3(grid), dim3(kCThreads), 0, s, tab, count);
+// The variant of the smallest padded size; grid-stride over at most the
+// workgroups that `cus` compute units hold.
+template <class F>
+hipError_t by_tiles(int n, F go) {
+  if (n <= 16)
+    go(TileNo<1>{});
+  else if (n <= 32)
+    go(TileNo<2>{});
+  else if (n <= 48)
+    go(TileNo<3>{});
+  else
+    go(TileNo<4>{});
   return hipGetLastError();
 }
 
-hipError_t launch_udt_complex(int n, int count, const double* w, double* u, double* d, double* t, int grid,
+hipError_t launch_greens_complex(const CChain* tab, int count, int nmax, int cus, hipStream_t s) {
+  if (count < 1 || cus < 1 || nmax < 1 || nmax > kCN) return hipErrorInvalidValue;
+  return by_tiles(nmax, [&](auto tiles) {
+    constexpr int NT = decltype(tiles)::q;
+    const int grid = std::min(count, Dim<NT>::chain_groups * cus);
+    hipLaunchKernelGGL(k_greens_complex<NT>, dim3(grid), dim3(kCThreads), 0, s, tab, count);
+  });
+}
+
+hipError_t launch_udt_complex(int n, int count, const double* w, double* u, double* d, double* t, int cus,
                               hipStream_t s) {
-  if (n < 1 || n > kCN || count < 1 || grid < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_udt_complex, dim3(grid), dim3(kCThreads), 0, s, n, count, w, u, d, t);
-  return hipGetLastError();
+  if (n < 1 || n > kCN || count < 1 || cus < 1) return hipErrorInvalidValue;
+  return by_tiles(n, [&](auto tiles) {
+    constexpr int NT = decltype(tiles)::q;
+    const int grid = std::min(count, Dim<NT>::udt_groups * cus);
+    hipLaunchKernelGGL(k_udt_complex<NT>, dim3(grid), dim3(kCThreads), 0, s, n, count, w, u, d, t);
+  });
 }
 
 }  // namespace sdq

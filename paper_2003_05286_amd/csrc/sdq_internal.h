@@ -223,7 +223,7 @@ hipError_t launch_prod(int nt, const Inst* inst, const SweepItem* items, int cou
 // complex UDT of independent matrices (sdq_complex.hip): w, u, t interleaved
 // (re, im) [count][n][n], d [count][n]; 1 <= n <= complex_udt_max_n()
 int complex_udt_max_n();
-hipError_t launch_udt_complex(int n, int count, const double* w, double* u, double* d, double* t, int grid,
+hipError_t launch_udt_complex(int n, int count, const double* w, double* u, double* d, double* t, int cus,
                               hipStream_t s);
 hipError_t launch_udt(int nt, int n, int count, const double* w, double* u, double* d, double* t,
                       hipStream_t s);
@@ -238,8 +238,8 @@ struct CChain {
   int32_t n, m, k, pad;
 };
 // G, log|det(1+B)| and its phase for `count` chains, n <= complex_udt_max_n(),
-// one workgroup per chain (grid-stride)
-hipError_t launch_greens_complex(const CChain* tab, int count, int grid, hipStream_t s);
+// one workgroup per chain (grid-stride); nmax the largest n among them
+hipError_t launch_greens_complex(const CChain* tab, int count, int nmax, int cus, hipStream_t s);
 // M <- left M right for count n x n matrices (device pointer table), n <= 128
 hipError_t launch_similarity(int nt, int n, int count, double* const* mats, const double* left,
                              const double* right, int grid, hipStream_t s);

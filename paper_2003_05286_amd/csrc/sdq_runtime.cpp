@@ -1463,10 +1463,8 @@ sdq_status sdq_udt_complex(sdq_ctx* ctx, int32_t n, int32_t count, const double*
   if (!w || !u || !d || !t) return fail(ctx, SDQ_EINVAL, "null pointer");
   HIP_TRY(hipSetDevice(ctx->device), "hipSetDevice");
   ctx->err.clear();
-  // two workgroups per CU (73 KB of LDS each), grid-stride over the matrices
-  const int grid = std::max(1, std::min(count, 2 * ctx->num_cu));
   return timed(ctx, "udt_complex",
-               [&] { return sdq::launch_udt_complex(n, count, w, u, d, t, grid, ctx->stream); });
+               [&] { return sdq::launch_udt_complex(n, count, w, u, d, t, std::max(1, ctx->num_cu), ctx->stream); });
 }
 
 sdq_status sdq_greens_complex(sdq_ctx* ctx, const sdq_complex_instance* inst, int32_t count, double* const* g,
@@ -1501,10 +1499,10 @@ sdq_status sdq_greens_complex(sdq_ctx* ctx, const sdq_complex_instance* inst, in
                          ctx->stream),
           "hipMemcpyAsync(chain table)");
   if (status) HIP_TRY(sdq::launch_fill_i32(status, count, 0, ctx->stream), "fill(status)");
-  // one workgroup per CU (148 KB of LDS), grid-stride over the chains
-  const int grid = std::max(1, std::min(count, ctx->num_cu));
+  int nmax = 1;
+  for (int i = 0; i < count; ++i) nmax = std::max(nmax, inst[i].n);
   return timed(ctx, "greens_complex", [&] {
-    return sdq::launch_greens_complex((const sdq::CChain*)ctx->d_ctab.p, count, grid, ctx->stream);
+    return sdq::launch_greens_complex((const sdq::CChain*)ctx->d_ctab.p, count, nmax, std::max(1, ctx->num_cu), ctx->stream);
   });
 }
 
