@@ -4,7 +4,9 @@
 //
 // Execution model.  One workgroup owns one chain (or one stage pair) at a
 // time and pulls work items from a queue in longest-first order (persistent
-// launch).  A workgroup has P = min(NT, 4) waves, NT = ceil(n/16).  The
+// launch).  A workgroup has P waves, NT = ceil(n/16): P = NT, one wave per
+// 16-column tile, where the norm-sorted blocked QR factors (sdq_block.hpp),
+// P = min(NT, 4) in the pivoted sweeps, the SVD and the local updates.  The
 // working n x n matrix lives in registers, split by 16-column tiles over the
 // waves; inside a wave it is held exactly in the accumulator layout of the
 // FP64 MFMA 16x16x4 instruction:
@@ -16,10 +18,12 @@
 // 16*NT/4 rows per lane.  This lets
 //   * the slice products W <- E diag(v) W run back to back on MFMA with the
 //     previous product as the B operand (no LDS round trip, no barrier),
-//   * the pivoted Householder QR work on the same registers: column norms
-//     and reflector dot products are lane-local sums plus two cross-row
-//     shuffles; the pivot column is exchanged through LDS with one barrier
-//     per column step,
+//   * the blocked QR take its panels and apply their compact-WY reflectors
+//     (MFMA again) to the same registers, two barriers per 16 columns, and
+//     the pivoted Householder QR, where the factors themselves are the
+//     result, work on them too: column norms and reflector dot products are
+//     lane-local sums plus two cross-row shuffles; the pivot column is
+//     exchanged through LDS with one barrier per column step,
 //   * Q be formed and R P^T T be multiplied in place.
 // The factor R (with the reflectors below it) is parked in LDS, column-major
 // by original column index, for Q formation, the T update and the solves.
@@ -28,6 +32,7 @@
 //   slice products, stage loop ...... Sec. 4.1 (stabilized product, with the
 //                                     naive/stabilized mixture every k slices)
 //   cpqr / form_q / T update ........ Sec. 4.2.2 (UDT from pivoted QR)
+//   stabilize_sorted ................. the same UDT, columns sorted by norm
 //   inv_one_plus ..................... Sec. 5.1 (Loh's Dp/Dm split)
 //   pair_tdisp ....................... Sec. 6.1 (inv_sum_loh), Sec. 6 (G(tau,0)
 //                                     by propagation inside a block)
@@ -321,21 +326,6 @@ __device__ __forceinline__ void set_identity(const Lane& L, RM<NT, P>& A) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) A.v[c][ti][r] = (row_of(L, ti, r) == col_of<NT, P>(L, c)) ? 1.0 : 0.0;
 }
-
-// entry [tj][rj] of one lane's column slice; tj, rj are wave-uniform
-template <int NT>
-__device__ __forceinline__ double reg_at(const double (&a)[NT][4], int tj, int rj) {
-  double t[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    t[r] = a[0][r];
-#pragma unroll
-    for (int ti = 1; ti < NT; ++ti)
-      if (ti == tj) t[r] = a[ti][r];
-  }
-  return rj == 0 ? t[0] : rj == 1 ? t[1] : rj == 2 ? t[2] : t[3];
-}
-
 
 // ---------------------------------------------------------------------------
 // C = A * B on FP64 MFMA.  A(ti, tk, r, i, k) is any callable returning the
@@ -2072,24 +2062,6 @@ __device__ __forceinline__ void load_lds_rm(const Lane& L, const double* a, RM<N
   }
 }
 
-// B operand from the staged matrix: B[row][col] = S.E[row][col] or its transpose
-template <int NT, int P, bool ELDS>
-__device__ __forceinline__ void load_rm_staged(const Lane& L, const Smem<NT, P, ELDS>& S,
-                                               RM<NT, P>& B, bool trans) {
-  using G = Geo<NT, P>;
-#pragma unroll
-  for (int c = 0; c < G::CT; ++c) {
-    const int col = col_of<NT, P>(L, c);
-#pragma unroll
-    for (int ti = 0; ti < NT; ++ti)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = row_of(L, ti, r);
-        B.v[c][ti][r] = tile_ok<NT, P>(L, c) ? (trans ? S.E[col * G::LDR + row] : S.E[row * G::LDR + col]) : 0.0;
-      }
-  }
-}
-
 template <int NT, int P, bool ELDS, bool DENSE = false>
 __device__ __forceinline__ void tdisp_outputs(const Lane& L, Smem<NT, P, ELDS>& S, const Inst& I, const int j,
                               const int ilo, const int ihi, const int32_t* __restrict__ l_list,
@@ -2809,21 +2781,9 @@ struct Launch {
   static constexpr bool kLds = lds_variant(NT);
   static constexpr bool kPairLds = NT <= 5;  // operand staging buffer fits beside the factor store
   static constexpr bool kSvd = NT <= 5;  // A and T of the Jacobi SVD both fit in LDS
-  // the dense-slice sweep (variant 3) is instantiated in its own translation
-  // unit (sdq_nt_dense.hip), so that it leaves the code of these alone
-  static constexpr bool kDenseLds = NT <= 5;  // a dense slice staged beside the factor store
-  static hipError_t dense_sweep(const Inst* inst, const SweepItem* items, int count, Queue* q, int grid,
-                                hipStream_t s) {
-    hipLaunchKernelGGL((k_sweep<NT, P, kDenseLds, false, true>), dim3(grid), dim3(Geo<NT, P>::THREADS), 0, s,
-                       inst, items, count, q, (double*)nullptr);
-    return hipGetLastError();
-  }
-  static hipError_t dense_info(KernelInfo* out) {
-    return info_of(k_sweep<NT, P, kDenseLds, false, true>, (int)sizeof(Smem<NT, P, kDenseLds>), out);
-  }
-  // block products (k_prod) and the sweep over them (variant 6), one wave
-  // per tile, from kProdMinNT tiles up; also instantiated in sdq_nt_dense.hip
-  // only
+  // block products (k_prod) and the pivoted sweep over them (variant 6), one
+  // wave per tile, from kProdMinNT tiles up; instantiated in sdq_nt_dense.hip
+  // only, so that they leave the code of the others alone
   static constexpr bool kProd = NT >= kProdMinNT;
   static hipError_t prod(const Inst* inst, const SweepItem* items, int count, Queue* q, int grid, hipStream_t s) {
     if constexpr (kProd) {

@@ -11,10 +11,8 @@ namespace sdq {
   hipError_t launch_udt_nt##N(int, int, const double*, double*, double*, double*, hipStream_t);  \
   hipError_t launch_sim_nt##N(int, int, double* const*, const double*, const double*, int, hipStream_t); \
   hipError_t kernel_info_nt##N(int, int, KernelInfo*);                                            \
-  hipError_t launch_dense_sweep_nt##N(const Inst*, const SweepItem*, int, Queue*, int, hipStream_t); \
   hipError_t launch_bprod_sweep_nt##N(const Inst*, const SweepItem*, int, Queue*, int, double*, hipStream_t); \
   hipError_t bprod_sweep_info_nt##N(KernelInfo*);                                                \
-  hipError_t dense_info_nt##N(KernelInfo*);                                                      \
   hipError_t launch_prod_nt##N(const Inst*, const SweepItem*, int, Queue*, int, hipStream_t);    \
   hipError_t prod_info_nt##N(KernelInfo*);                                                       \
   hipError_t launch_fast_sweep_nt##N(int, const Inst*, const SweepItem*, int, Queue*, int, double*, hipStream_t); \
@@ -47,11 +45,6 @@ hipError_t launch_sweep(int nt, int variant, const Inst* inst, const SweepItem* 
   if (nt == kSweepMaxNT) return launch_sweep_nt9(variant, inst, items, count, q, grid, tscr, s);
   if (variant >= kFastPlain) {
 #define C(N) launch_fast_sweep_nt##N(variant, inst, items, count, q, grid, tscr, s)
-    SDQ_SWITCH(C)
-#undef C
-  }
-  if (variant == 3) {
-#define C(N) launch_dense_sweep_nt##N(inst, items, count, q, grid, s)
     SDQ_SWITCH(C)
 #undef C
   }
@@ -113,11 +106,6 @@ hipError_t kernel_info(int kind, int nt, int variant, KernelInfo* out) {
   }
   if (kind == KK_SWEEP && variant == 6) {
 #define C(N) bprod_sweep_info_nt##N(out)
-    SDQ_SWITCH(C)
-#undef C
-  }
-  if (kind == KK_SWEEP && variant == 3) {
-#define C(N) dense_info_nt##N(out)
     SDQ_SWITCH(C)
 #undef C
   }

@@ -181,15 +181,14 @@ hipError_t launch_hmc_end(int count, int nf, const HmcChain* chains, double half
 // b = (ti*NT + tk)*4 + r holds at position l the entry
 // (16 ti + l%16, 16 tk + l/16 + 4 r) of the zero-padded matrix.
 hipError_t launch_swizzle(const double* e, int n, int trans, double* out, hipStream_t s);
-// Sweep kernel variants (per tile count nt, chosen by sdq_tune or the
-// defaults of sdq_create):
+// Sweep kernel variants with column pivoting, for what returns the factors or
+// multiplies them out (the plain scheme, sdq_chain_udt), and the SVD:
 //   0  slice exponential read from its swizzled HBM copy, T in registers
 //   1  slice exponential staged in LDS (3 <= nt <= 5), T in registers
-//   2  Jacobi SVD stabilizer          3  dense slices
+//   2  Jacobi SVD stabilizer
 //   4  one wave per 16-column tile, T kept in a per-workgroup HBM scratch
 //      between blocks (frees a register matrix), exponential from HBM
 //   5  as 4 with the exponential staged in LDS (3 <= nt <= 5)
-constexpr int kSweepVariants = 6;
 // variant 6: the sweep over block products (k_prod) with one factorization
 // each, one wave per tile with T in the workgroup scratch like variant 4
 // The sweeps with the norm-sorted blocked QR (one wave per tile), which every

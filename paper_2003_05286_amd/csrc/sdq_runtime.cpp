@@ -483,11 +483,17 @@ sdq_status build_plan(sdq_ctx* ctx, Plan& P, int32_t* status, int count, Built& 
                                    o_q + (qi++) * sizeof(Queue), 0});
   }
   for (const auto& r : P.sweep_ranges) {
-    // (above kMaxNT tiles and up to kSweepMaxNT: the one-workgroup sweep with
-    // T and the factor store in workgroup scratch, variant 4; over block
-    // products, variant 6)
+    // (pivoted above kMaxNT tiles and up to kSweepMaxNT: the one-workgroup
+    // sweep with T and the factor store in workgroup scratch, variant 4; over
+    // block products, variant 6)
     const bool bprod = ((P.bprod_mask >> r.nt) & 1u) != 0;
-    const bool fast = !P.pivoted && ctx->stab == SDQ_STAB_QR && r.nt <= sdq::kSweepMaxNT;
+    // The norm-sorted blocked QR wherever the factors are not themselves the
+    // result: against the pivoted sweeps 12.3 -> 7.3 ms at n = 64 (512
+    // chains), 7.1 -> 4.4 at n = 121 (24), 29.7 -> 15.3 at n = 144 (among 512),
+    // 0.21 -> 0.10 for one chain of n = 16.
+    // (Dense slices have the QR only, whatever the context's stabilizer.)
+    const bool fast =
+        !P.pivoted && (P.dense || ctx->stab == SDQ_STAB_QR) && r.nt <= sdq::kSweepMaxNT;
     const int tuned = r.nt <= sdq::kMaxNT ? ctx->tune[r.nt].variant : 4;
     const int variant = sweep_is_gang(r.nt) ? (P.pivoted ? 1 : 0)
                         : fast ? (bprod               ? sdq::kFastProd
@@ -495,7 +501,6 @@ sdq_status build_plan(sdq_ctx* ctx, Plan& P, int32_t* status, int count, Built& 
                                                       : sdq::kFastPlain)
                         : bprod ? 6
                         : r.nt > sdq::kMaxNT ? 4
-                        : P.dense ? 3
                         : (ctx->stab == SDQ_STAB_SVD ? 2 : tuned);
     const int grid = grid_for(ctx, sdq::KK_SWEEP, r.nt, variant, r.count);
     // classes may run concurrently: each launch gets its own T scratch
@@ -1889,9 +1894,10 @@ sdq_status sdq_chain_udt(sdq_ctx* ctx, const sdq_instance* inst, int32_t count, 
 
 // Autotuner: for each n, time sdq_logdet on a synthetic batch (two chains
 // per CU, m = 40, k = 10, a periodic ring's second-order slice exponential,
-// +-1 field) for every sweep variant (operand in LDS or HBM) and grid shape
-// (one workgroup per CU or the occupancy limit), keep the fastest.  Results
-// are cached as JSON lines {"arch", "n", "variant", "blocks_per_cu", "ms"}.
+// +-1 field) for each grid shape (one workgroup per CU or the occupancy
+// limit), keep the faster.  The variant is that of the pivoted sweeps, which
+// sdq_logdet does not run: it stays as it is.  Results are cached as JSON
+// lines {"arch", "n", "variant", "blocks_per_cu", "ms"}.
 sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const char* cache_path) {
   SDQ_API_RANGE("sdq_tune");
   if (!ctx) return SDQ_EINVAL;
@@ -1971,14 +1977,9 @@ sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const ch
     std::vector<sdq_instance> inst(chains);
     for (int c = 0; c < chains; ++c)
       inst[c] = sdq_instance{n, m, k, 0, dE, nullptr, dF + (size_t)c * m * n, 0.65};
-    // the sweep variants (exponential in LDS or HBM; T in registers with
-    // min(nt, 4) waves, or in scratch with one wave per tile) and the
-    // occupancy cap (one workgroup per CU, or the kernel's limit)
+    // the occupancy cap (one workgroup per CU, or the kernel's limit)
     std::vector<Tune> cands;
-    const bool lds = nt >= 3 && nt <= 5;
-    for (int v : {0, 1, 4, 5})
-      if ((v != 1 && v != 5) || lds)
-        for (int b : {1, 0}) cands.push_back(Tune{v, b});
+    for (int b : {1, 0}) cands.push_back(Tune{ctx->tune[nt].variant, b});
     double best = 1e300;
     Tune bt = ctx->tune[nt];
     for (const Tune& c : cands) {
