@@ -1184,6 +1184,46 @@ __device__ __forceinline__ void stage_swizzled(const Lane& L, double* dst, const
   }
 }
 
+// W <- B W (one wave per tile column) for B in the swizzled operand layout in
+// device memory, staged through `buf` CH tile columns at a time: nine waves
+// that each read the whole operand through buffer loads wait for most of them
+// (288 k cycles a product at n = 144, where its matrix instructions take 62 k).
+// Starts with a barrier.
+template <int NT, int CH>
+__device__ __forceinline__ void gemm_staged(const Lane& L, double* buf, const double* b, RM<NT, NT>& W) {
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  d4 acc[NT];
+#pragma unroll
+  for (int ti = 0; ti < NT; ++ti) acc[ti] = d4{0.0, 0.0, 0.0, 0.0};
+  static_for<(NT + CH - 1) / CH>([&](auto pc) {
+    constexpr int K0 = decltype(pc)::value * CH, CW = NT - K0 < CH ? NT - K0 : CH, RUN = CW * 256;
+    const auto* src = (const __attribute__((address_space(1))) d2*)gmem(b);
+    d2 x[2 * CW];
+#pragma unroll
+    for (int q = 0; q < 2 * CW; ++q) {
+      const int i = 2 * (L.t + q * 64 * NT);  // of NT rows of tiles, RUN entries each
+      x[q] = src[((i / RUN) * NT * 256 + K0 * 256 + i % RUN) / 2];
+    }
+    __syncthreads();  // what was in buf is read
+#pragma unroll
+    for (int q = 0; q < 2 * CW; ++q) ((d2*)buf)[L.t + q * 64 * NT] = x[q];
+    __syncthreads();
+#pragma unroll
+    for (int tk = 0; tk < CW; ++tk)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int ti = 0; ti < NT; ++ti)
+          acc[ti] = __builtin_amdgcn_mfma_f64_16x16x4f64(buf[ti * RUN + (tk * 4 + r) * 64 + L.l],
+                                                         W.v[0][K0 + tk][r], acc[ti], 0, 0, 0);
+  });
+#pragma unroll
+  for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) W.v[0][ti][r] = acc[ti][r];
+  __syncthreads();  // buf is read
+}
+
 // A register matrix kept in a workgroup's private global scratch between
 // uses: register [c][ti][r] of lane l of wave w at ((c NT + ti) 4 + r) 64 P +
 // 64 w + l, so every access of a wave is one contiguous 512-byte block.  Each
@@ -1660,6 +1700,9 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
             gemm_rb<NT, P>(L, [&](int, int, int, int i, int kk) -> double { return S.E[kk * G::LDR + i]; }, W, W);
           else
             gemm_rb<NT, P>(L, [&](int, int, int, int i, int kk) -> double { return S.E[i * G::LDR + kk]; }, W, W);
+        } else if constexpr (PSW && FAST) {
+          gemm_staged<NT, Smem<NT, P, ELDS>::RG ? (NT + 1) / 2 : NT>(
+              L, S.R, I.field + (size_t)(q - 1) * G::NP * G::NP, W);
         } else if constexpr (PSW) {
           // the slice in the swizzled, zero-padded operand layout (forward only)
           const EOp<NT, P, false> bop{nullptr, I.field + (size_t)(q - 1) * G::NP * G::NP, L.l};
@@ -1719,21 +1762,31 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
               const int tcol = 16 * L.w + L.cl;
               const auto* q = tsrc == 2 ? gmem(tscr) + L.w * 64 + L.cl
                                         : gmem(I.ckf) + (size_t)(jpair - 1) * sd + (size_t)n * n + min(tcol, n - 1);
+              int src[NT][4];
 #pragma unroll
               for (int ti = 0; ti < NT; ++ti)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                  const int src = S.sperm[row_of(L, ti, r)];
-                  const double unit = src == tcol ? 1.0 : 0.0;
-                  if (tsrc == 2) {
-                    Tr.v[0][ti][r] = q[(size_t)((src >> 4) * 4 + ((src >> 2) & 3)) * 64 * P + (src & 3) * 16];
-                  } else if (tsrc == 1) {
-                    const double x = q[(size_t)min(src, n - 1) * n];
-                    Tr.v[0][ti][r] = (src < n && tcol < n) ? x : unit;
-                  } else {
-                    Tr.v[0][ti][r] = unit;
-                  }
-                }
+                for (int r = 0; r < 4; ++r) src[ti][r] = S.sperm[row_of(L, ti, r)];
+              auto fill = [&](auto entry) {
+#pragma unroll
+                for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                  for (int r = 0; r < 4; ++r) Tr.v[0][ti][r] = entry(src[ti][r]);
+              };
+              // (one loop for each source: loads inside a branch of their own
+              // are waited for one by one, 165 k cycles at n = 144)
+              if (tsrc == 2) {
+                fill([&](int i) { return q[(size_t)((i >> 4) * 4 + ((i >> 2) & 3)) * 64 * P + (i & 3) * 16]; });
+              } else if (tsrc == 1) {
+                fill([&](int i) { return q[(size_t)min(i, n - 1) * n]; });
+#pragma unroll
+                for (int ti = 0; ti < NT; ++ti)
+#pragma unroll
+                  for (int r = 0; r < 4; ++r)
+                    if (src[ti][r] >= n || tcol >= n) Tr.v[0][ti][r] = src[ti][r] == tcol ? 1.0 : 0.0;
+              } else {
+                fill([&](int i) { return i == tcol ? 1.0 : 0.0; });
+              }
               return Tr;
             },
             [&](RM<NT, P>& Tn) {
