@@ -243,34 +243,30 @@ __device__ __attribute__((noinline)) void gang_apply(const GC& c, int p, int ct_
                                rt_ = uniform_rsrc(g.tw, 256);
   double* xb = c.geo.w * ldr + 6 * 256 <= kGangSlab ? L.S + c.geo.w * ldr : L.xbuf;
   double* col = L.S + (16 * (ct_lo + min(cti, nct - 1)) + ln.cl) * ldr + 16 * p + ln.g;
-  double tv[4], a2[kApplyTiles][4];
+  double tv[4], a[kApplyTiles][4];
   d4 x = d4{0.0, 0.0, 0.0, 0.0};
-  {
-    double a1[kApplyTiles][4];
 #pragma unroll
-    for (int i = 0; i < kApplyTiles; ++i) {
-      const int rt = p + min(part + ks * i, cnt - 1);
+  for (int i = 0; i < kApplyTiles; ++i)
+    if (part + ks * i < cnt) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) a1[i][r] = ld_buf<COH>(r1, ln.g * 16 + ln.cl + rt * 256, r * 64);
+      for (int r = 0; r < 4; ++r) a[i][r] = ld_buf<COH>(r1, ln.g * 16 + ln.cl + (p + part + ks * i) * 256, r * 64);
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      tv[r] = ld_buf<COH>(rt_, QT ? (ln.g + 4 * r) * 16 + ln.cl : ln.cl * 16 + ln.g + 4 * r, 0);
-#pragma unroll
-    for (int i = 0; i < kApplyTiles; ++i) {
-      const int k = part + ks * i;
-      if (on && k < cnt) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          x = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[i][r], col[16 * k + 4 * r], x, 0, 0, 0);
-      }
-    }
-  }
+  for (int r = 0; r < 4; ++r)
+    tv[r] = ld_buf<COH>(rt_, QT ? (ln.g + 4 * r) * 16 + ln.cl : ln.cl * 16 + ln.g + 4 * r, 0);
+  // X = V^T C, a tile's operand of the second product loaded behind its first
+  // (a barrier waits for every load: issued after this loop they would all be
+  // waited for in the first round of sums)
 #pragma unroll
   for (int i = 0; i < kApplyTiles; ++i) {
-    const int rt = p + min(part + ks * i, cnt - 1);
+    const int k = part + ks * i;
+    if (k < cnt) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a2[i][r] = ld_buf<COH>(r2, ln.l + rt * 256, r * 64);
+      for (int r = 0; r < 4; ++r) {
+        if (on) x = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][r], col[16 * k + 4 * r], x, 0, 0, 0);
+        a[i][r] = ld_buf<COH>(r2, ln.l + (p + k) * 256, r * 64);
+      }
+    }
   }
   double* slot = xb + ((on ? cti : 0) * sl + part % sl) * 256 + ln.l;
   for (int rd = 0; rd < rounds; ++rd) {
@@ -300,7 +296,7 @@ __device__ __attribute__((noinline)) void gang_apply(const GC& c, int p, int ct_
       if (k < cnt) {
         d4 acc = d4{col[16 * k], col[16 * k + 4], col[16 * k + 8], col[16 * k + 12]};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a2[i][r], x2[r], acc, 0, 0, 0);
+        for (int r = 0; r < 4; ++r) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][r], x2[r], acc, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) col[16 * k + 4 * r] = acc[r];
       }
