@@ -14,6 +14,13 @@
 // barrier inside, and the other waves apply it as a compact WY block
 // reflector on MFMA.
 //
+// Bound by the panel's wave: it issues one instruction every 4.7 cycles
+// whatever they depend on, 350 / 490 / 660 cycles a step at 16 / 64 / 112
+// rows; two chains share a CU up to n = 64, so that one's panels run beside
+// the other's products (80 k cycles a block then, 50 k alone).  Sweeps with
+// pivoting in every step -> with this: one chain of n = 16 0.21 -> 0.10 ms,
+// 512 of n = 64 12.3 -> 7.3, 24 of n = 121 7.1 -> 4.4.
+//
 // LDS: panel q (columns 16q .. 16q+15) in S.R at q NP 16, one 16 x 16 tile
 // per row tile: R on and above the diagonal, the reflectors below it (their
 // diagonal in S.tau); S.tw: the 16 x 16 triangular factors Tw,

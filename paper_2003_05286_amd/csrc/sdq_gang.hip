@@ -10,7 +10,10 @@
 //     multiplies its own columns on FP64 MFMA with E read from the swizzled,
 //     zero-padded copy in HBM (it stays in L2: all members and chains of one
 //     size read the same copy);
-//   * the column-pivoted Householder QR (Sec. 4.2.2) is distributed by
+//   * the QR of a sweep after its first block and of the middle matrices goes
+//     by panels of 16 columns, one exchange each (sdq_gang_block.hpp);
+//   * the column-pivoted Householder QR (Sec. 4.2.2; first blocks, blocks whose
+//     sort fails its test, the plain schemes) is distributed by
 //     columns.  At every step each member publishes its live column of
 //     largest downdated norm (rows below the step) with a pivot key; after
 //     one gang barrier every wave of every member reads the winning column

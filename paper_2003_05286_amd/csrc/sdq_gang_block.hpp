@@ -11,6 +11,11 @@
 // factor through coherent stores and one flag, and every member applies them to
 // its own columns on MFMA.
 //
+// Bound by the chain of panels: 28 k cycles to factor and publish one at n =
+// 256 (16.7 k in its 16 steps, 9 k storing), 20 k for the next owner to apply
+// it.  Against a pivot per column: sweeps 237 -> 91 ms at n = 256 (64 chains)
+// and 458 -> 157 at n = 1024, pairs 159 -> 33 and 128 -> 14.
+//
 // Published per panel p, in the gang's scratch: the reflectors (su on the
 // diagonal, zero above) as row-major 16-column rows and once more in the
 // operand order of V X, Tw [16][16], su[16] and R's diagonal [16].
@@ -226,7 +231,10 @@ __device__ void wait_panel(GC& c, unsigned seq) {
 // from p on, reads its share of the reflectors at once, and keeps to these
 // tiles of the slab in both products, so that only the 16 x 16 products
 // X = V^T C meet: ks parts are summed in a fixed order over up to four LDS
-// slots per column tile, a barrier per round.  Ends with a barrier.
+// slots per column tile, a barrier per round.  Ends with a barrier.  Some 20 k
+// cycles at n = 256, 4 k of them in each product (four waves a SIMD); with the
+// second product's operands loaded before the sums, and tiles beyond the
+// panel's too, it took 25 k.
 template <bool QT, bool COH>
 __device__ __attribute__((noinline)) void gang_apply(const GC& c, int p, int ct_lo) {
   const Lane ln = gang_lane(c);
