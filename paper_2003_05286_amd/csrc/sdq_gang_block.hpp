@@ -327,9 +327,16 @@ __device__ void slab_pad_unit(const GC& c) {
 // scratch, diag R in L.beta, R (column-major, npad x npad, zero below the
 // diagonal) in sc_R, visible to the gang.  Returns whether |R_ic| cs_c <=
 // growth |R_ii| cs_i everywhere (cs: L.tau; test = false: always).
+// A panel is published into scratch that the factorization before it used too,
+// so every member has to be done with that one (bsolve_gang, bform_gang read
+// its panels and R) before the first panel here is written.  The sort that
+// precedes a tested factorization exchanges columns after that; without it the
+// members meet here: a gang takes the middle matrices of many items in a row,
+// and nothing else holds a member back that has finished its own columns first.
 __device__ bool bqr_gang(GC& c_io, bool test) {
   GC c = c_io;
   const int nrt = c.geo.npad / 16, np = c.geo.npad, n = c.n, ldr = c.geo.ldr;
+  if (!test) gang_sync(c);
   slab_pad_unit(c);
 #pragma unroll 1
   for (int p = 0; p < nrt; ++p) {
