@@ -76,11 +76,13 @@ __device__ __forceinline__ double wave_sum_(double v) {
 }
 __device__ __forceinline__ double wave_sum(double v) { return wave_sum_<0>(v); }
 
-// for values >= 0
 // LDS work space of the factorization and of applying its Q.
 struct QrScratch {
   cplx sc[kCN];         // the reflectors' factors
-  cplx row[2][kCN];     // a row of a solution
+  union {
+    cplx row[2][kCN];       // a row of a solution
+    double norms[4][kCN];   // per wave: sums of squares of the columns
+  };
   cplx red[2][5][kCN];  // per wave: partial column products; [4]: row i
   double beta[kCN];     // diag R
 };
@@ -147,10 +149,12 @@ __device__ __forceinline__ int own_row(int lane, int w) {
 __device__ __forceinline__ cplx row_of(cplx v, int q, int t) { return {lane_of(v.x, 4 * q + t), lane_of(v.y, 4 * q + t)}; }
 
 // Sums of the squares of the rows >= r0 of every column (lane = column),
-// 16 Q0 <= r0; the same in every wave.  One barrier inside; `buf` is a
-// QrScratch::red that no wave reads any more.
+// 16 Q0 <= r0; the same in every wave.  One barrier inside, none after the
+// reads: `buf` is an array of its own (QrScratch::norms), since the next step
+// writes either half of `red` before a barrier, and its own next use comes
+// after that step's barrier.
 template <int NT, int Q0>
-__device__ __forceinline__ double col_squares(cplx (*buf)[kCN], const RegMat<NT>& A, int r0) {
+__device__ __forceinline__ double col_squares(double (*buf)[kCN], const RegMat<NT>& A, int r0) {
   const int lane = threadIdx.x & 63, w = wave_id();
   const int w0 = per_lane(16 * Q0 + w - r0);  // row 16 Q0 + w + d counts if w0 + d >= 0
   double s = 0.0;
@@ -162,9 +166,9 @@ __device__ __forceinline__ double col_squares(cplx (*buf)[kCN], const RegMat<NT>
       const cplx x = d >= 16 ? A.a[q][t] : select(w0 + d >= 0, A.a[q][t], cplx{0.0, 0.0});
       s = fma(x.x, x.x, fma(x.y, x.y, s));
     }
-  buf[w][lane].x = s;
+  buf[w][lane] = s;
   __syncthreads();
-  return (buf[0][lane].x + buf[1][lane].x) + (buf[2][lane].x + buf[3][lane].x);
+  return (buf[0][lane] + buf[1][lane]) + (buf[2][lane] + buf[3][lane]);
 }
 
 // sqrt(c) and 1 / sqrt(c) (Goldschmidt from v_rsq_f64), 1 / c (Newton from
@@ -257,7 +261,7 @@ __device__ __forceinline__ void cpqr_lds(cplx* M, QrScratch& X, cplx* tau, int* 
   each_row<NT>([&](int q, int t, int r) { A.a[q][t] = cplx{ldexp(A.a[q][t].x, -e), ldexp(A.a[q][t].y, -e)}; });
   int pos = lane;  // place of this lane's column
   // squared norm at its last computation, its inverse, and what is left of it
-  double s0 = col_squares<NT, 0>(X.red[1], A, 0), c2 = 1.0;
+  double s0 = col_squares<NT, 0>(X.norms, A, 0), c2 = 1.0;
   double r0 = s0 > 1e-280 ? 1.0 / s0 : 0.0;
   steps_up<NT>(n, [&](auto tile, int i) {
     constexpr int iq = decltype(tile)::q;
@@ -351,7 +355,7 @@ __device__ __forceinline__ void cpqr_lds(cplx* M, QrScratch& X, cplx* tau, int* 
       again = !(c2 > tol3z);
     }
     if (__any(again)) {
-      const double sn = col_squares<NT, iq>(X.red[(i + 1) & 1], A, i + 1);
+      const double sn = col_squares<NT, iq>(X.norms, A, i + 1);
       if (again) {
         s0 = sn;
         r0 = sn > 1e-280 ? 1.0 / sn : 0.0;
