@@ -237,7 +237,8 @@ sdq_status sdq_udt(sdq_ctx* ctx, int32_t n, int32_t count, const double* w, doub
  * D_i = 0 is left undivided), for `count` complex n x n matrices stored back
  * to back in w.  w, u, t: [count][n][n] complex, each entry two doubles
  * (re, im), row-major, device; d: [count][n] real, device.  The caller owns
- * all buffers; the call is ordered on the context's stream.  1 <= n <= 64
+ * all buffers; the call is ordered on the context's stream.  Entries below
+ * 2^-1074 of the largest one of their column count as zero.  1 <= n <= 64
  * (SDQ_EUNSUPPORTED above); SDQ_EINVAL for a NULL buffer or count < 0. */
 sdq_status sdq_udt_complex(sdq_ctx* ctx, int32_t n, int32_t count, const double* w, double* u,
                            double* d, double* t);

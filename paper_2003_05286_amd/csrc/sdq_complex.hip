@@ -171,6 +171,33 @@ __device__ __forceinline__ double col_squares(double (*buf)[kCN], const RegMat<N
   return (buf[0][lane] + buf[1][lane]) + (buf[2][lane] + buf[3][lane]);
 }
 
+// Largest real or imaginary part in the rows >= r0 of every column, as
+// col_squares; with a barrier before it writes.
+template <int NT, int Q0>
+__device__ __forceinline__ double col_max(double (*buf)[kCN], const RegMat<NT>& A, int r0) {
+  const int lane = threadIdx.x & 63, w = wave_id();
+  const int w0 = per_lane(16 * Q0 + w - r0);
+  double m = 0.0;
+#pragma unroll
+  for (int q = Q0; q < NT; ++q)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int d = 16 * (q - Q0) + 4 * t;
+      if (d >= 16 || w0 + d >= 0) m = fmax(m, fmax(fabs(A.a[q][t].x), fabs(A.a[q][t].y)));
+    }
+  __syncthreads();
+  buf[w][lane] = m;
+  __syncthreads();
+  return fmax(fmax(buf[0][lane], buf[1][lane]), fmax(buf[2][lane], buf[3][lane]));
+}
+
+// What remains of a column is scaled up, the whole column with it, once its
+// squares sum to less than kSmallSquares (they would soon underflow, and the
+// reflector with them); by 2^kMaxShift in all at most, so that the finished
+// rows, at most 8 in size, do not overflow.
+constexpr double kSmallSquares = 1e-200;
+constexpr int kMaxShift = 1000;
+
 // sqrt(c) and 1 / sqrt(c) (Goldschmidt from v_rsq_f64), 1 / c (Newton from
 // v_rcp_f64) to the last place or two, for c in 1e-285 .. 1e285: what the
 // library adds for the other arguments is a third of a step's scalar chain.
@@ -249,15 +276,15 @@ __device__ __forceinline__ void cpqr_lds(cplx* M, QrScratch& X, cplx* tau, int* 
     A.a[q][t] = r < n && lane < n ? v : cplx{0.0, 0.0};
   });
   // every column to entries of at most 1 by a power of two, undone in R: a
-  // reflector does not depend on its column's scale, no square overflows, and
-  // a column whose squares vanish is zero to 1e-140 of what it was
+  // reflector does not depend on its column's scale and no square overflows
+  // (what remains of a column is scaled up again where its squares would vanish)
   double mx = 0.0;
   each_row<NT>([&](int q, int t, int r) { mx = fmax(mx, fmax(fabs(A.a[q][t].x), fabs(A.a[q][t].y))); });
   X.red[0][w][lane].x = mx;
   __syncthreads();
 #pragma unroll
   for (int v = 0; v < 4; ++v) mx = fmax(mx, X.red[0][v][lane].x);
-  const int e = __builtin_amdgcn_frexp_exp(mx);
+  int e = __builtin_amdgcn_frexp_exp(mx), shifted = 0;
   each_row<NT>([&](int q, int t, int r) { A.a[q][t] = cplx{ldexp(A.a[q][t].x, -e), ldexp(A.a[q][t].y, -e)}; });
   int pos = lane;  // place of this lane's column
   // squared norm at its last computation, its inverse, and what is left of it
@@ -355,7 +382,17 @@ __device__ __forceinline__ void cpqr_lds(cplx* M, QrScratch& X, cplx* tau, int* 
       again = !(c2 > tol3z);
     }
     if (__any(again)) {
-      const double sn = col_squares<NT, iq>(X.norms, A, i + 1);
+      double sn = col_squares<NT, iq>(X.norms, A, i + 1);
+      const bool small = again && sn < kSmallSquares && shifted < kMaxShift;
+      if (__any(small)) {
+        const double m = col_max<NT, iq>(X.norms, A, i + 1);
+        const int s = small && m > 0.0 ? min(-__builtin_amdgcn_frexp_exp(m), kMaxShift - shifted) : 0;
+        each_row<NT>([&](int q, int t, int r) { A.a[q][t] = cplx{ldexp(A.a[q][t].x, s), ldexp(A.a[q][t].y, s)}; });
+        e -= s;
+        shifted += s;
+        __syncthreads();  // the maxima are read
+        sn = col_squares<NT, iq>(X.norms, A, i + 1);
+      }
       if (again) {
         s0 = sn;
         r0 = sn > 1e-280 ? 1.0 / sn : 0.0;
