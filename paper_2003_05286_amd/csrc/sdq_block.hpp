@@ -253,8 +253,9 @@ __device__ __forceinline__ void sum_and_pick(double p, double x, bool in_g0, dou
 // the matrix are zero).  The reflector of column J is kept unscaled,
 // v_J = (su at row J; column J below it), H = I - c v v^T with
 // h = ||x||, su = alpha + sign(alpha) h, c = 1 / (h |su|), and always
-// reflects (a column with nothing below row J changes sign), so there is no
-// special case.  On return b holds R above the diagonal, the reflectors below
+// reflects (a column with nothing below row J changes sign), so that only a
+// column of zeros, or one whose squares leave the range of a double, is a
+// special case: plain_panel (the caller looks at beta) and panel_careful.  On return b holds R above the diagonal, the reflectors below
 // it and alpha on it; su_l, beta_l the reflector's and R's diagonal entry of
 // the lane's column; T row cl of the triangular factor.
 // Bound: one wave issues an instruction about every five cycles whatever its
@@ -316,6 +317,82 @@ __device__ __forceinline__ void panel_qr(const Lane& L, double (&b)[NT][4], doub
 #pragma unroll
   for (int r = 0; r < 4; ++r) al = L.g + 4 * r == L.cl ? b[0][r] : al;
   su_l = sum_col(al) + hs_l;
+}
+
+// Whether panel_qr's squares stayed inside the range: every ||x|| of the panel
+// (|beta_l|) between these powers of two, zero and NaN not among them.
+// (Entries below 2^-537 do not count beside 2^-300; a reflector's
+// products with columns of any other panel stay normal too.)
+__device__ __forceinline__ bool plain_panel(double beta_l) {
+  const double h = fabs(beta_l);
+  return __all(h >= 0x1p-300 && h <= 0x1p300);
+}
+
+// one wave's LDS accesses before it, by all lanes, before those after it
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The same panel, in LDS, for columns of any size, by one wave: before a
+// column becomes a reflector it is scaled to unit size by a power of two (the
+// reflector stays so; R's entry is scaled back), and a column of zeros reflects
+// its first entry: v = e_J, c = 2, so that every column's reflector reflects.
+// Entry (i, c), 0 <= i < rows, at x: in panel layout, or (ld > 0) at c ld + i;
+// R with its diagonal on return.  tw: the triangular factor, a tile or (ld > 0) row-major;
+// su_l: the diagonal of the lane's reflector.
+// Reached by middle matrices that are singular or far from one in size (and by
+// NaN); a row at a time, as slow as that is.
+struct CarefulDiag {
+  double su_l, beta_l;
+};
+template <bool TILES>
+__device__ __forceinline__ CarefulDiag panel_careful(double* x, double* tw, int rows, int ld) {
+  const Lane L = lane_id_per_item();
+  auto at = [&](int i, int c) -> double& {
+    return TILES ? x[kTile * (i >> 4) + tile_idx(i & 15, c)] : x[c * ld + i];
+  };
+  auto tri = [&](int i, int c) -> double& { return tw[TILES ? tile_idx(i, c) : 16 * i + c]; };
+  CarefulDiag out = {0.0, 0.0};
+  wave_fence();
+#pragma unroll 1
+  for (int J = 0; J < 16; ++J) {
+    double mx = 0.0;
+#pragma unroll 1
+    for (int i = J + L.l; i < rows; i += 64) mx = fmax(mx, fabs(at(i, J)));
+#pragma unroll 1
+    for (int m = 32; m >= 1; m >>= 1) mx = fmax(mx, __shfl_xor(mx, m));
+    const int e = mx > 0.0 && isfinite(mx) ? ilogb(mx) : 0;
+#pragma unroll 1
+    for (int i = J + L.l; i < rows; i += 64) at(i, J) = ldexp(at(i, J), -e);
+    wave_fence();
+    double p = 0.0;
+#pragma unroll 1
+    for (int i = L.g; i < rows; i += 4)
+      if (i > J) p = fma(at(i, J), at(i, L.cl), p);
+    const double dot = sum_col(p), ajc = at(J, L.cl);
+    const double s = __shfl(dot, J), alpha = __shfl(ajc, J);
+    const double hs = copysign(sqrt(fma(alpha, alpha, s)), alpha);
+    const double su = hs == 0.0 ? 1.0 : alpha + hs;
+    const double c = hs == 0.0 ? 2.0 : 2.0 / fma(su, su, s);
+    const double d = fma(su, ajc, dot), f = -c * d;
+    wave_fence();  // row J is read
+    if (L.cl > J) {
+#pragma unroll 1
+      for (int i = L.g; i < rows; i += 4)
+        if (i > J) at(i, L.cl) = fma(at(i, J), f, at(i, L.cl));
+      if (L.g == 0) at(J, L.cl) = fma(su, f, ajc);
+    }
+    if (L.cl == J) out = CarefulDiag{su, -ldexp(hs, e)};
+    double ts = 0.0;
+#pragma unroll 1
+    for (int i = 0; i < J; ++i) ts = fma(__shfl(d, i), tri(L.cl, i), ts);
+    if (L.g == 0) tri(L.cl, J) = L.cl == J ? c : (L.cl < J ? -c * ts : 0.0);
+    wave_fence();
+  }
+  if (L.g == 0) at(L.cl, L.cl) = out.beta_l;
+  wave_fence();
+  return out;
 }
 
 // C <- Q_p^T C (QT) or Q_p C for one column tile, rows in b[0 .. cnt) from
@@ -416,15 +493,19 @@ __device__ __forceinline__ void panel_factor(SM& S, double (&b)[NT][4], const in
   double T[16], su_l, beta_l;
   const int cnt = NT - p;
   double* vp = S.R + panel_off<NT, SM>(p);
-  // R above the panel goes out first; its registers are zero rows from here on
+  // R above the panel goes out first; its registers are zero rows from here on.
+  // The panel's rows go to their place as they are, for panel_careful.
 #pragma unroll
-  for (int t = 1; t < NT; ++t)
+  for (int t = 0; t < NT; ++t)
     if (t >= cnt) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         upper_st<NT>(S, p, t - cnt, tile_idx(L.g + 4 * r, L.cl), b[t][r]);
         b[t][r] = 0.0;
       }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) vp[kTile * t + tile_idx(L.g + 4 * r, L.cl)] = b[t][r];
     }
   if constexpr (NT >= 4) {
     // the lower half of the panels have at most half the rows
@@ -433,21 +514,28 @@ __device__ __forceinline__ void panel_factor(SM& S, double (&b)[NT][4], const in
   } else {
     panel_qr<NT, NT>(L, b, T, su_l, beta_l);
   }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) b[0][r] = L.g + 4 * r == L.cl ? beta_l : b[0][r];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-    if (t < cnt) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) vp[kTile * t + tile_idx(L.g + 4 * r, L.cl)] = b[t][r];
-    }
   double* tw = S.tw + p * kTile;
+  if (plain_panel(beta_l)) {
+    const Lane L = lane_id_per_item();
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (L.g == q) {
+    for (int r = 0; r < 4; ++r) b[0][r] = L.g + 4 * r == L.cl ? beta_l : b[0][r];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) tw[tile_idx(L.cl, 4 * q + c)] = T[4 * q + c];
-    }
+    for (int t = 0; t < NT; ++t)
+      if (t < cnt) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) vp[kTile * t + tile_idx(L.g + 4 * r, L.cl)] = b[t][r];
+      }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (L.g == q) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) tw[tile_idx(L.cl, 4 * q + c)] = T[4 * q + c];
+      }
+  } else {
+    const CarefulDiag cd = panel_careful<true>(vp, tw, 16 * cnt, 0);
+    su_l = cd.su_l;
+    beta_l = cd.beta_l;
+  }
   if (L.g == 0) {
     S.tau[16 * p + L.cl] = su_l;
     S.red_diag[16 * p + L.cl] = beta_l;

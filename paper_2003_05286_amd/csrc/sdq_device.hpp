@@ -58,9 +58,12 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // sweep and the equal-time inversion at n <= 64 (they fit 256 registers per
 // lane with little or no spilling), one otherwise
 constexpr int minb_for(int nt) { return nt <= 4 ? 2 : 1; }
+// (one tile, one wave: three waves a SIMD for the blocked-QR sweep, four for
+// dense slices and for the pairs that solve through it)
+constexpr int minb_fast1(bool dense) { return dense ? 4 : 3; }
 // (the site loop of the local updates keeps both flavours' G and E^-1 in
 // registers: one)
-constexpr int minb_pair(int nt, int mode) { return mode == 4 ? 1 : minb_for(nt); }
+constexpr int minb_pair(int nt, int mode) { return mode == 4 ? 1 : (nt == 1 && mode <= 2 ? 4 : minb_for(nt)); }
 
 template <int NT, int P_>
 struct Geo {
@@ -1521,10 +1524,11 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
     scale = S.dcur[col];
     sort_t();
     block_qr<NT, 0>(L, S, W, nullptr);
-    // growth test: |R_ic| <= gamma |R_ii| in the original scales
+    // growth test: |R_ic| <= gamma |R_ii| in the original scales (NaN fails it)
     L = lane_id_per_item();
     for (int t = L.t; t < G::NP; t += G::THREADS) S.dnew[t] = fabs(S.red_diag[t]) * S.dcur[t];
     double lift = 0.0;
+    bool grown = false;
     const double* dg = S.R + panel_off<NT, Smem<NT, NT, ELDS>>(L.w);
 #pragma unroll
     for (int t = 0; t < NT; ++t)
@@ -1536,11 +1540,14 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
           const double x = t == L.w ? dg[at] : upper_ld<NT>(S, L.w, t, at);
           const double lim = kSortedGrowth * fabs(S.red_diag[row]) * S.dcur[row];
           const double y = fabs(x) * scale;
-          if (row < col && y > lim) lift = fmax(lift, y);
+          if (row < col && !(y <= lim)) {
+            grown = true;
+            lift = fmax(lift, y);
+          }
         }
       }
     lift = max_col(lift);
-    const bool any = __any(lift > 0.0 && live);
+    const bool any = __any(grown && live);
     if (L.l == 0) S.ired[L.w] = any ? 1 : 0;
     __syncthreads();
     int failed = 0;
@@ -1930,7 +1937,7 @@ __device__ __forceinline__ void sweep_items(const Inst* __restrict__ insts, cons
 
 template <int NT, int P, bool ELDS, bool SVD = false, bool DENSE = false, bool TG = false, bool PSW = false,
           bool FAST = false>
-__global__ __launch_bounds__(64 * P, minb_for(NT)) void k_sweep(const Inst* __restrict__ insts,
+__global__ __launch_bounds__(64 * P, FAST && NT == 1 ? minb_fast1(DENSE) : minb_for(NT)) void k_sweep(const Inst* __restrict__ insts,
                                                             const SweepItem* __restrict__ items,
                                                             int count, Queue* q, double* tscr) {
   sweep_items<NT, P, ELDS, SVD, DENSE, TG, PSW, FAST>(insts, items, count, q, tscr);

@@ -125,6 +125,34 @@ __device__ __forceinline__ void gang_panel_steps(const Lane& ln, double (&b)[RT]
   });
 }
 
+// The panel whose steps left the range of a double's squares, from the slab,
+// which still holds its columns (panel_careful; wave 0 alone).  The triangular
+// factor in the half of L.pred that the last step does not use: another wave
+// may still be reading its own half and writing L.gram.
+__device__ __attribute__((noinline)) void gang_panel_careful(const GC& c, int p) {
+  const Lane ln = gang_lane(c);
+  const int rows = c.geo.npad - 16 * p, ldr = c.geo.ldr;
+  double* col = L.S + (16 * p - c.c0) * ldr + 16 * p;
+  const CarefulDiag cd = panel_careful<false>(col, L.pred, rows, ldr);
+  const double su = cd.su_l, beta = cd.beta_l;
+  const GPanel g = panel_at(c, p);
+  if (ln.g == 0) {
+    st_coh(g.meta + ln.cl, su);
+    st_coh(g.meta + 16 + ln.cl, beta);
+  }
+#pragma unroll 1
+  for (int i = ln.g; i < rows; i += 4) {
+    const double x = col[ln.cl * ldr + i], v = i > ln.cl ? x : (i == ln.cl ? su : 0.0);
+    const int rt = p + (i >> 4), row = i & 15;
+    st_coh(g.v1 + rt * 256 + row * 16 + ln.cl, v);
+    st_coh(g.v2 + rt * 256 + (ln.cl >> 2) * 64 + (ln.cl & 3) * 16 + row, v);
+    if (i < 16) {
+      st_coh(g.tw + ln.cl * 16 + i, L.pred[ln.cl * 16 + i]);
+      if (i > ln.cl) col[ln.cl * ldr + i] = 0.0;
+    }
+  }
+}
+
 // Factor panel p (in this member's slab) and write it to the gang's scratch;
 // the slab keeps R's diagonal tile.  Every wave of the workgroup calls it.
 // Not inlined: the inline assembly's operands must not be spilled, and the
@@ -152,6 +180,11 @@ __device__ __attribute__((noinline)) void gang_panel(const GC& c, int p) {
     }
   }
   gang_panel_steps<RT, NW4>(ln, b, hs_l);
+  if (!plain_panel(hs_l)) {  // the same numbers in every wave
+    if (ln.w == 0) gang_panel_careful(c, p);
+    __builtin_amdgcn_s_waitcnt(0);
+    return;
+  }
   const GPanel g = panel_at(c, p);
   if (ln.w == 0) {
     double al = 0.0;
@@ -326,7 +359,7 @@ __device__ void slab_pad_unit(const GC& c) {
 // The slab's matrix = Q R, columns as they stand: panels in the gang's
 // scratch, diag R in L.beta, R (column-major, npad x npad, zero below the
 // diagonal) in sc_R, visible to the gang.  Returns whether |R_ic| cs_c <=
-// growth |R_ii| cs_i everywhere (cs: L.tau; test = false: always).
+// growth |R_ii| cs_i everywhere (cs: L.tau; NaN fails; test = false: always).
 // A panel is published into scratch that the factorization before it used too,
 // so every member has to be done with that one (bsolve_gang, bform_gang read
 // its panels and R) before the first panel here is written.  The sort that
@@ -368,7 +401,7 @@ __device__ bool bqr_gang(GC& c_io, bool test) {
       const int cc = idx / np, i = idx - cc * np, gc = c.c0 + cc;
       if (gc >= np) continue;
       const double x = i <= gc ? L.S[cc * ldr + i] : 0.0;
-      if (test && i < gc && gc < n && fabs(x) * L.tau[gc] > kSortedGrowth * fabs(L.beta[i]) * L.tau[i]) bad = 1;
+      if (test && i < gc && gc < n && !(fabs(x) * L.tau[gc] <= kSortedGrowth * fabs(L.beta[i]) * L.tau[i])) bad = 1;
       gmem(R)[(int64_t)gc * np + i] = x;
     }
   }
