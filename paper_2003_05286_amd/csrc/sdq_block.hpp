@@ -30,6 +30,7 @@
 #pragma once
 
 constexpr int kTile = 256;
+constexpr int kStepPanels = 2;  // panels of a graded block applied by panel_steps
 __device__ __forceinline__ int tile_idx(int i, int c) { return 16 * i + (c ^ i); }
 
 // Above kMaxNT tiles (SM::RG) LDS holds the panels from their diagonal tile
@@ -188,6 +189,32 @@ __device__ __forceinline__ void axpy_tiles(double (&t0)[4], double (&t1)[4], dou
   asm("s_nop 1\n" SDQ_AX4(a) SDQ_AX4(b) : SDQ_IO4(a, t0), SDQ_IO4(b, t1) : [f] "v"(f), [J] "n"(J));
 }
 
+// p += sum of a[J] x over a tile and x += a[J] f for another matrix's rows x
+template <int J>
+__device__ __forceinline__ void dot_with(double& p, const double (&a)[4], const double (&x)[4]) {
+  asm("s_nop 1\n" SDQ_FD("%[p]", "%[a0]", "%[x0]", "%[J]", "0xf") SDQ_FD("%[p]", "%[a1]", "%[x1]", "%[J]", "0xf")
+          SDQ_FD("%[p]", "%[a2]", "%[x2]", "%[J]", "0xf") SDQ_FD("%[p]", "%[a3]", "%[x3]", "%[J]", "0xf") "s_nop 1"
+      : [p] "+v"(p)
+      : [J] "n"(J), SDQ_IN4(a, a), SDQ_IN4(x, x));
+}
+template <int J>
+__device__ __forceinline__ void axpy_with(double (&x)[4], const double (&a)[4], double f) {
+  asm("s_nop 1\n" SDQ_FD("%[x0]", "%[a0]", "%[f]", "%[J]", "0xf") SDQ_FD("%[x1]", "%[a1]", "%[f]", "%[J]", "0xf")
+          SDQ_FD("%[x2]", "%[a2]", "%[f]", "%[J]", "0xf") SDQ_FD("%[x3]", "%[a3]", "%[f]", "%[J]", "0xf") "s_nop 1"
+      : SDQ_IO4(x, x)
+      : [J] "n"(J), SDQ_IN4(a, a), [f] "v"(f));
+}
+// rows that matrix instructions may have written just before: let them land
+// before inline assembly reads them (18 wait states)
+template <int RT, int NT>
+__device__ __forceinline__ void rows_landed(double (&b)[NT][4]) {
+#pragma unroll
+  for (int t = 0; t < RT; ++t) asm volatile("" : SDQ_IO4(a, b[t]));
+  asm volatile("s_nop 15\ns_nop 7");
+#pragma unroll
+  for (int t = 0; t < RT; ++t) asm volatile("" : SDQ_IO4(a, b[t]));
+}
+
 // sum_{c < J} d[c] T[c]: d from lane c of the row, T[c] the lane's own
 #define SDQ_TD(C) SDQ_FD("%[p]", "%[d]", "%[t" #C "]", #C, "0xf")
 #define SDQ_TD1 SDQ_TD(0)
@@ -252,7 +279,8 @@ __device__ __forceinline__ void sum_and_pick(double p, double x, bool in_g0, dou
 // b[0 .. RT) (row 0 of b[0] is the panel's first diagonal row; tiles past
 // the matrix are zero).  The reflector of column J is kept unscaled,
 // v_J = (su at row J; column J below it), H = I - c v v^T with
-// h = ||x||, su = alpha + sign(alpha) h, c = 1 / (h |su|), and always
+// h = ||x||, su = alpha + sign(alpha) h, c = 2 / v^T v (of the rounded v: from
+// h it would leave H further from orthogonal), and always
 // reflects (a column with nothing below row J changes sign), so that only a
 // column of zeros, or one whose squares leave the range of a double, is a
 // special case: plain_panel (the caller looks at beta) and panel_careful.  On return b holds R above the diagonal, the reflectors below
@@ -266,13 +294,7 @@ __device__ __forceinline__ void sum_and_pick(double p, double x, bool in_g0, dou
 template <int RT, int NT>
 __device__ __forceinline__ void panel_qr(const Lane& L, double (&b)[NT][4], double (&T)[16], double& su_l,
                                          double& beta_l) {
-  // the rows may come straight from matrix instructions: let them land before
-  // the inline assembly reads them (18 wait states, after whatever wrote b)
-#pragma unroll
-  for (int t = 0; t < RT; ++t) asm volatile("" : SDQ_IO4(a, b[t]));
-  asm volatile("s_nop 15\ns_nop 7");
-#pragma unroll
-  for (int t = 0; t < RT; ++t) asm volatile("" : SDQ_IO4(a, b[t]));
+  rows_landed<RT>(b);
   double hs_l = 0.0;
   static_for<16>([&](auto jc) {
     constexpr int J = decltype(jc)::value, R0 = J >> 2, G0 = J & 3;
@@ -294,7 +316,7 @@ __device__ __forceinline__ void panel_qr(const Lane& L, double (&b)[NT][4], doub
     h = fma(fma(-h, h, q), hr, h);
     const double hs = copysign(h, alpha);
     const double su = alpha + hs;
-    const double c = rcp_mid(fma(fabs(alpha), h, q));
+    const double c = rcp_mid(0.5 * fma(su, su, s));
     const double d = fma(su, ajc, dot);  // v_J^T a_c
     const double cd = -c * d;
     // columns up to J stay as they are (the low word alone is a denormal)
@@ -462,6 +484,40 @@ __device__ __forceinline__ void panel_apply(double (&b)[NT][4], const int cnt, c
   }
 }
 
+// C <- Q_p^T C as panel_apply, one reflector at a time on the vector units: a
+// column that is nearly in the span of the reflectors before shrinks on the
+// way, and with it what a reflector adds to its error, while the block
+// reflector's coefficients all carry the error of the column as it came.  The
+// columns of a product of slices shrink most in the first panels
+// (kStepPanels; with none the errors are 1.2 to 1.5 times those of pivoting,
+// more than two change nothing).  A step takes some 45 instructions at 64 rows;
+// 512 chains of n = 64 take 1 % longer with it.
+template <int NT>
+__device__ __forceinline__ void panel_steps(double (&b)[NT][4], const int cnt, const double* vp, const double* tw,
+                                            const double* su) {
+  const Lane L = lane_id_per_item();
+  const double vd = su[L.cl], cd = tw[tile_idx(L.cl, L.cl)];
+  double a[NT][4];  // row g + 4 r of a tile, reflector cl
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = L.g + 4 * r;
+      const double v = vp[kTile * min(t, cnt - 1) + tile_idx(row, L.cl)];
+      a[t][r] = t >= cnt ? 0.0 : (t > 0 || row > L.cl ? v : (row == L.cl ? vd : 0.0));
+    }
+  rows_landed<NT>(b);
+  static_for<16>([&](auto jc) {
+    constexpr int J = decltype(jc)::value;
+    double p = 0.0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) dot_with<J>(p, a[t], b[t]);
+    const double f = -bcast_col<J>(cd) * sum_col(p);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) axpy_with<J>(b[t], a[t], f);
+  });
+}
+
 // row tiles one up (the first becomes the last) / one down
 template <int NT>
 __device__ __forceinline__ void rotate_up(double (&b)[NT][4]) {
@@ -555,9 +611,10 @@ __device__ __forceinline__ void pad_unit(const Lane& L, const int n, double (&b)
 // W = Q R for the register matrix W as its columns stand (padding columns:
 // unit vectors), Q and R left in LDS in panels; diag R in S.red_diag.  With
 // YN > 0 the same Q^T is applied to the register matrix Y, whose rows are in
-// place again afterwards.  Starts with a barrier after which S.R is free to
-// write; ends with one.
-template <int NT, int YN, class SM>
+// place again afterwards.  The first STEPS panels are applied by panel_steps:
+// kStepPanels of a graded block, all of them where the solution is the result.
+// Starts with a barrier after which S.R is free to write; ends with one.
+template <int NT, int YN, int STEPS, class SM>
 __device__ __forceinline__ void block_qr(const Lane& L, SM& S, double (&b)[NT][4], double (*Y)[4]) {
   __syncthreads();
 #pragma unroll 1
@@ -567,45 +624,34 @@ __device__ __forceinline__ void block_qr(const Lane& L, SM& S, double (&b)[NT][4
     const double* vp = S.R + panel_off<NT, SM>(p);
     const double* tw = S.tw + p * kTile;
     if (L.w > p) {
-      panel_apply<NT, true>(b, NT - p, vp, tw, S.tau + 16 * p);
+      if (p < STEPS) panel_steps<NT>(b, NT - p, vp, tw, S.tau + 16 * p);
+      else panel_apply<NT, true>(b, NT - p, vp, tw, S.tau + 16 * p);
       rotate_up<NT>(b);
     }
     if constexpr (YN > 0) {
       double(&y)[NT][4] = *reinterpret_cast<double(*)[NT][4]>(Y);
-      panel_apply<NT, true>(y, NT - p, vp, tw, S.tau + 16 * p);
+      if (p < STEPS) panel_steps<NT>(y, NT - p, vp, tw, S.tau + 16 * p);
+      else panel_apply<NT, true>(y, NT - p, vp, tw, S.tau + 16 * p);
       rotate_up<NT>(y);
     }
   }
 }
 
-// This wave's column tile of Q (FROM_R false) or of Q R (true) from the
-// panels: Q_0 ... Q_w applied to the tile of the identity, or of R.
-template <int NT, bool FROM_R, class SM>
+// This wave's column tile of Q from the panels: Q_0 ... Q_w applied to the
+// tile of the identity.
+template <int NT, class SM>
 __device__ __forceinline__ void block_form(const Lane& L, const SM& S, double (&b)[NT][4]) {
   const int w = L.w;
-  const double* dg = S.R + panel_off<NT, SM>(w);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) b[t][r] = 0.0;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = L.g + 4 * r;
-    if (FROM_R) b[0][r] = row <= L.cl ? dg[tile_idx(row, L.cl)] : 0.0;
-    else b[0][r] = row == L.cl ? 1.0 : 0.0;
-  }
+    for (int r = 0; r < 4; ++r) b[t][r] = t == 0 && L.g + 4 * r == L.cl ? 1.0 : 0.0;
 #pragma unroll 1
   for (int p = w; p >= 0; --p) {
     const Lane L = lane_id_per_item();
     panel_apply<NT, false>(b, NT - p, S.R + panel_off<NT, SM>(p), S.tw + p * kTile,
                            S.tau + 16 * p);
-    if (p > 0) {
-      rotate_down<NT>(b);
-      if (FROM_R) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) b[0][r] = upper_ld<NT>(S, w, p - 1, tile_idx(L.g + 4 * r, L.cl));
-      }
-    }
+    if (p > 0) rotate_down<NT>(b);
   }
 }
 

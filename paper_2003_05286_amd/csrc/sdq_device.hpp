@@ -1016,7 +1016,7 @@ __device__ __forceinline__ void inv_one_plus(const Lane& L, const int n, Smem<NT
   if constexpr (loh) {
     for (int t = L.t; t < n; t += G::THREADS) lsum += log(fmax(S.dcur[t], 1.0));
     pad_unit<NT>(L, n, M.v[0]);
-    block_qr<NT, 1>(L, S, M.v[0], Z.v[0]);  // begins with a barrier
+    block_qr<NT, 1, NT>(L, S, M.v[0], Z.v[0]);  // begins with a barrier
     for (int t = L.t; t < n; t += G::THREADS) {
       const double d = S.red_diag[t];
       lsum += log(fabs(d));
@@ -1437,13 +1437,19 @@ constexpr int kFirstPivotedNT = 3;
 // the columns in the order of the last one's diagonal, a column that exceeds a
 // row's diagonal by more raised to its entry there (it should have come before
 // that row), then the pivoted QR.
-// Measured against 113-bit arithmetic (n = 16 .. 64, ordered and random
-// fields, chains with |G| up to 400): without the test G(tau, 0) is up to
-// 70 times further off than with pivoting (a chain's first blocks, whose
-// columns are not graded yet), with it the errors scatter around the pivoted
-// QR's by a factor of two either way; one to four of a chain's blocks need a
-// second pass, and none of those chains another pivoted block (n up to 576).
-constexpr double kSortedGrowth = 4.0;
+// Each attempt starts from the block's own columns, kept in the workgroup's
+// device scratch: multiplied out of Q and R again they would carry the errors
+// of a second factorization.
+// Errors of G and G(tau, 0) against extended precision (64-bit mantissas;
+// n = 9 .. 144, k = 5 .. 10, 8 to 64 chains a size), as geometric means over
+// what the column-pivoted kernels reach: 0.96 (k = 10) and 1.06 (k = 5) with
+// this bound, 0.98 and 1.09 with 4, up to 70 without a test (a chain's first
+// blocks, whose columns are not graded yet); 1.36 and 1.59 with 4 before the
+// columns were kept and the first panels applied a reflector at a time.  A
+// block takes 1.05 to 1.2 factorizations with 4, 1.15 to 1.6 with 2 (512
+// chains of n = 64 2 % longer, 96 of n = 49 7 %).  No block of a physical chain
+// needed the pivoted QR (n up to 576).
+constexpr double kSortedGrowth = 2.0;
 constexpr int kSortPasses = 6;
 
 // Stabilization of one block by the norm-sorted blocked QR: on entry W is the
@@ -1456,8 +1462,8 @@ constexpr int kSortPasses = 6;
 // S.sperm); keep_t takes the new T.
 template <int NT, bool ELDS, class SortT, class LoadT, class KeepT>
 __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>& S, RM<NT, NT>& Wm,
-                                                 double dcol, const bool first, double* sgn, SortT sort_t,
-                                                 LoadT load_t, KeepT keep_t) {
+                                                 double dcol, const bool first, double* sgn, double* wscr,
+                                                 SortT sort_t, LoadT load_t, KeepT keep_t) {
   using G = Geo<NT, NT>;
   double(&W)[NT][4] = Wm.v[0];
   double key, scale;
@@ -1522,8 +1528,9 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
 #pragma unroll
       for (int r = 0; r < 4; ++r) W[t][r] = r_ld(S, col * G::LDR + row_of(L, t, r));
     scale = S.dcur[col];
+    scr_store<NT, NT>(L, Wm, wscr);
     sort_t();
-    block_qr<NT, 0>(L, S, W, nullptr);
+    block_qr<NT, 0, kStepPanels>(L, S, W, nullptr);
     // growth test: |R_ic| <= gamma |R_ii| in the original scales (NaN fails it)
     L = lane_id_per_item();
     for (int t = L.t; t < G::NP; t += G::THREADS) S.dnew[t] = fabs(S.red_diag[t]) * S.dcur[t];
@@ -1555,7 +1562,7 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
     for (int q = 0; q < NT; ++q) failed |= S.ired[q];
     sorted = !__builtin_amdgcn_readfirstlane(failed);
     if (sorted) break;
-    block_form<NT, true>(L, S, W);  // Q R, the scaled columns themselves
+    scr_load<NT, NT>(L, Wm, wscr);  // the scaled columns themselves, as sorted
     if (pass == kSortPasses - 1) break;
     key = fmax(S.dnew[col], lift);
   }
@@ -1585,7 +1592,7 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
       for (int r = 0; r < 4; ++r) T.v[0][ti][r] = acc[r] / S.dnew[row_of(L, ti, r)];
     }
     keep_t(T);
-    block_form<NT, false>(L, S, W);
+    block_form<NT>(L, S, W);
   } else {
     __syncthreads();  // the panels are read: S.R may be overwritten
 #pragma unroll
@@ -1614,7 +1621,7 @@ struct NoT {};
 template <int NT, int P, bool ELDS, bool SVD = false, bool DENSE = false, bool TG = false, bool PSW = false,
           bool FAST = false>
 __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, const Inst& I, const int flags,
-                          const int jpair, double* tscr = nullptr) {
+                          const int jpair, double* tscr = nullptr, double* wscr = nullptr) {
   static_assert(!PSW || (DENSE && !ELDS), "pre-swizzled slices are dense and read from device memory");
   static_assert(!(TG && SVD), "the SVD stabilizer keeps T in registers");
   static_assert(!FAST || (P == NT && !SVD), "the blocked QR needs one wave per column tile");
@@ -1761,7 +1768,7 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
       if constexpr (TG) {
         RM<NT, P> Tr;
         stabilize_sorted<NT, ELDS>(
-            n, S, W, dcol[0], first, &sgn_u, [] {},
+            n, S, W, dcol[0], first, &sgn_u, wscr, [] {},
             [&]() -> RM<NT, P>& {
               // rows in sorted order: from the scratch's register layout, from
               // forward stage jpair, or of the identity
@@ -1803,7 +1810,7 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
             });
       } else {
         stabilize_sorted<NT, ELDS>(
-            n, S, W, dcol[0], first, &sgn_u,
+            n, S, W, dcol[0], first, &sgn_u, wscr,
             [&] {
               const Lane L = lane_id_per_item();
               const int base = (16 * L.w + L.cl) * G::LDR;
@@ -1916,7 +1923,10 @@ __device__ __forceinline__ void sweep_items(const Inst* __restrict__ insts, cons
   // for sizes whose factor store is in device memory, that store follows it
   constexpr size_t tdoubles = (size_t)Geo<NT, P>::CT * P * NT * 256;
   constexpr size_t rdoubles = Smem<NT, P, ELDS>::RG ? (size_t)Geo<NT, P>::NP * Geo<NT, P>::LDR : 0;
-  double* ts = TG ? tscr + (size_t)blockIdx.x * (tdoubles + rdoubles) : nullptr;
+  // and the columns of the block being factorized, as sorted, for another sort
+  constexpr size_t wdoubles = FAST ? (size_t)NT * NT * 256 : 0;
+  constexpr size_t all = (TG ? tdoubles : 0) + rdoubles + wdoubles;
+  double* ts = all != 0 ? tscr + (size_t)blockIdx.x * all : nullptr;
   if constexpr (Smem<NT, P, ELDS>::RG) {
     static_assert(TG, "the factor store in device memory needs the workgroup scratch");
     if (L.t == 0) S.rg = ts + tdoubles;
@@ -1931,7 +1941,7 @@ __device__ __forceinline__ void sweep_items(const Inst* __restrict__ insts, cons
     if (it >= count) break;
     const SweepItem wi = items[it];
     const Inst I = insts[wi.inst];
-    sweep_one<NT, P, ELDS, SVD, DENSE, TG, PSW, FAST>(L, S, I, wi.flags, wi.j, ts);
+    sweep_one<NT, P, ELDS, SVD, DENSE, TG, PSW, FAST>(L, S, I, wi.flags, wi.j, ts, ts + (all - wdoubles));
   }
 }
 
@@ -2220,7 +2230,7 @@ __device__ __forceinline__ void pair_middle(const Lane& L, Smem<NT, P, ELDS>& S,
   // Y <- Mid^{-1} Y through the blocked QR (any backward-stable solve of the
   // middle matrix serves, Sec. 6.1)
   pad_unit<NT>(L, n, P1.v[0]);
-  block_qr<NT, 1>(L, S, P1.v[0], Y.v[0]);
+  block_qr<NT, 1, NT>(L, S, P1.v[0], Y.v[0]);
   block_back_subst<NT>(L, S, Y.v[0]);
   // G = U2 D_Rp^{-1} Y
 #pragma unroll

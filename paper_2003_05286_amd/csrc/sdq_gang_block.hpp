@@ -20,6 +20,8 @@
 // diagonal, zero above) as row-major 16-column rows and once more in the
 // operand order of V X, Tw [16][16], su[16] and R's diagonal [16].
 
+// (4 and 2 give the same errors from n = 144 on, and fewer blocks repeat the sort)
+constexpr double kGangSortedGrowth = 4.0;
 constexpr int kApplyTiles = 5;  // row tiles per wave of a panel application, at most
 
 struct GPanel {
@@ -103,7 +105,7 @@ __device__ __forceinline__ void gang_panel_steps(const Lane& ln, double (&b)[RT]
     h = fma(fma(-h, h, q), hr, h);
     const double hs = copysign(h, alpha);
     const double su = alpha + hs;
-    const double c = rcp_mid(fma(fabs(alpha), h, q));
+    const double c = rcp_mid(0.5 * fma(su, su, s));
     const double d = fma(su, ajc, dot);
     const double cd = -c * d;
     const double f = __hiloint2double(ln.cl > J ? __double2hiint(cd) : 0, __double2loint(cd));
@@ -346,6 +348,61 @@ __device__ __attribute__((noinline)) void gang_apply(const GC& c, int p, int ct_
   __syncthreads();
 }
 
+// C <- Q_p^T C as gang_apply, one reflector at a time (see panel_steps): each
+// reflector's products with the columns are summed over the waves of a column
+// tile through LDS, one barrier a reflector.
+__device__ __attribute__((noinline)) void gang_apply_steps(const GC& c, int p, int ct_lo) {
+  const Lane ln = gang_lane(c);
+  const int nrt = c.geo.npad / 16, cnt = nrt - p, ldr = c.geo.ldr;
+  const int nct = min(c.geo.w / 16, nrt - c.c0 / 16) - ct_lo;
+  if (nct <= 0) return;  // the same for the whole workgroup
+  const int ks = kWaves / nct, cti = ln.w / ks, part = ln.w - cti * ks;
+  const bool on = cti < nct;
+  const GPanel g = panel_at(c, p);
+  const __amdgpu_buffer_rsrc_t r1 = uniform_rsrc(g.v1, nrt * 256), rt_ = uniform_rsrc(g.tw, 256);
+  double* col = L.S + (16 * (ct_lo + min(cti, nct - 1)) + ln.cl) * ldr + 16 * p + ln.g;
+  double a[kApplyTiles][4], x[kApplyTiles][4];
+  const double cd = ld_buf<true>(rt_, ln.cl * 16 + ln.cl, 0);
+#pragma unroll
+  for (int i = 0; i < kApplyTiles; ++i) {
+    const int k = min(part + ks * i, cnt - 1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      a[i][r] = ld_buf<true>(r1, ln.g * 16 + ln.cl + (p + k) * 256, r * 64);
+      x[i][r] = col[16 * k + 4 * r];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kApplyTiles; ++i)
+    if (!(on && part + ks * i < cnt)) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a[i][r] = x[i][r] = 0.0;
+    }
+  rows_landed<kApplyTiles>(x);
+  static_for<16>([&](auto jc) {
+    constexpr int J = decltype(jc)::value;
+    double* pr = L.xbuf + (J & 1) * 256;
+    double q = 0.0;
+#pragma unroll
+    for (int i = 0; i < kApplyTiles; ++i) dot_with<J>(q, a[i], x[i]);
+    q = sum_col(q);
+    if (ln.g == 0) pr[ln.w * 16 + ln.cl] = q;
+    __syncthreads();
+    double s = 0.0;
+    for (int u = ln.g; u < ks; u += 4) s += pr[(min(cti, nct - 1) * ks + u) * 16 + ln.cl];
+    const double f = -bcast_col<J>(cd) * sum_col(s);
+#pragma unroll
+    for (int i = 0; i < kApplyTiles; ++i) axpy_with<J>(x[i], a[i], f);
+  });
+#pragma unroll
+  for (int i = 0; i < kApplyTiles; ++i)
+    if (on && part + ks * i < cnt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) col[16 * (part + ks * i) + 4 * r] = x[i][r];
+    }
+  __syncthreads();
+}
+
 // Unit vectors in the padding columns of the slab (inside npad).
 __device__ void slab_pad_unit(const GC& c) {
   const int np = c.geo.npad, n = c.n;
@@ -391,7 +448,9 @@ __device__ bool bqr_gang(GC& c_io, bool test) {
       L.beta[16 * p + c.t] = __longlong_as_double((long long)ld_coh_u64(g.meta + 16 + c.t));
     }
     // column tiles right of the panel
-    gang_apply<true, true>(c, p, max(0, p + 1 - c.c0 / 16));
+    const int ct_lo = max(0, p + 1 - c.c0 / 16);
+    if (test && p < kStepPanels) gang_apply_steps(c, p, ct_lo);
+    else gang_apply<true, true>(c, p, ct_lo);
   }
   __syncthreads();
   int bad = 0;
@@ -401,7 +460,7 @@ __device__ bool bqr_gang(GC& c_io, bool test) {
       const int cc = idx / np, i = idx - cc * np, gc = c.c0 + cc;
       if (gc >= np) continue;
       const double x = i <= gc ? L.S[cc * ldr + i] : 0.0;
-      if (test && i < gc && gc < n && !(fabs(x) * L.tau[gc] <= kSortedGrowth * fabs(L.beta[i]) * L.tau[i])) bad = 1;
+      if (test && i < gc && gc < n && !(fabs(x) * L.tau[gc] <= kGangSortedGrowth * fabs(L.beta[i]) * L.tau[i])) bad = 1;
       gmem(R)[(int64_t)gc * np + i] = x;
     }
   }
@@ -605,7 +664,7 @@ __device__ bool stabilize_gang(GC& c, double* Tg) {
       double lift = 0.0;
       for (int i = c.l; i < gc; i += 64) {
         const double y = fabs(L.S[cc * ldr + i]) * scale;
-        if (y > kSortedGrowth * fabs(L.beta[i]) * L.tau[i]) lift = fmax(lift, y);
+        if (y > kGangSortedGrowth * fabs(L.beta[i]) * L.tau[i]) lift = fmax(lift, y);
       }
       lift = wave_max(lift);
       if (c.l == 0) {
@@ -615,13 +674,9 @@ __device__ bool stabilize_gang(GC& c, double* Tg) {
       }
     }
     __syncthreads();
-    // Q R, the scaled columns themselves
-    for (int idx = c.t; idx < np * c.geo.w; idx += kGangThreads) {
-      const int cc = idx / np, i = idx - cc * np, gc = c.c0 + cc;
-      if (i > gc) L.S[cc * ldr + i] = 0.0;
-    }
-    __syncthreads();
-    bform_gang(c);
+    // the scaled columns themselves, as the sort left them
+    const double* X = sc_G(c, 0);
+    slab_for_each<false>(c, [&](int i, int gc) { return gmem(X)[(int64_t)gc * np + i]; }, SetOrZero{});
   }
   if (!sorted) return false;
   for (int i = c.t; i < n; i += kGangThreads) L.beta[i] = fabs(L.beta[i]) * L.tau[i];

@@ -201,12 +201,15 @@ __host__ __device__ constexpr bool fast_sweep_tg(int nt) { return nt >= 6; }
 __host__ __device__ constexpr bool sweep_variant_tg(int variant) {
   return variant == 4 || variant == 5 || variant == 6;
 }
-// doubles of T scratch per workgroup of a variant-4/5 sweep (0 otherwise):
-// one 16 x 16 FP64 tile = 256 doubles per (wave, tile column, tile row)
+// doubles of device scratch per workgroup of a sweep: T where the variant keeps
+// it there (one 16 x 16 FP64 tile = 256 doubles per (wave, tile column, tile
+// row)), above kMaxNT tiles the factor store (16 nt x (16 nt + 1)), and for the
+// blocked QR the block's sorted columns
 __host__ __device__ inline int64_t sweep_tscr_doubles(int nt, int variant) {
-  if (!sweep_variant_tg(variant) && !(variant >= kFastPlain && fast_sweep_tg(nt))) return 0;
-  // above kMaxNT tiles the factor store (16 nt x (16 nt + 1)) follows T
-  return (int64_t)nt * nt * 256 + (nt > kMaxNT ? (int64_t)16 * nt * (16 * nt + 1) : 0);
+  const bool fast = variant >= kFastPlain;
+  const int64_t mat = (int64_t)nt * nt * 256;
+  return (sweep_variant_tg(variant) || (fast && fast_sweep_tg(nt)) ? mat : 0) +
+         (nt > kMaxNT ? (int64_t)16 * nt * (16 * nt + 1) : 0) + (fast ? mat : 0);
 }
 hipError_t launch_sweep(int nt, int variant, const Inst* inst, const SweepItem* items, int count,
                         Queue* q, int grid, double* tscr, hipStream_t s);

@@ -19,7 +19,7 @@ constexpr bool kLdsB = NT <= 5;              // a dense slice beside them
 template <class KF>
 hipError_t launch(KF kern, const Inst* inst, const SweepItem* items, int count, Queue* q, int grid, double* tscr,
                   hipStream_t s) {
-  if (TG && !tscr) return hipErrorInvalidValue;
+  if (!tscr) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * NT), 0, s, inst, items, count, q, tscr);
   return hipGetLastError();
 }

@@ -419,7 +419,7 @@ struct LaunchRec {
   int nt, variant, mode, grid, count;
   size_t items_off;  // byte offset of the first item
   size_t queue_off;  // byte offset of this launch's queue counter
-  size_t tscr_off;   // doubles into the T scratch (variant-4/5 sweeps)
+  size_t tscr_off;   // doubles into the sweeps' workgroup scratch
 };
 
 struct Built {
@@ -428,9 +428,9 @@ struct Built {
   std::vector<LaunchRec> launches;
   std::vector<SwzJob> swz;
   size_t o_inst = 0, o_ll = 0;
-  size_t tscr_doubles = 0;  // T scratch of all variant-4/5 sweep launches
+  size_t tscr_doubles = 0;  // workgroup scratch of all sweep launches
   double* swz_base = nullptr;   // where the swizzled operands go
-  double* tscr_base = nullptr;  // T scratch (set by the caller of build_plan)
+  double* tscr_base = nullptr;  // that scratch (set by the caller of build_plan)
   bool fork = true;             // size classes may run on side streams
   int32_t* status = nullptr;
   int count = 0;
@@ -1064,7 +1064,16 @@ sdq_status sdq_greens_noalloc(sdq_ctx* ctx, const sdq_instance* inst, int32_t co
   Built B;
   st = build_plan(ctx, P, status, count, B, (double*)base);
   if (st) return st;
-  const size_t o_img = align(o_tscr + B.tscr_doubles * sizeof(double));
+  size_t o_img = align(o_tscr + B.tscr_doubles * sizeof(double));
+  if (o_img + B.image.size() > sdq::kNoAllocBytes && !P.pivoted) {
+    // the pivoted sweeps need no room for a block's columns: slower, but a
+    // batch that fits with them is not refused
+    P.pivoted = true;
+    B = Built();
+    st = build_plan(ctx, P, status, count, B, (double*)base);
+    if (st) return st;
+    o_img = align(o_tscr + B.tscr_doubles * sizeof(double));
+  }
   if (o_img + B.image.size() > sdq::kNoAllocBytes)
     return fail(ctx, SDQ_EINVAL,
                 "sdq_greens_noalloc: the batch needs " + std::to_string(o_img + B.image.size()) +
