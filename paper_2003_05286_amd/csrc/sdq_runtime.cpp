@@ -932,10 +932,11 @@ sdq_status sdq_greens(sdq_ctx* ctx, const sdq_instance* inst, int32_t count, sdq
         crit = nt;
       }
     }
+    const int sweep = P.pivoted ? 6 : sdq::kFastProd;
     for (int nt = sdq::kProdMinNT; nt <= sdq::kSweepMaxNT; ++nt) {
       if (cnt_nt[nt] == 0) continue;
       if (ctx->bprod == 1 ||
-          (nt == crit && cnt_nt[nt] <= grid_for(ctx, sdq::KK_SWEEP, nt, 6, 1 << 30)))
+          (nt == crit && cnt_nt[nt] <= grid_for(ctx, sdq::KK_SWEEP, nt, sweep, 1 << 30)))
         P.bprod_mask |= 1u << nt;
     }
   }
