@@ -392,11 +392,12 @@ sdq_status sdq_set_stabilizer(sdq_ctx* ctx, int32_t stab);
 sdq_status sdq_similarity(sdq_ctx* ctx, int32_t n, int32_t count, const double* left,
                           const double* right, double* const* mats);
 
-/* Time every kernel variant for each n of n_list[count] (host) on the
- * device, keep the fastest per n in ctx, and if cache_path is not NULL
- * append the choices to that JSON-lines file (read back by later contexts
- * through the same call; an existing entry for (arch, n) is used without
- * re-timing).  Sizes n > 128 have a single kernel and are accepted but not
+/* Time the stabilized sweep for each n of n_list[count] (host) on the device
+ * with one workgroup per CU and with as many as fit, keep the faster per n in
+ * ctx, and if cache_path is not NULL append the choices to that JSON-lines
+ * file (read back by later contexts through the same call; an existing entry
+ * for (arch, n) and the same sweep kernel is used without re-timing, others
+ * are left alone).  Sizes n > 128 have a single kernel and are accepted but not
  * timed. */
 sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const char* cache_path);
 

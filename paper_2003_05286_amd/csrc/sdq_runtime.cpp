@@ -62,6 +62,7 @@ struct Handle {
 struct Tune {
   int variant = 0;     // sweep kernel variant (1 = slice exponential staged in LDS)
   int blocks_per_cu = 0;  // 0 = occupancy limit
+  int sweep = 0;  // the sweep variant that limit was measured on (0: it holds for all)
 };
 
 // one planned batch: what gets uploaded and launched.  Sweeps run first,
@@ -329,8 +330,10 @@ int grid_for(sdq_ctx* ctx, int kind, int nt, int variant, int count) {
     return ng;
   }
   int per_cu = info(ctx, kind, nt, variant).blocks_per_cu;
-  if (kind == sdq::KK_SWEEP && nt <= sdq::kMaxNT && ctx->tune[nt].blocks_per_cu > 0)
-    per_cu = std::min(per_cu, ctx->tune[nt].blocks_per_cu);
+  if (kind == sdq::KK_SWEEP && nt <= sdq::kMaxNT) {
+    const Tune& t = ctx->tune[nt];
+    if (t.blocks_per_cu > 0 && (t.sweep == 0 || t.sweep == variant)) per_cu = std::min(per_cu, t.blocks_per_cu);
+  }
   const long long g = (long long)per_cu * ctx->num_cu;
   return (int)std::max(1LL, std::min<long long>(count, g));
 }
@@ -1905,9 +1908,11 @@ sdq_status sdq_chain_udt(sdq_ctx* ctx, const sdq_instance* inst, int32_t count, 
 // Autotuner: for each n, time sdq_logdet on a synthetic batch (two chains
 // per CU, m = 40, k = 10, a periodic ring's second-order slice exponential,
 // +-1 field) for each grid shape (one workgroup per CU or the occupancy
-// limit), keep the faster.  The variant is that of the pivoted sweeps, which
-// sdq_logdet does not run: it stays as it is.  Results are cached as JSON
-// lines {"arch", "n", "variant", "blocks_per_cu", "ms"}.
+// limit), keep the faster for the sweep that ran.  The variant is that of the
+// pivoted sweeps, which sdq_logdet does not run: it stays as it is.  Results
+// are cached as JSON lines {"arch", "n", "variant", "blocks_per_cu", "ms",
+// "sweep"}; lines of another sweep, or of none (they timed the pivoted
+// kernels), do not count.
 sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const char* cache_path) {
   SDQ_API_RANGE("sdq_tune");
   if (!ctx) return SDQ_EINVAL;
@@ -1919,17 +1924,21 @@ sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const ch
   HIP_TRY(hipGetDeviceProperties(&prop, ctx->device), "hipGetDeviceProperties");
   std::string arch = prop.gcnArchName;
   arch = arch.substr(0, arch.find(':'));
-  std::map<int, Tune> cached;
+  const int sweep = ctx->stab == SDQ_STAB_SVD ? 2 : sdq::kFastPlain;  // what sdq_logdet runs
+  std::map<int, int> cached;
   if (cache_path) {
     if (FILE* f = fopen(cache_path, "r")) {
       char line[512];
       while (fgets(line, sizeof line, f)) {
         char a[64] = {0};
-        int n = 0, v = 0, b = 0;
-        if (sscanf(line, " {\"arch\": \"%63[^\"]\", \"n\": %d, \"variant\": %d, \"blocks_per_cu\": %d", a, &n, &v,
-                   &b) == 4 &&
-            arch == a)
-          cached[n] = Tune{v, b};
+        int n = 0, v = 0, b = 0, sw = 0;
+        double ms = 0.0;
+        if (sscanf(line,
+                   " {\"arch\": \"%63[^\"]\", \"n\": %d, \"variant\": %d, \"blocks_per_cu\": %d, \"ms\": %lf, "
+                   "\"sweep\": %d",
+                   a, &n, &v, &b, &ms, &sw) == 6 &&
+            arch == a && sw == sweep)
+          cached[n] = b;
       }
       fclose(f);
     }
@@ -1943,7 +1952,8 @@ sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const ch
     if (is_gang(nt)) continue;  // one gang kernel per size: nothing to choose
     auto hit = cached.find(n);
     if (hit != cached.end()) {
-      ctx->tune[nt] = hit->second;
+      ctx->tune[nt].blocks_per_cu = hit->second;
+      ctx->tune[nt].sweep = sweep;
       continue;
     }
     const int m = 40, k = 10, chains = 2 * ctx->num_cu;
@@ -1989,7 +1999,7 @@ sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const ch
       inst[c] = sdq_instance{n, m, k, 0, dE, nullptr, dF + (size_t)c * m * n, 0.65};
     // the occupancy cap (one workgroup per CU, or the kernel's limit)
     std::vector<Tune> cands;
-    for (int b : {1, 0}) cands.push_back(Tune{ctx->tune[nt].variant, b});
+    for (int b : {1, 0}) cands.push_back(Tune{ctx->tune[nt].variant, b, sweep});
     double best = 1e300;
     Tune bt = ctx->tune[nt];
     for (const Tune& c : cands) {
@@ -2014,8 +2024,9 @@ sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const ch
     ctx->tune[nt] = bt;
     if (result == SDQ_OK && cache_path) {
       if (FILE* f = fopen(cache_path, "a")) {
-        fprintf(f, "{\"arch\": \"%s\", \"n\": %d, \"variant\": %d, \"blocks_per_cu\": %d, \"ms\": %.4f}\n",
-                arch.c_str(), n, bt.variant, bt.blocks_per_cu, best);
+        fprintf(f,
+                "{\"arch\": \"%s\", \"n\": %d, \"variant\": %d, \"blocks_per_cu\": %d, \"ms\": %.4f, \"sweep\": %d}\n",
+                arch.c_str(), n, bt.variant, bt.blocks_per_cu, best, sweep);
         fclose(f);
       }
     }
