@@ -24,6 +24,26 @@
 constexpr double kGangSortedGrowth = 4.0;
 constexpr int kApplyTiles = 5;  // row tiles per wave of a panel application, at most
 
+// The exchange area of a panel application or of a triangular solve: six
+// 16 x 16 slots behind the slab where they fit, else the four of L.xbuf.
+__host__ __device__ constexpr bool slots_in_slab(const GangGeom& g) { return g.w * g.ldr + 6 * 256 <= kGangSlab; }
+// That area and kApplyTiles hold for every size: nct column tiles of a member
+// share the waves, and a wave's tiles and the slots (four for one or two
+// column tiles, else one each) follow.
+constexpr bool gang_blocks_fit() {
+  for (int nt = kMaxNT + 1; nt <= kGangMaxN / 16; ++nt) {
+    const GangGeom g = gang_geom(nt);
+    if (g.G == 0) return false;
+    for (int nct = 1; nct <= g.w / 16; ++nct) {
+      const int ks = kWaves / nct, slots = nct <= 2 ? 4 : nct;
+      if (ks * kApplyTiles < nt && nct == g.w / 16) return false;
+      if (slots > (slots_in_slab(g) ? 6 : 4)) return false;
+    }
+  }
+  return true;
+}
+static_assert(gang_blocks_fit(), "a panel application's tiles and exchange slots");
+
 struct GPanel {
   double* v1;
   double* v2;
@@ -284,7 +304,7 @@ __device__ __attribute__((noinline)) void gang_apply(const GC& c, int p, int ct_
   const GPanel g = panel_at(c, p);
   const __amdgpu_buffer_rsrc_t r1 = uniform_rsrc(g.v1, nrt * 256), r2 = uniform_rsrc(g.v2, nrt * 256),
                                rt_ = uniform_rsrc(g.tw, 256);
-  double* xb = c.geo.w * ldr + 6 * 256 <= kGangSlab ? L.S + c.geo.w * ldr : L.xbuf;
+  double* xb = slots_in_slab(c.geo) ? L.S + c.geo.w * ldr : L.xbuf;
   double* col = L.S + (16 * (ct_lo + min(cti, nct - 1)) + ln.cl) * ldr + 16 * p + ln.g;
   double tv[4], a[kApplyTiles][4];
   d4 x = d4{0.0, 0.0, 0.0, 0.0};
@@ -531,7 +551,7 @@ __device__ void bsolve_gang(const GC& c) {
   for (int p = 0; p < nrt; ++p) gang_apply<true, false>(c, p, 0);
   const int nct = min(c.geo.w / 16, nrt - c.c0 / 16);
   if (nct <= 0) return;
-  double* xb = c.geo.w * ldr + 6 * 256 <= kGangSlab ? L.S + c.geo.w * ldr : L.xbuf;
+  double* xb = slots_in_slab(c.geo) ? L.S + c.geo.w * ldr : L.xbuf;
   const int ks = kWaves / nct;
 #pragma unroll 1
   for (int p = nrt - 1; p >= 0; --p) {

@@ -275,8 +275,8 @@ struct GangGeom {
   int ldr;   // LDS column stride
 };
 
-__host__ __device__ inline GangGeom gang_geom(int nt) {
-  GangGeom g;
+__host__ __device__ constexpr GangGeom gang_geom(int nt) {
+  GangGeom g{};
   g.npad = 16 * nt;
   g.ldr = g.npad + 4;
   g.G = 0;
