@@ -2846,12 +2846,11 @@ __global__ __launch_bounds__(64 * P) void k_similarity(int n, int count, double*
 // waves per chain: one per 16-column tile, at most four
 constexpr int waves_for(int nt) { return nt < 4 ? nt : 4; }
 // LDS-staged slice exponential: where it still leaves room for useful occupancy
-constexpr bool lds_variant(int nt) { return nt >= 3 && nt <= 5; }
 
 template <int NT>
 struct Launch {
   static constexpr int P = waves_for(NT);
-  static constexpr bool kLds = lds_variant(NT);
+  static constexpr bool kLds = pivoted_variant(NT) == 1;
   static constexpr bool kPairLds = NT <= 5;  // operand staging buffer fits beside the factor store
   static constexpr bool kSvd = NT <= 5;  // A and T of the Jacobi SVD both fit in LDS
   // block products (k_prod) and the pivoted sweep over them (variant 6), one
@@ -2895,8 +2894,7 @@ struct Launch {
   static hipError_t dense_pair_info(KernelInfo* out) {
     return info_of<NT>(k_pair<NT, NT, kPairLds, PAIR_TDISP_DENSE>, (int)sizeof(Smem<NT, NT, kPairLds>), out);
   }
-  // variants 4 and 5: one wave per 16-column tile (PT = NT waves), T in the
-  // per-workgroup scratch between blocks
+  // one wave per 16-column tile
   static constexpr int PT = NT;
   static hipError_t sweep(int variant, const Inst* inst, const SweepItem* items, int count, Queue* q,
                           int grid, double* tscr, hipStream_t s) {
@@ -2909,22 +2907,15 @@ struct Launch {
       }
       return hipErrorInvalidValue;
     }
-    if (variant == 4 || variant == 5) {
+    if (variant != pivoted_variant(NT)) return hipErrorInvalidValue;
+    if constexpr (pivoted_variant(NT) == 4) {
       if (!tscr) return hipErrorInvalidValue;
-      if (variant == 5 && kLds)
-        hipLaunchKernelGGL((k_sweep<NT, PT, kLds, false, false, true>), dim3(grid), dim3(Geo<NT, PT>::THREADS), 0,
-                           s, inst, items, count, q, tscr);
-      else
-        hipLaunchKernelGGL((k_sweep<NT, PT, false, false, false, true>), dim3(grid), dim3(Geo<NT, PT>::THREADS),
-                           0, s, inst, items, count, q, tscr);
-      return hipGetLastError();
+      hipLaunchKernelGGL((k_sweep<NT, PT, false, false, false, true>), dim3(grid), dim3(Geo<NT, PT>::THREADS), 0, s,
+                         inst, items, count, q, tscr);
+    } else {
+      hipLaunchKernelGGL((k_sweep<NT, P, kLds>), dim3(grid), dim3(Geo<NT, P>::THREADS), 0, s, inst, items, count, q,
+                         none);
     }
-    if (variant == 1 && kLds)
-      hipLaunchKernelGGL((k_sweep<NT, P, kLds>), dim3(grid), dim3(Geo<NT, P>::THREADS), 0, s, inst,
-                         items, count, q, none);
-    else
-      hipLaunchKernelGGL((k_sweep<NT, P, false>), dim3(grid), dim3(Geo<NT, P>::THREADS), 0, s, inst,
-                         items, count, q, none);
     return hipGetLastError();
   }
   static hipError_t pair(int mode, const Inst* inst, const PairItem* items, int count,
@@ -2968,17 +2959,14 @@ struct Launch {
     return e;
   }
   static hipError_t info(int kind, int variant, KernelInfo* out) {
-    if (kind == KK_SWEEP && (variant == 4 || variant == 5)) {
-      if (variant == 5 && kLds)
-        return info_of<PT>(k_sweep<NT, PT, kLds, false, false, true>, (int)sizeof(Smem<NT, PT, kLds>), out);
-      return info_of<PT>(k_sweep<NT, PT, false, false, false, true>, (int)sizeof(Smem<NT, PT, false>), out);
-    }
     if (kind == KK_SWEEP) {
       if constexpr (kSvd)
         if (variant == 2) return info_of(k_sweep<NT, P, true, true>, (int)sizeof(Smem<NT, P, true>), out);
-      if (variant == 1 && kLds)
+      if (variant != pivoted_variant(NT)) return hipErrorInvalidValue;
+      if constexpr (pivoted_variant(NT) == 4)
+        return info_of<PT>(k_sweep<NT, PT, false, false, false, true>, (int)sizeof(Smem<NT, PT, false>), out);
+      else
         return info_of(k_sweep<NT, P, kLds>, (int)sizeof(Smem<NT, P, kLds>), out);
-      return info_of(k_sweep<NT, P, false>, (int)sizeof(Smem<NT, P, false>), out);
     }
     if (kind == KK_PAIR)
       return info_of<PT>(k_pair<NT, PT, kPairLds, PAIR_TDISP>, (int)sizeof(Smem<NT, PT, kPairLds>), out);

@@ -105,15 +105,14 @@ struct GC {
 __device__ __forceinline__ double* sc_R(const GC& c) { return c.base; }
 __device__ __forceinline__ double* sc_V(const GC& c) { return c.base + gang_mat(c.geo); }
 __device__ __forceinline__ double* sc_T(const GC& c) { return c.base + 2 * gang_mat(c.geo); }
-__device__ __forceinline__ double* sc_U(const GC& c) { return c.base + 3 * gang_mat(c.geo); }
-__device__ __forceinline__ double* sc_G(const GC& c, int b) { return c.base + (4 + b) * gang_mat(c.geo); }
-__device__ __forceinline__ double* sc_X(const GC& c) { return c.base + 6 * gang_mat(c.geo); }
+__device__ __forceinline__ double* sc_G(const GC& c, int b) { return c.base + (3 + b) * gang_mat(c.geo); }
+__device__ __forceinline__ double* sc_X(const GC& c) { return c.base + 5 * gang_mat(c.geo); }
 __device__ __forceinline__ double* sc_cand(const GC& c, int buf) {
-  return c.base + 8 * gang_mat(c.geo) + (int64_t)buf * c.geo.G * gang_cand_stride(c.geo);
+  return c.base + 7 * gang_mat(c.geo) + (int64_t)buf * c.geo.G * gang_cand_stride(c.geo);
 }
-__device__ __forceinline__ double* sc_V2(const GC& c) { return c.base + 7 * gang_mat(c.geo); }
+__device__ __forceinline__ double* sc_V2(const GC& c) { return c.base + 6 * gang_mat(c.geo); }
 __device__ __forceinline__ double* sc_tw(const GC& c) {
-  return c.base + 8 * gang_mat(c.geo) + 2 * c.geo.G * gang_cand_stride(c.geo) + 64;
+  return c.base + 7 * gang_mat(c.geo) + 2 * c.geo.G * gang_cand_stride(c.geo) + 64;
 }
 __device__ __forceinline__ double* sc_meta(const GC& c) { return sc_tw(c) + (int64_t)(c.geo.npad / 16) * 256; }
 __device__ __forceinline__ double* sc_keys(const GC& c) { return sc_meta(c) + (int64_t)(c.geo.npad / 16) * 32; }
@@ -1415,11 +1414,7 @@ hipError_t launch_gang_sweep(bool pivoted, const Inst* inst, SweepItem* items, i
     }();
     if (e == hipSuccess) e = launch_fill_i32((int32_t*)a.bars, a.ngangs * kGangBarWords, 0, s);
     if (e != hipSuccess) return e;
-    e = [&]() -> hipError_t {
-#define C(R) coop_launch(k_gang_sweep<R, false>, a, s, inst, items, count, 0)
-      SDQ_RL_SWITCH(C)
-#undef C
-    }();
+    e = coop_launch(k_gang_sweep<16, false>, a, s, inst, items, count, 0);  // (the same for every size)
     if (e == hipSuccess) e = launch_fill_i32((int32_t*)a.bars, a.ngangs * kGangBarWords, 0, s);
     if (e != hipSuccess) return e;
   }
@@ -1432,10 +1427,9 @@ hipError_t launch_gang_sweep(bool pivoted, const Inst* inst, SweepItem* items, i
 hipError_t launch_gang_pair(int mode, const Inst* inst, const PairItem* items, int count,
                             const int32_t* l_list, GangArgs a, hipStream_t s) {
   if (mode != PAIR_EQUAL && mode != PAIR_TDISP && mode != PAIR_GRAD) return hipErrorInvalidValue;
-#define C(R)                                                                                  \
-  (mode == PAIR_EQUAL ? coop_launch(k_gang_pair<PAIR_EQUAL, R>, a, s, inst, items, count, l_list) \
-   : mode == PAIR_TDISP ? coop_launch(k_gang_pair<PAIR_TDISP, R>, a, s, inst, items, count, l_list) \
-                        : coop_launch(k_gang_pair<PAIR_GRAD, R>, a, s, inst, items, count, l_list))
+  if (mode == PAIR_TDISP) return coop_launch(k_gang_pair<PAIR_TDISP, 16>, a, s, inst, items, count, l_list);
+  if (mode == PAIR_GRAD) return coop_launch(k_gang_pair<PAIR_GRAD, 16>, a, s, inst, items, count, l_list);
+#define C(R) coop_launch(k_gang_pair<PAIR_EQUAL, R>, a, s, inst, items, count, l_list)
   SDQ_RL_SWITCH(C)
 #undef C
 }

@@ -598,10 +598,9 @@ __device__ void sort_gang(GC& c, int pass) {
   gang_sync(c);
   for (int i = c.t; i < np; i += kGangThreads) L.tau[i] = i < n ? gmem(keys)[i] : -1.0;
   __syncthreads();
-  int rank[(kGangMaxN + kGangThreads - 1) / kGangThreads], from = 0;
-  double sc = 1.0;
   static_assert(kGangMaxN <= kGangThreads, "one column per thread");
-  rank[0] = c.t;
+  int rank = c.t, from = 0;
+  double sc = 1.0;
   if (c.t < n) {
     const double k = L.tau[c.t];
     int before = 0;
@@ -610,16 +609,16 @@ __device__ void sort_gang(GC& c, int pass) {
       const double ki = L.tau[i];
       before += (ki > k || (ki == k && i < c.t)) ? 1 : 0;
     }
-    rank[0] = before;
+    rank = before;
     sc = gmem(scales)[c.t];
     from = pass == 0 ? c.t : (int)L.piv[c.t];
   }
   __syncthreads();
   if (c.t < np) {
-    L.tau[rank[0]] = sc;
-    L.piv[rank[0]] = c.t < n ? from : c.t;
+    L.tau[rank] = sc;
+    L.piv[rank] = c.t < n ? from : c.t;
     // place of every column, for the exchange (L.beta is free)
-    L.beta[c.t] = (double)rank[0];
+    L.beta[c.t] = (double)rank;
   }
   __syncthreads();
   double* X = sc_G(c, 0);

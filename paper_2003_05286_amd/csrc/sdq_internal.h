@@ -183,14 +183,15 @@ hipError_t launch_hmc_end(int count, int nf, const HmcChain* chains, double half
 hipError_t launch_swizzle(const double* e, int n, int trans, double* out, hipStream_t s);
 // Sweep kernel variants with column pivoting, for what returns the factors or
 // multiplies them out (the plain scheme, sdq_chain_udt), and the SVD:
-//   0  slice exponential read from its swizzled HBM copy, T in registers
-//   1  slice exponential staged in LDS (3 <= nt <= 5), T in registers
+//   0  (nt <= 2) slice exponential read from its swizzled HBM copy, T in registers
+//   1  (nt 3 .. 5) slice exponential staged in LDS, T in registers
 //   2  Jacobi SVD stabilizer
-//   4  one wave per 16-column tile, T kept in a per-workgroup HBM scratch
-//      between blocks (frees a register matrix), exponential from HBM
-//   5  as 4 with the exponential staged in LDS (3 <= nt <= 5)
+//   4  (nt >= 6) one wave per 16-column tile, T kept in a per-workgroup HBM
+//      scratch between blocks (with four waves the register matrices of n > 80
+//      spill), exponential from HBM
 // variant 6: the sweep over block products (k_prod) with one factorization
 // each, one wave per tile with T in the workgroup scratch like variant 4
+__host__ __device__ constexpr int pivoted_variant(int nt) { return nt >= 6 ? 4 : nt >= 3 ? 1 : 0; }
 // The sweeps with the norm-sorted blocked QR (one wave per tile), which every
 // caller takes whose factors are not themselves a result:
 constexpr int kFastPlain = 7;  // slices E diag(v)
@@ -199,7 +200,7 @@ constexpr int kFastProd = 9;   // block products (k_prod), tile counts kProdMinN
 // T in the workgroup scratch between blocks (else in registers)
 __host__ __device__ constexpr bool fast_sweep_tg(int nt) { return nt >= 6; }
 __host__ __device__ constexpr bool sweep_variant_tg(int variant) {
-  return variant == 4 || variant == 5 || variant == 6;
+  return variant == 4 || variant == 6;
 }
 // doubles of device scratch per workgroup of a sweep: T where the variant keeps
 // it there (one 16 x 16 FP64 tile = 256 doubles per (wave, tile column, tile
@@ -292,13 +293,13 @@ __host__ __device__ constexpr GangGeom gang_geom(int nt) {
   return g;
 }
 
-// per-gang scratch (doubles): R, V, T, U, two G buffers, X, V in operand
-// order, candidates, then the panels' triangular factors and diagonals, and
+// per-gang scratch (doubles): R, V, T, two G buffers, X, V in operand order,
+// candidates, then the panels' triangular factors and diagonals, and
 // the sort's keys and scales
 __host__ __device__ inline int64_t gang_mat(const GangGeom& g) { return (int64_t)g.npad * g.npad; }
 __host__ __device__ inline int64_t gang_cand_stride(const GangGeom& g) { return g.npad + 8; }
 __host__ __device__ inline int64_t gang_doubles(const GangGeom& g) {
-  return 8 * gang_mat(g) + 2 * g.G * gang_cand_stride(g) + 64 + (int64_t)(g.npad / 16) * (256 + 32) + 2 * g.npad;
+  return 7 * gang_mat(g) + 2 * g.G * gang_cand_stride(g) + 64 + (int64_t)(g.npad / 16) * (256 + 32) + 2 * g.npad;
 }
 
 struct GangArgs {

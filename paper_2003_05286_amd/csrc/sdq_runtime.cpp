@@ -60,7 +60,6 @@ struct Handle {
 };
 
 struct Tune {
-  int variant = 0;     // sweep kernel variant (1 = slice exponential staged in LDS)
   int blocks_per_cu = 0;  // 0 = occupancy limit
   int sweep = 0;  // the sweep variant that limit was measured on (0: it holds for all)
 };
@@ -101,7 +100,7 @@ struct sdq_ctx {
   std::string err;
   int num_cu = 256;
   DevBuf d_upload, d_ck, d_swz, d_fin;
-  DevBuf d_tscr;  // per-workgroup T scratch of the variant-4/5 sweeps
+  DevBuf d_tscr;  // workgroup scratch of the sweeps
   DevBuf d_gang;  // per-gang scratch of the n > 128 kernels (bars first)
   DevBuf d_ptrs;  // matrix pointer table of sdq_similarity
   DevBuf d_metro;  // sdq_metropolis: field table, proposed log|det|, signs and status
@@ -497,14 +496,13 @@ sdq_status build_plan(sdq_ctx* ctx, Plan& P, int32_t* status, int count, Built& 
     // (Dense slices have the QR only, whatever the context's stabilizer.)
     const bool fast =
         !P.pivoted && (P.dense || ctx->stab == SDQ_STAB_QR) && r.nt <= sdq::kSweepMaxNT;
-    const int tuned = r.nt <= sdq::kMaxNT ? ctx->tune[r.nt].variant : 4;
     const int variant = sweep_is_gang(r.nt) ? (P.pivoted ? 1 : 0)
                         : fast ? (bprod               ? sdq::kFastProd
                                   : P.dense           ? sdq::kFastDense
                                                       : sdq::kFastPlain)
                         : bprod ? 6
-                        : r.nt > sdq::kMaxNT ? 4
-                        : (ctx->stab == SDQ_STAB_SVD ? 2 : tuned);
+                        : ctx->stab == SDQ_STAB_SVD && r.nt <= sdq::kMaxNT ? 2
+                                                                           : sdq::pivoted_variant(r.nt);
     const int grid = grid_for(ctx, sdq::KK_SWEEP, r.nt, variant, r.count);
     // classes may run concurrently: each launch gets its own T scratch
     const size_t toff = B.tscr_doubles;
@@ -832,16 +830,8 @@ sdq_status sdq_create(sdq_ctx** out, int device, void* hip_stream) {
       ctx->na_ev = nullptr;
     }
   }
-  for (int nt = 0; nt <= sdq::kMaxNT; ++nt) {
-    ctx->tune[nt] = Tune{};
-    // defaults (sdq_tune measures them): the slice exponential staged in LDS
-    // where that variant exists; above 80 sites one wave per tile with T in
-    // scratch (with four waves the register matrices of n > 80 spill)
-    ctx->tune[nt].variant = nt >= 6 ? 4 : ((nt >= 3 && nt <= 5) ? 1 : 0);
-  }
-  // debug overrides (environment): SDQ_SWEEP_VARIANT, SDQ_BLOCKS_PER_CU
-  if (const char* v = getenv("SDQ_SWEEP_VARIANT"))
-    for (int nt = 0; nt <= sdq::kMaxNT; ++nt) ctx->tune[nt].variant = atoi(v);
+  for (int nt = 0; nt <= sdq::kMaxNT; ++nt) ctx->tune[nt] = Tune{};
+  // debug override (environment)
   if (const char* v = getenv("SDQ_BLOCKS_PER_CU"))
     for (int nt = 0; nt <= sdq::kMaxNT; ++nt) ctx->tune[nt].blocks_per_cu = atoi(v);
   if (const char* v = getenv("SDQ_BLOCK_PRODUCTS")) ctx->bprod = std::min(2, std::max(0, atoi(v)));
@@ -1908,11 +1898,10 @@ sdq_status sdq_chain_udt(sdq_ctx* ctx, const sdq_instance* inst, int32_t count, 
 // Autotuner: for each n, time sdq_logdet on a synthetic batch (two chains
 // per CU, m = 40, k = 10, a periodic ring's second-order slice exponential,
 // +-1 field) for each grid shape (one workgroup per CU or the occupancy
-// limit), keep the faster for the sweep that ran.  The variant is that of the
-// pivoted sweeps, which sdq_logdet does not run: it stays as it is.  Results
-// are cached as JSON lines {"arch", "n", "variant", "blocks_per_cu", "ms",
-// "sweep"}; lines of another sweep, or of none (they timed the pivoted
-// kernels), do not count.
+// limit), keep the faster for the sweep that ran.  Results are cached as JSON
+// lines {"arch", "n", "variant", "blocks_per_cu", "ms", "sweep"} ("variant":
+// the pivoted sweep of that size, which is fixed); lines of another sweep, or of
+// none (they timed the pivoted kernels), do not count.
 sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const char* cache_path) {
   SDQ_API_RANGE("sdq_tune");
   if (!ctx) return SDQ_EINVAL;
@@ -1999,7 +1988,7 @@ sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const ch
       inst[c] = sdq_instance{n, m, k, 0, dE, nullptr, dF + (size_t)c * m * n, 0.65};
     // the occupancy cap (one workgroup per CU, or the kernel's limit)
     std::vector<Tune> cands;
-    for (int b : {1, 0}) cands.push_back(Tune{ctx->tune[nt].variant, b, sweep});
+    for (int b : {1, 0}) cands.push_back(Tune{b, sweep});
     double best = 1e300;
     Tune bt = ctx->tune[nt];
     for (const Tune& c : cands) {
@@ -2026,7 +2015,7 @@ sdq_status sdq_tune(sdq_ctx* ctx, const int32_t* n_list, int32_t count, const ch
       if (FILE* f = fopen(cache_path, "a")) {
         fprintf(f,
                 "{\"arch\": \"%s\", \"n\": %d, \"variant\": %d, \"blocks_per_cu\": %d, \"ms\": %.4f, \"sweep\": %d}\n",
-                arch.c_str(), n, bt.variant, bt.blocks_per_cu, best, sweep);
+                arch.c_str(), n, sdq::pivoted_variant(nt), bt.blocks_per_cu, best, sweep);
         fclose(f);
       }
     }
