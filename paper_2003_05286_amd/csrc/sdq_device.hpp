@@ -1187,6 +1187,31 @@ __device__ __forceinline__ void stage_swizzled(const Lane& L, double* dst, const
   }
 }
 
+// A dense n x n matrix, zero-padded, into an LDS array of row stride LDR,
+// sixteen loads of a lane together; between barriers.
+template <int NT, int P>
+__device__ __forceinline__ void stage_dense(const Lane& L, double* dst, const double* b, const int n) {
+  using G = Geo<NT, P>;
+  constexpr int IT = G::NP * G::NP / G::THREADS, CH = IT % 16 == 0 ? 16 : 4;
+  static_assert(G::NP * G::NP % G::THREADS == 0 && IT % CH == 0, "whole rounds");
+  __syncthreads();
+#pragma unroll 1
+  for (int e = 0; e < IT; e += CH) {
+    double x[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+      const int idx = L.t + (e + q) * G::THREADS, i = idx / G::NP, kk = idx - i * G::NP;
+      x[q] = gmem(b)[(size_t)min(i, n - 1) * n + min(kk, n - 1)];
+    }
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+      const int idx = L.t + (e + q) * G::THREADS, i = idx / G::NP, kk = idx - i * G::NP;
+      dst[i * G::LDR + kk] = i < n && kk < n ? x[q] : 0.0;
+    }
+  }
+  __syncthreads();
+}
+
 // W <- B W (one wave per tile column) for B in the swizzled operand layout in
 // device memory, staged through `buf` CH tile columns at a time: nine waves
 // that each read the whole operand through buffer loads wait for most of them
@@ -1722,7 +1747,14 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
           const EOp<NT, P, false> bop{nullptr, I.field + (size_t)(q - 1) * G::NP * G::NP, L.l};
           gemm_rb<NT, P>(L, bop, W, W);
         } else {
-          gemm_gm<NT, P>(L, Bq, n, adj, W, W);
+          // through the factor store, which is free during the products (read
+          // from device memory by every wave, the products took 1.3 times as
+          // long at n = 112 and their addresses spilled a thousand registers)
+          stage_dense<NT, P>(L, S.R, Bq, n);
+          if (adj)
+            gemm_rb<NT, P>(L, [&](int, int, int, int i, int kk) -> double { return S.R[kk * G::LDR + i]; }, W, W);
+          else
+            gemm_rb<NT, P>(L, [&](int, int, int, int i, int kk) -> double { return S.R[i * G::LDR + kk]; }, W, W);
         }
       }
     } else {
