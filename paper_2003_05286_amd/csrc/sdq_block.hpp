@@ -285,18 +285,22 @@ __device__ __forceinline__ void sum_and_pick(double p, double x, bool in_g0, dou
 // column of zeros, or one whose squares leave the range of a double, is a
 // special case: plain_panel (the caller looks at beta) and panel_careful.  On return b holds R above the diagonal, the reflectors below
 // it and alpha on it; su_l, beta_l the reflector's and R's diagonal entry of
-// the lane's column; T row cl of the triangular factor.
+// the lane's column; T row cl of the triangular factor.  Columns from `live`
+// on are unit vectors (padding): of a one-tile matrix, groups of four such steps
+// are left out, with T zero there and R's diagonal one (a chain of two sites
+// took 1.3 times as long as with pivoting otherwise; at eight tiles the
+// branches spill a thousand registers).
 // Bound: one wave issues an instruction about every five cycles whatever its
 // dependences are, so the step is written for few instructions (82 at 64
 // rows): straight-line code, no LDS access, no barrier; the dot products of
 // column J with all columns give its norm and the Gram entries of the
 // triangular factor too.
 template <int RT, int NT>
-__device__ __forceinline__ void panel_qr(const Lane& L, double (&b)[NT][4], double (&T)[16], double& su_l,
-                                         double& beta_l) {
+__device__ __forceinline__ void panel_qr(const Lane& L, const int live, double (&b)[NT][4], double (&T)[16],
+                                         double& su_l, double& beta_l) {
   rows_landed<RT>(b);
-  double hs_l = 0.0;
-  static_for<16>([&](auto jc) {
+  double hs_l = -1.0;
+  auto step = [&](auto jc) {
     constexpr int J = decltype(jc)::value, R0 = J >> 2, G0 = J & 3;
     double p = 0.0;
     dot_head<J, RT>(p, b);
@@ -332,6 +336,15 @@ __device__ __forceinline__ void panel_qr(const Lane& L, double (&b)[NT][4], doub
     // (the sum is zero in the rows from J on)
     const double ts = tri_dot<J>(d, T);
     T[J] = L.cl == J ? c : -c * ts;
+  };
+  static_for<4>([&](auto gc) {
+    constexpr int J0 = 4 * decltype(gc)::value;
+    if (NT > 1 || J0 < live) {
+      static_for<4>([&](auto jc) { step(std::integral_constant<int, J0 + decltype(jc)::value>{}); });
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) T[J0 + q] = 0.0;
+    }
   });
   // beta = -hs, su = alpha + hs, alpha on the diagonal
   beta_l = -hs_l;
@@ -544,10 +557,10 @@ __device__ __forceinline__ void rotate_down(double (&b)[NT][4]) {
 // diagonal one) and store it: panel and R above it, Tw, the reflectors'
 // diagonal (S.tau) and diag R.
 template <int NT, class SM>
-__device__ __forceinline__ void panel_factor(SM& S, double (&b)[NT][4], const int p) {
+__device__ __forceinline__ void panel_factor(SM& S, double (&b)[NT][4], const int p, const int n) {
   const Lane L = lane_id_per_item();
   double T[16], su_l, beta_l;
-  const int cnt = NT - p;
+  const int cnt = NT - p, live = n - 16 * p;
   double* vp = S.R + panel_off<NT, SM>(p);
   // R above the panel goes out first; its registers are zero rows from here on.
   // The panel's rows go to their place as they are, for panel_careful.
@@ -565,10 +578,10 @@ __device__ __forceinline__ void panel_factor(SM& S, double (&b)[NT][4], const in
     }
   if constexpr (NT >= 4) {
     // the lower half of the panels have at most half the rows
-    if (cnt <= NT / 2) panel_qr<NT / 2, NT>(L, b, T, su_l, beta_l);
-    else panel_qr<NT, NT>(L, b, T, su_l, beta_l);
+    if (cnt <= NT / 2) panel_qr<NT / 2, NT>(L, live, b, T, su_l, beta_l);
+    else panel_qr<NT, NT>(L, live, b, T, su_l, beta_l);
   } else {
-    panel_qr<NT, NT>(L, b, T, su_l, beta_l);
+    panel_qr<NT, NT>(L, live, b, T, su_l, beta_l);
   }
   double* tw = S.tw + p * kTile;
   if (plain_panel(beta_l)) {
@@ -615,11 +628,11 @@ __device__ __forceinline__ void pad_unit(const Lane& L, const int n, double (&b)
 // kStepPanels of a graded block, all of them where the solution is the result.
 // Starts with a barrier after which S.R is free to write; ends with one.
 template <int NT, int YN, int STEPS, class SM>
-__device__ __forceinline__ void block_qr(const Lane& L, SM& S, double (&b)[NT][4], double (*Y)[4]) {
+__device__ __forceinline__ void block_qr(const Lane& L, const int n, SM& S, double (&b)[NT][4], double (*Y)[4]) {
   __syncthreads();
 #pragma unroll 1
   for (int p = 0; p < NT; ++p) {
-    if (L.w == p) panel_factor<NT>(S, b, p);
+    if (L.w == p) panel_factor<NT>(S, b, p, n);
     __syncthreads();
     const double* vp = S.R + panel_off<NT, SM>(p);
     const double* tw = S.tw + p * kTile;

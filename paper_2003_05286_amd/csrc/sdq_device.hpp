@@ -1016,7 +1016,7 @@ __device__ __forceinline__ void inv_one_plus(const Lane& L, const int n, Smem<NT
   if constexpr (loh) {
     for (int t = L.t; t < n; t += G::THREADS) lsum += log(fmax(S.dcur[t], 1.0));
     pad_unit<NT>(L, n, M.v[0]);
-    block_qr<NT, 1, NT>(L, S, M.v[0], Z.v[0]);  // begins with a barrier
+    block_qr<NT, 1, NT>(L, n, S, M.v[0], Z.v[0]);  // begins with a barrier
     for (int t = L.t; t < n; t += G::THREADS) {
       const double d = S.red_diag[t];
       lsum += log(fabs(d));
@@ -1457,6 +1457,10 @@ __device__ __forceinline__ int jsvd_udt(const Lane& L, const int n, Smem<NT, P, 
 // three tiles on its growth test fails in every pass (R outgrows its diagonal
 // by 5 to 15 at n = 64 to 256), so it takes the pivoted QR at once.
 constexpr int kFirstPivotedNT = 3;
+// Chains of one or two sites are pivoted throughout: two steps cost less than
+// the sort (one chain of 100 slices, n = 1: 87 us against 111, n = 2: 97
+// against 111; n = 3: 108 against 112, n = 4: 120 against 111).
+constexpr int kTinyPivoted = 2;
 // Acceptance of a norm-sorted QR: R's rows may exceed its diagonal by this
 // factor (a pivoted QR's never do).  Up to kSortPasses attempts, each with
 // the columns in the order of the last one's diagonal, a column that exceeds a
@@ -1487,7 +1491,7 @@ constexpr int kSortPasses = 6;
 // S.sperm); keep_t takes the new T.
 template <int NT, bool ELDS, class SortT, class LoadT, class KeepT>
 __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>& S, RM<NT, NT>& Wm,
-                                                 double dcol, const bool first, double* sgn, double* wscr,
+                                                 double dcol, const bool pivot, double* sgn, double* wscr,
                                                  SortT sort_t, LoadT load_t, KeepT keep_t) {
   using G = Geo<NT, NT>;
   double(&W)[NT][4] = Wm.v[0];
@@ -1512,12 +1516,12 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
     const double ss = sum_col((sp[0] + sp[1]) + (sp[2] + sp[3]));
     scale = dcol * usc;
     key = sqrt(ss) * scale;
-    // (an ungraded first block straight to the pivoted QR: its columns in place)
-    if (first && L.g == 0) S.sperm[16 * L.w + L.cl] = 16 * L.w + L.cl;
+    // (straight to the pivoted QR: the columns in place)
+    if (pivot && L.g == 0) S.sperm[16 * L.w + L.cl] = 16 * L.w + L.cl;
   }
   bool sorted = false;
 #pragma unroll 1
-  for (int pass = 0; !first; ++pass) {
+  for (int pass = 0; !pivot; ++pass) {
     Lane L = lane_id_per_item();
     const int col = 16 * L.w + L.cl;
     const bool live = col < n;
@@ -1555,7 +1559,7 @@ __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>
     scale = S.dcur[col];
     scr_store<NT, NT>(L, Wm, wscr);
     sort_t();
-    block_qr<NT, 0, kStepPanels>(L, S, W, nullptr);
+    block_qr<NT, 0, kStepPanels>(L, n, S, W, nullptr);
     // growth test: |R_ic| <= gamma |R_ii| in the original scales (NaN fails it)
     L = lane_id_per_item();
     for (int t = L.t; t < G::NP; t += G::THREADS) S.dnew[t] = fabs(S.red_diag[t]) * S.dcur[t];
@@ -1796,11 +1800,12 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
       sgn_u = sgn_run * ps;
       sgn_run = sgn_u;
     } else if constexpr (FAST) {
-      const bool first = NT >= kFirstPivotedNT && s == s_lo && !(block && jpair > 0);
+      const bool pivot = (NT >= kFirstPivotedNT && s == s_lo && !(block && jpair > 0)) ||
+                         (NT == 1 && n <= kTinyPivoted);
       if constexpr (TG) {
         RM<NT, P> Tr;
         stabilize_sorted<NT, ELDS>(
-            n, S, W, dcol[0], first, &sgn_u, wscr, [] {},
+            n, S, W, dcol[0], pivot, &sgn_u, wscr, [] {},
             [&]() -> RM<NT, P>& {
               // rows in sorted order: from the scratch's register layout, from
               // forward stage jpair, or of the identity
@@ -1842,7 +1847,7 @@ __device__ __forceinline__ void sweep_one(const Lane& L, Smem<NT, P, ELDS>& S, c
             });
       } else {
         stabilize_sorted<NT, ELDS>(
-            n, S, W, dcol[0], first, &sgn_u, wscr,
+            n, S, W, dcol[0], pivot, &sgn_u, wscr,
             [&] {
               const Lane L = lane_id_per_item();
               const int base = (16 * L.w + L.cl) * G::LDR;
@@ -2262,7 +2267,7 @@ __device__ __forceinline__ void pair_middle(const Lane& L, Smem<NT, P, ELDS>& S,
   // Y <- Mid^{-1} Y through the blocked QR (any backward-stable solve of the
   // middle matrix serves, Sec. 6.1)
   pad_unit<NT>(L, n, P1.v[0]);
-  block_qr<NT, 1, NT>(L, S, P1.v[0], Y.v[0]);
+  block_qr<NT, 1, NT>(L, n, S, P1.v[0], Y.v[0]);
   block_back_subst<NT>(L, S, Y.v[0]);
   // G = U2 D_Rp^{-1} Y
 #pragma unroll
