@@ -12,14 +12,14 @@
 // kSortedGrowth).  Without a pivot search the QR is a sequence of
 // 16-column panels: the wave holding a panel factors it by itself, with no
 // barrier inside, and the other waves apply it as a compact WY block
-// reflector on MFMA.
+// reflector on MFMA (the first ones reflector by reflector: panel_steps).
 //
 // Bound by the panel's wave: it issues one instruction every 4.7 cycles
 // whatever they depend on, 350 / 490 / 660 cycles a step at 16 / 64 / 112
 // rows; two chains share a CU up to n = 64, so that one's panels run beside
-// the other's products (80 k cycles a block then, 50 k alone).  Sweeps with
-// pivoting in every step -> with this: one chain of n = 16 0.21 -> 0.10 ms,
-// 512 of n = 64 12.3 -> 7.3, 24 of n = 121 7.1 -> 4.4.
+// the other's products.  Sweeps with pivoting in every step -> with this: one
+// chain of n = 16 0.21 -> 0.11 ms, 96 of n = 49 1.49 -> 1.14, 512 of n = 64
+// 12.4 -> 7.5, 24 of n = 121 7.1 -> 4.6.
 //
 // LDS: panel q (columns 16q .. 16q+15) in S.R at q NP 16, one 16 x 16 tile
 // per row tile: R on and above the diagonal, the reflectors below it (their
@@ -189,20 +189,62 @@ __device__ __forceinline__ void axpy_tiles(double (&t0)[4], double (&t1)[4], dou
   asm("s_nop 1\n" SDQ_AX4(a) SDQ_AX4(b) : SDQ_IO4(a, t0), SDQ_IO4(b, t1) : [f] "v"(f), [J] "n"(J));
 }
 
-// p += sum of a[J] x over a tile and x += a[J] f for another matrix's rows x
+// p += sum of a[J] x over one or two tiles and x += a[J] f, for another
+// matrix's rows x; a lane exchange may follow dot_with after dot_done only
+#define SDQ_DW(X, Y) SDQ_FD("%[p]", "%[" #X "]", "%[" #Y "]", "%[J]", "0xf")
+#define SDQ_AW(X, Y) SDQ_FD("%[" #Y "]", "%[" #X "]", "%[f]", "%[J]", "0xf")
+#define SDQ_W4(OP, A, X) OP(A##0, X##0) OP(A##1, X##1) OP(A##2, X##2) OP(A##3, X##3)
 template <int J>
 __device__ __forceinline__ void dot_with(double& p, const double (&a)[4], const double (&x)[4]) {
-  asm("s_nop 1\n" SDQ_FD("%[p]", "%[a0]", "%[x0]", "%[J]", "0xf") SDQ_FD("%[p]", "%[a1]", "%[x1]", "%[J]", "0xf")
-          SDQ_FD("%[p]", "%[a2]", "%[x2]", "%[J]", "0xf") SDQ_FD("%[p]", "%[a3]", "%[x3]", "%[J]", "0xf") "s_nop 1"
-      : [p] "+v"(p)
-      : [J] "n"(J), SDQ_IN4(a, a), SDQ_IN4(x, x));
+  asm("s_nop 1\n" SDQ_W4(SDQ_DW, a, x) : [p] "+v"(p) : [J] "n"(J), SDQ_IN4(a, a), SDQ_IN4(x, x));
 }
 template <int J>
+__device__ __forceinline__ void dot_with(double& p, const double (&a)[4], const double (&x)[4], const double (&b)[4],
+                                         const double (&y)[4]) {
+  asm("s_nop 1\n" SDQ_W4(SDQ_DW, a, x) SDQ_W4(SDQ_DW, b, y)
+      : [p] "+v"(p)
+      : [J] "n"(J), SDQ_IN4(a, a), SDQ_IN4(x, x), SDQ_IN4(b, b), SDQ_IN4(y, y));
+}
+__device__ __forceinline__ void dot_done(double& p) { asm("s_nop 1" : "+v"(p)); }
+template <int J>
 __device__ __forceinline__ void axpy_with(double (&x)[4], const double (&a)[4], double f) {
-  asm("s_nop 1\n" SDQ_FD("%[x0]", "%[a0]", "%[f]", "%[J]", "0xf") SDQ_FD("%[x1]", "%[a1]", "%[f]", "%[J]", "0xf")
-          SDQ_FD("%[x2]", "%[a2]", "%[f]", "%[J]", "0xf") SDQ_FD("%[x3]", "%[a3]", "%[f]", "%[J]", "0xf") "s_nop 1"
-      : SDQ_IO4(x, x)
-      : [J] "n"(J), SDQ_IN4(a, a), [f] "v"(f));
+  asm("s_nop 1\n" SDQ_W4(SDQ_AW, a, x) : SDQ_IO4(x, x) : [J] "n"(J), SDQ_IN4(a, a), [f] "v"(f));
+}
+template <int J>
+__device__ __forceinline__ void axpy_with(double (&x)[4], const double (&a)[4], double (&y)[4], const double (&b)[4],
+                                          double f) {
+  asm("s_nop 1\n" SDQ_W4(SDQ_AW, a, x) SDQ_W4(SDQ_AW, b, y)
+      : SDQ_IO4(x, x), SDQ_IO4(y, y)
+      : [J] "n"(J), SDQ_IN4(a, a), SDQ_IN4(b, b), [f] "v"(f));
+}
+// the same over NT tiles, and the rows' last write two wait states before a
+// matrix instruction may read them
+template <int J, int NT>
+__device__ __forceinline__ double dot_rows(const double (&a)[NT][4], const double (&x)[NT][4]) {
+  double p = 0.0;
+  static_for<NT / 2>([&](auto tc) {
+    constexpr int t = 2 * decltype(tc)::value;
+    dot_with<J>(p, a[t], x[t], a[t + 1], x[t + 1]);
+  });
+  if constexpr (NT % 2 == 1) dot_with<J>(p, a[NT - 1], x[NT - 1]);
+  dot_done(p);
+  return p;
+}
+template <int J, int NT>
+__device__ __forceinline__ void axpy_rows(double (&x)[NT][4], const double (&a)[NT][4], double f) {
+  static_for<NT / 2>([&](auto tc) {
+    constexpr int t = 2 * decltype(tc)::value;
+    axpy_with<J>(x[t], a[t], x[t + 1], a[t + 1], f);
+  });
+  if constexpr (NT % 2 == 1) axpy_with<J>(x[NT - 1], a[NT - 1], f);
+}
+template <int NT>
+__device__ __forceinline__ void rows_done(double (&x)[NT][4]) {
+#pragma unroll
+  for (int t = 0; t < NT; ++t) asm volatile("" : SDQ_IO4(a, x[t]));
+  asm volatile("s_nop 1");
+#pragma unroll
+  for (int t = 0; t < NT; ++t) asm volatile("" : SDQ_IO4(a, x[t]));
 }
 // rows that matrix instructions may have written just before: let them land
 // before inline assembly reads them (18 wait states)
@@ -503,7 +545,7 @@ __device__ __forceinline__ void panel_apply(double (&b)[NT][4], const int cnt, c
 // reflector's coefficients all carry the error of the column as it came.  The
 // columns of a product of slices shrink most in the first panels
 // (kStepPanels; with none the errors are 1.2 to 1.5 times those of pivoting,
-// more than two change nothing).  A step takes some 45 instructions at 64 rows;
+// more than two change nothing).  A step takes some 50 instructions at 64 rows;
 // 512 chains of n = 64 take 1 % longer with it.
 template <int NT>
 __device__ __forceinline__ void panel_steps(double (&b)[NT][4], const int cnt, const double* vp, const double* tw,
@@ -522,13 +564,10 @@ __device__ __forceinline__ void panel_steps(double (&b)[NT][4], const int cnt, c
   rows_landed<NT>(b);
   static_for<16>([&](auto jc) {
     constexpr int J = decltype(jc)::value;
-    double p = 0.0;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) dot_with<J>(p, a[t], b[t]);
-    const double f = -bcast_col<J>(cd) * sum_col(p);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) axpy_with<J>(b[t], a[t], f);
+    const double f = -bcast_col<J>(cd) * sum_col(dot_rows<J>(a, b));
+    axpy_rows<J>(b, a, f);
   });
+  rows_done(b);
 }
 
 // row tiles one up (the first becomes the last) / one down

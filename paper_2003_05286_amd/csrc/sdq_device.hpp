@@ -19,7 +19,7 @@
 //   * the slice products W <- E diag(v) W run back to back on MFMA with the
 //     previous product as the B operand (no LDS round trip, no barrier),
 //   * the blocked QR take its panels and apply their compact-WY reflectors
-//     (MFMA again) to the same registers, two barriers per 16 columns, and
+//     (MFMA again) to the same registers, one barrier per 16 columns, and
 //     the pivoted Householder QR, where the factors themselves are the
 //     result, work on them too: column norms and reflector dot products are
 //     lane-local sums plus two cross-row shuffles; the pivot column is
@@ -2186,9 +2186,11 @@ __device__ __forceinline__ void tdisp_outputs(const Lane& L, Smem<NT, P, ELDS>& 
 // EQUAL: the equal-time G at the same boundary,
 //   [1 + B(tau,0) B(beta,tau)]^{-1} = U2 D_Rp^{-1} Mid^{-1} D_Lm U1^T
 // with the same middle matrix (App. A.1's two factors split as in Sec. 5.1).
-// Mid is solved through the blocked QR: bound by its panels as the sweep's;
-// 20480 pairs of n = 64 2.51 ms, 3.77 with the column-pivoted elimination that
-// took a barrier per column (n = 121: 1.45 both ways, 24 chains).
+// Mid is solved through the blocked QR, its panels applied a reflector at a
+// time (a block reflector's errors would show in G(tau,0), 5 % at k = 5): bound
+// by the panels as the sweep; 20480 pairs of n = 64 2.76 ms, 3.76 with the
+// column-pivoted elimination that took a barrier per column (n = 121, 24 chains:
+// 1.46 and 1.44).
 template <int NT, int P, bool ELDS, bool EQUAL>
 __device__ __forceinline__ void pair_middle(const Lane& L, Smem<NT, P, ELDS>& S, const Inst& I, const int j,
                                             RM<NT, P>& Gm) {

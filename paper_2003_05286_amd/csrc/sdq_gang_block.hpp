@@ -13,8 +13,8 @@
 //
 // Bound by the chain of panels: 28 k cycles to factor and publish one at n =
 // 256 (16.7 k in its 16 steps, 9 k storing), 20 k for the next owner to apply
-// it.  Against a pivot per column: sweeps 237 -> 91 ms at n = 256 (64 chains)
-// and 458 -> 157 at n = 1024, pairs 159 -> 33 and 128 -> 14.
+// it.  Against a pivot per column: sweeps 237 -> 92 ms at n = 256 (64 chains)
+// and 459 -> 158 at n = 1024, pairs 161 -> 34 and 129 -> 14.
 //
 // Published per panel p, in the gang's scratch: the reflectors (su on the
 // diagonal, zero above) as row-major 16-column rows and once more in the
@@ -402,17 +402,13 @@ __device__ __attribute__((noinline)) void gang_apply_steps(const GC& c, int p, i
   static_for<16>([&](auto jc) {
     constexpr int J = decltype(jc)::value;
     double* pr = L.xbuf + (J & 1) * 256;
-    double q = 0.0;
-#pragma unroll
-    for (int i = 0; i < kApplyTiles; ++i) dot_with<J>(q, a[i], x[i]);
-    q = sum_col(q);
+    const double q = sum_col(dot_rows<J>(a, x));
     if (ln.g == 0) pr[ln.w * 16 + ln.cl] = q;
     __syncthreads();
     double s = 0.0;
     for (int u = ln.g; u < ks; u += 4) s += pr[(min(cti, nct - 1) * ks + u) * 16 + ln.cl];
     const double f = -bcast_col<J>(cd) * sum_col(s);
-#pragma unroll
-    for (int i = 0; i < kApplyTiles; ++i) axpy_with<J>(x[i], a[i], f);
+    axpy_rows<J>(x, a, f);
   });
 #pragma unroll
   for (int i = 0; i < kApplyTiles; ++i)

@@ -490,9 +490,9 @@ sdq_status build_plan(sdq_ctx* ctx, Plan& P, int32_t* status, int count, Built& 
     // block products, variant 6)
     const bool bprod = ((P.bprod_mask >> r.nt) & 1u) != 0;
     // The norm-sorted blocked QR wherever the factors are not themselves the
-    // result: against the pivoted sweeps 12.3 -> 7.3 ms at n = 64 (512
-    // chains), 7.1 -> 4.4 at n = 121 (24), 29.7 -> 15.3 at n = 144 (among 512),
-    // 0.21 -> 0.10 for one chain of n = 16.
+    // result: against the pivoted sweeps 12.4 -> 7.5 ms at n = 64 (512
+    // chains), 7.1 -> 4.6 at n = 121 (24), 29.7 -> 9.9 at n = 144 (among 512),
+    // 0.21 -> 0.11 for one chain of n = 16.
     // (Dense slices have the QR only, whatever the context's stabilizer.)
     const bool fast =
         !P.pivoted && (P.dense || ctx->stab == SDQ_STAB_QR) && r.nt <= sdq::kSweepMaxNT;
