@@ -1471,13 +1471,14 @@ constexpr int kTinyPivoted = 2;
 // of a second factorization.
 // Errors of G and G(tau, 0) against extended precision (64-bit mantissas;
 // n = 9 .. 144, k = 5 .. 10, 8 to 64 chains a size), as geometric means over
-// what the column-pivoted kernels reach: 0.96 (k = 10) and 1.06 (k = 5) with
-// this bound, 0.98 and 1.09 with 4, up to 70 without a test (a chain's first
-// blocks, whose columns are not graded yet); 1.36 and 1.59 with 4 before the
-// columns were kept and the first panels applied a reflector at a time.  A
+// what the column-pivoted kernels reach: 0.98 (k = 8, 10) and 1.06 (k = 5, 7)
+// with this bound, 1.00 with 4 (k = 8, 10), up to 70 without a test (a chain's
+// first blocks, whose columns are not graded yet); 1.36 and 1.59 with 4 before
+// the columns were kept and the first panels applied a reflector at a time.  A
 // block takes 1.05 to 1.2 factorizations with 4, 1.15 to 1.6 with 2 (512
-// chains of n = 64 2 % longer, 96 of n = 49 7 %).  No block of a physical chain
-// needed the pivoted QR (n up to 576).
+// chains of n = 64 2 % longer, 96 of n = 49 7 %).  Of 15 000 blocks of Hubbard
+// chains (n = 9 .. 144, U = 2 .. 8) one in eleven sorts again, up to five times,
+// and none gives up.
 constexpr double kSortedGrowth = 2.0;
 constexpr int kSortPasses = 6;
 
