@@ -322,10 +322,11 @@ __device__ __forceinline__ void sum_and_pick(double p, double x, bool in_g0, dou
 // the matrix are zero).  The reflector of column J is kept unscaled,
 // v_J = (su at row J; column J below it), H = I - c v v^T with
 // h = ||x||, su = alpha + sign(alpha) h, c = 2 / v^T v (of the rounded v: from
-// h it would leave H further from orthogonal), and always
-// reflects (a column with nothing below row J changes sign), so that only a
-// column of zeros, or one whose squares leave the range of a double, is a
-// special case: plain_panel (the caller looks at beta) and panel_careful.  On return b holds R above the diagonal, the reflectors below
+// h it would leave H further from orthogonal), and always reflects (a column
+// with nothing below row J changes sign), so that only a column of zeros, or
+// one whose squares leave the range of a double, is a special case: the caller
+// looks at beta (plain_panel) and takes panel_careful for those.
+// On return b holds R above the diagonal, the reflectors below
 // it and alpha on it; su_l, beta_l the reflector's and R's diagonal entry of
 // the lane's column; T row cl of the triangular factor.  Columns from `live`
 // on are unit vectors (padding): of a one-tile matrix, groups of four such steps
@@ -416,8 +417,8 @@ __device__ __forceinline__ void wave_fence() {
 // reflector stays so; R's entry is scaled back), and a column of zeros reflects
 // its first entry: v = e_J, c = 2, so that every column's reflector reflects.
 // Entry (i, c), 0 <= i < rows, at x: in panel layout, or (ld > 0) at c ld + i;
-// R with its diagonal on return.  tw: the triangular factor, a tile or (ld > 0) row-major;
-// su_l: the diagonal of the lane's reflector.
+// R with its diagonal on return.  tw: the triangular factor, a tile or (ld > 0)
+// row-major; su_l: the diagonal of the lane's reflector.
 // Reached by middle matrices that are singular or far from one in size (and by
 // NaN); a row at a time, as slow as that is.
 struct CarefulDiag {

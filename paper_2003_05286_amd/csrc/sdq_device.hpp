@@ -1489,7 +1489,8 @@ constexpr int kSortPasses = 6;
 // norm of W D and factorized as they stand; T's rows follow the sort and take
 // the scales.  T is in registers (sort_t moves its rows while the factor store
 // is free) or in the workgroup's scratch (load_t gathers its rows in the order
-// S.sperm); keep_t takes the new T.
+// S.sperm); keep_t takes the new T.  wscr: the workgroup's scratch for the
+// sorted columns; pivot: no sort, the pivoted QR at once.
 template <int NT, bool ELDS, class SortT, class LoadT, class KeepT>
 __device__ __forceinline__ void stabilize_sorted(const int n, Smem<NT, NT, ELDS>& S, RM<NT, NT>& Wm,
                                                  double dcol, const bool pivot, double* sgn, double* wscr,
